@@ -93,6 +93,10 @@ struct AxisTaps {
 // of each voxel ([6][N] FP32) and nothing else.
 constexpr int kHessianOut = 16;
 
+// Layout parameter of the fixed-radius feature kernels whose storage type and layout are run-time
+// values (XYArgs::odt, XYArgs::layout).
+constexpr int kAnyOut = 17;
+
 struct ScaleTaps {
     AxisTaps ax[3];  // x, y, z
     float sigma2;    // sigma^2 (mm^2): scale normalization of the Hessian for the eigenvalues

@@ -11,11 +11,13 @@
 // keep it at a few 1e-7.
 //
 // Two kernels per scale:
-//   k_zpass   one voxel per lane: (Gz, D1z, D2z) of I along z -> workspace, 12 B/voxel;
-//   k_xypass  one 64 x 8 (x, y) tile of one z slice per 256-lane workgroup: the three z-filtered
+//   k_zpass_r   a run of 16 slices per lane: (Gz, D1z, D2z) of I along z -> workspace, 12 B/voxel;
+//   k_xypass_r  one 64 x 8 (x, y) tile of one z slice per 256-lane workgroup: the three z-filtered
 //             fields of the tile plus halo are staged in LDS, the y filters produce six fields
 //             (kept in LDS), the x filters give H per voxel, and the epilogue computes the
 //             gradient (first scale), |g|_max, k, the eigenvalues of sigma^2 H and V.
+// Both take the stencil radius (2..15, every radius there is) as a template parameter; only a volume
+// whose in-plane spacings give x and y different radii takes the run-time-radius tile (k_xypass).
 #include <math.h>
 
 #include "common.hpp"
@@ -23,22 +25,15 @@
 
 namespace dvr {
 
-// z pass: (Gz, D1z, D2z) of I for every voxel.  The grid covers each z plane in 256-voxel runs
-// (blockIdx.x) and the planes (blockIdx.y), so lanes read consecutive x and the boundary class of
-// z is uniform per workgroup.
-template <int DT>
-__global__ __launch_bounds__(256) void k_zpass(const void *__restrict__ vol, float *__restrict__ ws, int nx, int ny,
-                                               int nz, AxisTaps tz)
-{
-    const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
-    const uint32_t e = blockIdx.x * 256u + threadIdx.x;
-    if (e >= plane) return;
-    zpass_voxel<DT>(vol, ws, nx, ny, nz, tz, e, (int)blockIdx.y);
-}
+// Stencil radii of the fixed-radius kernels: every radius a Gaussian of radius 1 .. DVR_MAX_RADIUS gives.
+// At radius 13 (three scales on a 149 x 193 x 224 volume) the tile below takes 0.16 ms a scale where the
+// run-time radius of k_xypass took 1.19.
+constexpr int kRFastMin = 2, kRFastMax = DVR_MAX_RADIUS + 1;
 
-// Fixed-radius z pass: a lane takes TZ consecutive voxels of one (x, y) column and keeps the
-// TZ + 2R inputs it needs in registers, so each input is loaded (TZ + 2R) / TZ times instead of
-// 2R + 1 times.
+// z pass, (Gz, D1z, D2z) of I for every voxel: a lane takes TZ consecutive voxels of one (x, y) column
+// and keeps the TZ + 2R inputs it needs in registers, so each input is loaded (TZ + 2R) / TZ times
+// instead of 2R + 1 times.  The grid covers each z plane in 256-voxel runs (blockIdx.x, so lanes read
+// consecutive x) and the runs of TZ planes (blockIdx.y).
 template <int DT, int R, int TZ>
 __global__ __launch_bounds__(256) void k_zpass_r(const void *__restrict__ vol, float *__restrict__ ws, int nx, int ny,
                                                  int nz, AxisTaps tz)
@@ -70,7 +65,7 @@ constexpr int kTZ = 16;  // slices per lane of the fixed-radius z pass (8: 2-16 
 template <int DT, int R>
 static hipError_t launch_z_r(const void *vol, float *ws, const dvr_grid &g, const AxisTaps &tz, hipStream_t st)
 {
-    if constexpr (R > 10) {
+    if constexpr (R > kRFastMax) {
         return hipErrorInvalidValue;
     } else {
         if (tz.R != R) return launch_z_r<DT, R + 1>(vol, ws, g, tz, st);
@@ -126,8 +121,6 @@ __global__ __launch_bounds__(NT, (R >= 6 && R <= 9) ? 6 : 1) void k_xypass_r(XYA
         if ((threadIdx.x & 63) == 0) atomic_max_pos(a.fro_pass ? a.fro : a.gmax, vmax);
     }
 }
-
-constexpr int kRFastMin = 2, kRFastMax = 10;
 
 template <int DT, int OUT_DT, int LAYOUT, int R>
 static hipError_t launch_xy_r(const XYArgs &a, const ScaleTaps &taps, hipStream_t st)
@@ -247,25 +240,17 @@ static hipError_t launch_xy(const XYArgs &a, const ScaleTaps &taps, hipStream_t 
     return hipGetLastError();
 }
 
-static hipError_t launch_z_any(const void *vol, int vol_dt, const dvr_grid &g, const AxisTaps &tz, float *ws_fields,
-                               hipStream_t st)
+static hipError_t launch_z(const void *vol, int vol_dt, const dvr_grid &g, const AxisTaps &tz, float *ws_fields,
+                           hipStream_t st)
 {
-    if (tz.R >= 2 && tz.R <= 10)
-        return (vol_dt == DVR_F32) ? launch_z_r<DVR_F32, 2>(vol, ws_fields, g, tz, st)
-                                   : launch_z_r<DVR_F16, 2>(vol, ws_fields, g, tz, st);
-    const uint32_t plane = (uint32_t)g.nx * (uint32_t)g.ny;
-    dim3 zgrid((plane + 255) / 256, g.nz);
-    if (vol_dt == DVR_F32)
-        hipLaunchKernelGGL(k_zpass<DVR_F32>, zgrid, dim3(256), 0, st, vol, ws_fields, g.nx, g.ny, g.nz, tz);
-    else
-        hipLaunchKernelGGL(k_zpass<DVR_F16>, zgrid, dim3(256), 0, st, vol, ws_fields, g.nx, g.ny, g.nz, tz);
-    return hipGetLastError();
+    return (vol_dt == DVR_F32) ? launch_z_r<DVR_F32, kRFastMin>(vol, ws_fields, g, tz, st)
+                               : launch_z_r<DVR_F16, kRFastMin>(vol, ws_fields, g, tz, st);
 }
 
 hipError_t launch_hessian(const void *vol, int vol_dt, const dvr_grid &g, const ScaleTaps &taps, float *ws_fields,
                           float *H, hipStream_t st)
 {
-    hipError_t e = launch_z_any(vol, vol_dt, g, taps.ax[2], ws_fields, st);
+    hipError_t e = launch_z(vol, vol_dt, g, taps.ax[2], ws_fields, st);
     if (e != hipSuccess) return e;
     XYArgs a = {};
     a.ws = ws_fields;
@@ -277,7 +262,7 @@ hipError_t launch_hessian(const void *vol, int vol_dt, const dvr_grid &g, const 
     a.first = 0;
     a.fro_pass = 0;
     const int R = taps.ax[0].R;
-    if (R == taps.ax[1].R && R >= kRFastMin && R <= kRFastMax)
+    if (R == taps.ax[1].R)
         return (vol_dt == DVR_F32) ? launch_xy_r<DVR_F32, DVR_F32, kHessianOut, kRFastMin>(a, taps, st)
                                    : launch_xy_r<DVR_F16, DVR_F32, kHessianOut, kRFastMin>(a, taps, st);
     if (vol_dt == DVR_F32) return launch_xy<DVR_F32, DVR_F32, kHessianOut>(a, taps, st);
@@ -290,19 +275,7 @@ hipError_t launch_features_scale(const void *vol, int vol_dt, const dvr_grid &g,
                                  bool fro_pass, hipStream_t st)
 {
     (void)last_scale;
-    const uint32_t plane = (uint32_t)g.nx * (uint32_t)g.ny;
-    dim3 zgrid((plane + 255) / 256, g.nz);
-    hipError_t e;
-    if (taps.ax[2].R >= 2 && taps.ax[2].R <= 10) {
-        e = (vol_dt == DVR_F32) ? launch_z_r<DVR_F32, 2>(vol, ws_fields, g, taps.ax[2], st)
-                                : launch_z_r<DVR_F16, 2>(vol, ws_fields, g, taps.ax[2], st);
-    } else {
-        if (vol_dt == DVR_F32)
-            hipLaunchKernelGGL(k_zpass<DVR_F32>, zgrid, dim3(256), 0, st, vol, ws_fields, g.nx, g.ny, g.nz, taps.ax[2]);
-        else
-            hipLaunchKernelGGL(k_zpass<DVR_F16>, zgrid, dim3(256), 0, st, vol, ws_fields, g.nx, g.ny, g.nz, taps.ax[2]);
-        e = hipGetLastError();
-    }
+    hipError_t e = launch_z(vol, vol_dt, g, taps.ax[2], ws_fields, st);
     if (e != hipSuccess) return e;
 
     XYArgs a;
@@ -326,8 +299,12 @@ hipError_t launch_features_scale(const void *vol, int vol_dt, const dvr_grid &g,
     a.first = (scale_index == 0) && !fro_pass;
     a.fro_pass = fro_pass;
     const int odt = out.dtype, lay = out.layout;
-    const int R = taps.ax[0].R;
-    if (R == taps.ax[1].R && R >= kRFastMin && R <= kRFastMax) {
+    a.odt = odt;
+    a.layout = lay;
+    if (taps.ax[0].R == taps.ax[1].R) {
+        // the layouts that are rendered most have kernels of their own; the others share one whose
+        // storage type and layout are run-time values (2-11 % slower than its own kernel where both
+        // exist, 1.4-1.8x faster per call than the run-time-radius tile they took before)
         if (vol_dt == DVR_F32 && odt == DVR_F32 && lay == DVR_PLANAR)
             return launch_xy_r<DVR_F32, DVR_F32, DVR_PLANAR, kRFastMin>(a, taps, st);
         if (vol_dt == DVR_F16 && odt == DVR_F16 && lay == DVR_INTERLEAVED)
@@ -336,7 +313,10 @@ hipError_t launch_features_scale(const void *vol, int vol_dt, const dvr_grid &g,
             return launch_xy_r<DVR_F32, DVR_F32, DVR_SPLIT, kRFastMin>(a, taps, st);
         if (vol_dt == DVR_F16 && odt == DVR_F16 && lay == DVR_SPLIT)
             return launch_xy_r<DVR_F16, DVR_F16, DVR_SPLIT, kRFastMin>(a, taps, st);
+        return (vol_dt == DVR_F32) ? launch_xy_r<DVR_F32, DVR_F32, kAnyOut, kRFastMin>(a, taps, st)
+                                   : launch_xy_r<DVR_F16, DVR_F32, kAnyOut, kRFastMin>(a, taps, st);
     }
+    // in-plane spacings so unequal that the radii differ: the run-time-radius tile
 #define DVR_XY(D, O, L) \
     if (vol_dt == D && odt == O && lay == L) return launch_xy<D, O, L>(a, taps, st);
     DVR_XY(DVR_F32, DVR_F32, DVR_PLANAR)

@@ -15,8 +15,9 @@
 //      a Jacobi eigen-decomposition (those voxels listed over the workgroup's 1024 and solved one per
 //      lane); at the first scale it also writes dL/dg + dL/dk dk/dg and the arg-max key of |g|;
 //   2. the x, y and z transposes apply the transposed operators (the forward's z-then-y-then-x order
-//      reversed: six fields after x, three after y, one accumulated into dL/dI after z): for radii
-//      2..10 k_tx_lds_r, k_ty_run_r, k_tz_run_r, else k_tx_lds (k_tx), k_ty_run, k_tz_run.
+//      reversed: six fields after x, three after y, one accumulated into dL/dI after z):
+//      k_tx_lds_r (k_tx for rows of more chunks than a grid holds), k_ty_run_r, k_tz_run_r, with the
+//      stencil radius a template parameter.
 // Last, dL/d|g|_max goes to the arg-max voxel's gradient (k_fb_gmax) and the transposed central
 // difference of the gradient is added (k_fb_gradT).
 //
@@ -28,6 +29,8 @@
 #include "features_dev.hpp"
 
 namespace dvr {
+
+constexpr int kRMax = DVR_MAX_RADIUS + 1;  // the largest stencil radius (the smallest is 2)
 
 // B[f][d + R][i]: weight of input i + d in output i of operator f (0: G, 1: D1 G, 2: D2 G) along an
 // axis of n voxels; clamped taps fold onto the end voxels, the first and last rows are one-sided.
@@ -406,65 +409,12 @@ __global__ __launch_bounds__(256) void k_tx(const float *__restrict__ Hb, float 
 // y + ny z, blockIdx.y = chunk): the six fields of the chunk and its R-voxel halo are staged in LDS
 // once, instead of 6 (2R + 1) global loads per output.  An output whose contributing forward rows
 // i in [x - R, x + R] all lie in [R, nx - 1 - R] (no clamped or one-sided taps) takes the weights from
-// the taps themselves, which is what the band table holds there (a single tap per entry); the
-// others read the band table.  Same products in the same order as k_tx: the same bits.
+// the taps themselves, which is what the band table holds there (a single tap per entry): its 2R + 1
+// taps are unrolled (offset m = x - i from R down to -R: the rows in ascending order), the weights
+// are compile-time-indexed kernel arguments held in scalar registers and the LDS reads take
+// immediate offsets.  The others loop over the band table.  Same products in the same order as k_tx:
+// the same bits.
 constexpr int kTxChunk = 256;
-__global__ __launch_bounds__(256) void k_tx_lds(const float *__restrict__ Hb, float *__restrict__ X,
-                                                const float *__restrict__ B, AxisTaps t, int nx, int ny, int nz)
-{
-    __shared__ float s[6][kTxChunk + 2 * (DVR_MAX_RADIUS + 1)];
-    __shared__ float tg[DVR_MAX_RADIUS + 2], td1[DVR_MAX_RADIUS + 2], td2[DVR_MAX_RADIUS + 2];
-    const int R = t.R, W = 2 * R + 1;
-    const size_t N = (size_t)nx * (size_t)ny * (size_t)nz;
-    const size_t rbase = (size_t)blockIdx.x * (size_t)nx;
-    const int x0 = (int)blockIdx.y * kTxChunk;
-    const int lo = max(0, x0 - R), hi = min(nx, x0 + kTxChunk + R);
-    for (int p = (int)threadIdx.x; p < hi - lo; p += 256) {
-#pragma unroll
-        for (int f = 0; f < 6; ++f) s[f][p] = Hb[(size_t)f * N + rbase + (size_t)(lo + p)];
-    }
-    if (threadIdx.x <= (unsigned)R) {
-        tg[threadIdx.x] = t.G[threadIdx.x];
-        td1[threadIdx.x] = t.D1[threadIdx.x];
-        td2[threadIdx.x] = t.D2[threadIdx.x];
-    }
-    __syncthreads();
-    const int x = x0 + (int)threadIdx.x;
-    if (x >= nx) return;
-    const bool interior = x - 2 * R >= 0 && x + 2 * R <= nx - 1;
-    float acc[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const int i0 = max(0, x - R), i1 = min(nx - 1, x + R);
-    for (int i = i0; i <= i1; ++i) {
-        const int d = x - i + R;
-        float b0, b1, b2;
-        if (interior) {
-            const int m = x - i, am = m < 0 ? -m : m;
-            b0 = tg[am];
-            b1 = m > 0 ? td1[am] : (m < 0 ? -td1[am] : 0.f);
-            b2 = td2[am];
-        } else {
-            b0 = B[(size_t)d * nx + i];
-            b1 = B[(size_t)(W + d) * nx + i];
-            b2 = B[(size_t)(2 * W + d) * nx + i];
-        }
-        const int li = i - lo;
-        acc[0] = fmaf(b2, s[0][li], acc[0]);
-        acc[1] = fmaf(b0, s[1][li], acc[1]);
-        acc[2] = fmaf(b0, s[2][li], acc[2]);
-        acc[3] = fmaf(b1, s[3][li], acc[3]);
-        acc[4] = fmaf(b1, s[4][li], acc[4]);
-        acc[5] = fmaf(b0, s[5][li], acc[5]);
-    }
-    const size_t o = rbase + (size_t)x;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) X[(size_t)k * N + o] = acc[k];
-}
-
-// Fixed-radius form of k_tx_lds for the radii of the forward's fixed-radius kernels: an interior
-// output unrolls its 2R + 1 taps (offset m = x - i from R down to -R: the rows in ascending order),
-// so its weights are compile-time-indexed kernel arguments held in scalar registers and its LDS
-// reads take immediate offsets; the others loop over the band table as k_tx_lds does.  The same
-// products in the same order: the same bits.
 template <int R>
 __global__ __launch_bounds__(256) void k_tx_lds_r(const float *__restrict__ Hb, float *__restrict__ X,
                                                   const float *__restrict__ B, AxisTaps t, int nx, int ny, int nz)
@@ -517,120 +467,33 @@ __global__ __launch_bounds__(256) void k_tx_lds_r(const float *__restrict__ Hb, 
     for (int k = 0; k < 6; ++k) X[(size_t)k * N + o] = acc[k];
 }
 
-// the fixed-radius x transpose for radii 2..10, else the generic one
 template <int R>
 static void launch_tx_lds(const float *Hb, float *X, const float *B, const AxisTaps &t, const dvr_grid &g,
                           unsigned xchunks, hipStream_t st)
 {
-    if constexpr (R > 10) {
-        hipLaunchKernelGGL(k_tx_lds, dim3((unsigned)g.ny * (unsigned)g.nz, xchunks), dim3(256), 0, st, Hb, X, B, t,
-                           g.nx, g.ny, g.nz);
-    } else {
+    if constexpr (R <= kRMax) {
         if (t.R != R) return launch_tx_lds<R + 1>(Hb, X, B, t, g, xchunks, st);
         hipLaunchKernelGGL(k_tx_lds_r<R>, dim3((unsigned)g.ny * (unsigned)g.nz, xchunks), dim3(256), 0, st, Hb, X, B,
                            t, g.nx, g.ny, g.nz);
     }
 }
 
-// y and z: each lane walks a run of kTRun consecutive outputs along the axis at one position of the
-// other two (k_ty_run: blockIdx.y = run, blockIdx.z = z; k_tz_run: blockIdx.y = run), so every input
-// row along the axis is loaded once per run rather than once per output it reaches (2R + 1 times:
-// those re-reads through the caches bound a one-output-per-lane form).  Each output sums the rows i
-// of its band in ascending order.  The band-table reads are uniform over the workgroup.
+// y and z: each lane walks a run of K consecutive outputs along the axis at one position of the other
+// two (k_ty_run_r: blockIdx.y = run, blockIdx.z = z-slices; k_tz_run_r: blockIdx.y = run), so every
+// input row along the axis is loaded once per run rather than once per output it reaches (2R + 1
+// times: those re-reads through the caches bound a one-output-per-lane form).  Each output sums the
+// rows i of its band in ascending order.  The walk over the K + 2R input rows of a run is unrolled:
+// row j of the run (i = start - R + j) reaches outputs q with j - 2R <= q <= j at band offset
+// d = q - j + 2R, both known at compile time, so only the axis ends and the run's ragged tail are
+// tested at run time.  The band-table reads are uniform over a wave.
 //
 // y: the three z-groups: Y0 = G^T X_xx + (D2 G)^T X_yy + (D1 G)^T X_xy (z operator G),
-// Y1 = G^T X_xz + (D1 G)^T X_yz (z operator D1 G), Y2 = G^T X_zz (z operator D2 G)
-constexpr int kTyRun = 8, kTzRun = 4;
-// waves per workgroup of the fixed-radius y and z transposes (y: one z-slice each; z: consecutive
-// stretches of 64 plane positions): one-wave workgroups are limited by the workgroup slots of a CU
+// Y1 = G^T X_xz + (D1 G)^T X_yz (z operator D1 G), Y2 = G^T X_zz (z operator D2 G);
+// z: dL/dI += G^T Y0 + (D1 G)^T Y1 + (D2 G)^T Y2 along z.
+//
+// Waves per workgroup (y: one z-slice each; z: consecutive stretches of 64 plane positions):
+// one-wave workgroups are limited by the workgroup slots of a CU.
 constexpr int kTWaves = 4;
-template <int kTRun>
-__global__ __launch_bounds__(64) void k_ty_run(const float *__restrict__ X, float *__restrict__ Y,
-                                               const float *__restrict__ B, int nx, int ny, int nz, int R)
-{
-    const int x = (int)(blockIdx.x * 64u + threadIdx.x);
-    if (x >= nx) return;
-    const int yb = (int)blockIdx.y * kTRun, z = (int)blockIdx.z;
-    const int nq = min(kTRun, ny - yb);
-    const size_t plane = (size_t)nx * (size_t)ny, N = plane * (size_t)nz;
-    const size_t col = (size_t)z * plane + (size_t)x;
-    const int W = 2 * R + 1;
-    float y0[kTRun], y1[kTRun], y2[kTRun];
-#pragma unroll
-    for (int q = 0; q < kTRun; ++q) y0[q] = y1[q] = y2[q] = 0.f;
-    const int i0 = max(0, yb - R), i1 = min(ny - 1, yb + nq - 1 + R);
-#pragma unroll 2
-    for (int i = i0; i <= i1; ++i) {
-        const size_t sidx = col + (size_t)i * nx;
-        const float x0 = X[sidx], x1 = X[N + sidx], x2 = X[2 * N + sidx];
-        const float x3 = X[3 * N + sidx], x4 = X[4 * N + sidx], x5 = X[5 * N + sidx];
-#pragma unroll
-        for (int q = 0; q < kTRun; ++q) {
-            const int d = yb + q - i + R;
-            if (q < nq && d >= 0 && d < W) {
-                const float b0 = B[(size_t)d * ny + i], b1 = B[(size_t)(W + d) * ny + i];
-                const float b2 = B[(size_t)(2 * W + d) * ny + i];
-                y0[q] = fmaf(b0, x0, y0[q]);
-                y0[q] = fmaf(b2, x1, y0[q]);
-                y0[q] = fmaf(b1, x3, y0[q]);
-                y1[q] = fmaf(b0, x4, y1[q]);
-                y1[q] = fmaf(b1, x5, y1[q]);
-                y2[q] = fmaf(b0, x2, y2[q]);
-            }
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < kTRun; ++q) {
-        if (q < nq) {
-            const size_t o = col + (size_t)(yb + q) * nx;
-            Y[o] = y0[q];
-            Y[N + o] = y1[q];
-            Y[2 * N + o] = y2[q];
-        }
-    }
-}
-
-// z: dL/dI += G^T Y0 + (D1 G)^T Y1 + (D2 G)^T Y2 along z
-template <int kTRun>
-__global__ __launch_bounds__(64) void k_tz_run(const float *__restrict__ Y, float *__restrict__ dvol,
-                                               const float *__restrict__ B, int nx, int ny, int nz, int R)
-{
-    const size_t plane = (size_t)nx * (size_t)ny;
-    const size_t e = (size_t)blockIdx.x * 64u + threadIdx.x;
-    if (e >= plane) return;
-    const int zb = (int)blockIdx.y * kTRun;
-    const int nq = min(kTRun, nz - zb);
-    const size_t N = plane * (size_t)nz;
-    const int W = 2 * R + 1;
-    float acc[kTRun];
-#pragma unroll
-    for (int q = 0; q < kTRun; ++q) acc[q] = 0.f;
-    const int i0 = max(0, zb - R), i1 = min(nz - 1, zb + nq - 1 + R);
-#pragma unroll 4
-    for (int i = i0; i <= i1; ++i) {
-        const size_t sidx = (size_t)i * plane + e;
-        const float v0 = Y[sidx], v1 = Y[N + sidx], v2 = Y[2 * N + sidx];
-#pragma unroll
-        for (int q = 0; q < kTRun; ++q) {
-            const int d = zb + q - i + R;
-            if (q < nq && d >= 0 && d < W) {
-                const float b0 = B[(size_t)d * nz + i], b1 = B[(size_t)(W + d) * nz + i];
-                const float b2 = B[(size_t)(2 * W + d) * nz + i];
-                acc[q] = fmaf(b0, v0, acc[q]);
-                acc[q] = fmaf(b1, v1, acc[q]);
-                acc[q] = fmaf(b2, v2, acc[q]);
-            }
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < kTRun; ++q)
-        if (q < nq) dvol[(size_t)(zb + q) * plane + e] += acc[q];
-}
-
-// Fixed-radius forms of k_ty_run and k_tz_run (R = 2..10): the walk over the K + 2R input rows of
-// a run is unrolled, row j of the run (i = start - R + j) reaches outputs q with j - 2R <= q <= j at
-// band offset d = q - j + 2R, both known at compile time, so only the axis ends and the run's
-// ragged tail are tested at run time.  Same rows, products and order: the same bits.
 template <int K, int R>
 __global__ __launch_bounds__(64 * kTWaves) void k_ty_run_r(const float *__restrict__ X, float *__restrict__ Y,
                                                            const float *__restrict__ B, int nx, int ny, int nz)
@@ -714,14 +577,12 @@ __global__ __launch_bounds__(64 * kTWaves) void k_tz_run_r(const float *__restri
         if (q < nq) dvol[(size_t)(zb + q) * plane + e] += acc[q];
 }
 
-// the fixed-radius y and z transposes for radii 2..10 (runs of kTyRunR, kTzRunR), else the generic
-// ones (runs of kTyRun, kTzRun)
 constexpr int kTyRunR = 8, kTzRunR = 8;
-static dim3 ty_grid(const dvr_grid &g, int K, int nw = 1)
+static dim3 ty_grid(const dvr_grid &g, int K, int nw)
 {
     return dim3((unsigned)((g.nx + 63) / 64), (unsigned)((g.ny + K - 1) / K), (unsigned)((g.nz + nw - 1) / nw));
 }
-static dim3 tz_grid(const dvr_grid &g, int K, int nw = 1)
+static dim3 tz_grid(const dvr_grid &g, int K, int nw)
 {
     const size_t plane = (size_t)g.nx * (size_t)g.ny;
     return dim3((unsigned)((plane + 64 * nw - 1) / (64 * nw)), (unsigned)((g.nz + K - 1) / K));
@@ -730,9 +591,7 @@ static dim3 tz_grid(const dvr_grid &g, int K, int nw = 1)
 template <int R>
 static void launch_ty(const float *X, float *Y, const float *B, int Ry, const dvr_grid &g, hipStream_t st)
 {
-    if constexpr (R > 10) {
-        hipLaunchKernelGGL(k_ty_run<kTyRun>, ty_grid(g, kTyRun), dim3(64), 0, st, X, Y, B, g.nx, g.ny, g.nz, Ry);
-    } else {
+    if constexpr (R <= kRMax) {
         if (Ry != R) return launch_ty<R + 1>(X, Y, B, Ry, g, st);
         hipLaunchKernelGGL((k_ty_run_r<kTyRunR, R>), ty_grid(g, kTyRunR, kTWaves), dim3(64 * kTWaves), 0, st, X, Y, B,
                            g.nx, g.ny, g.nz);
@@ -742,9 +601,7 @@ static void launch_ty(const float *X, float *Y, const float *B, int Ry, const dv
 template <int R>
 static void launch_tz(const float *Y, float *dvol, const float *B, int Rz, const dvr_grid &g, hipStream_t st)
 {
-    if constexpr (R > 10) {
-        hipLaunchKernelGGL(k_tz_run<kTzRun>, tz_grid(g, kTzRun), dim3(64), 0, st, Y, dvol, B, g.nx, g.ny, g.nz, Rz);
-    } else {
+    if constexpr (R <= kRMax) {
         if (Rz != R) return launch_tz<R + 1>(Y, dvol, B, Rz, g, st);
         hipLaunchKernelGGL((k_tz_run_r<kTzRunR, R>), tz_grid(g, kTzRunR, kTWaves), dim3(64 * kTWaves), 0, st, Y, dvol,
                            B, g.nx, g.ny, g.nz);

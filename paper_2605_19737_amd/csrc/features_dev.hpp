@@ -4,6 +4,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace dvr {
@@ -367,7 +369,84 @@ struct XYArgs {
     float inv2a2, inv2b2;
     float tau;
     int first, fro_pass;
+    int odt, layout;  // storage type and layout of the outputs (read where the kernel's are run-time values)
 };
+
+// Stores of one voxel (index v of N) in storage type OUT_DT and layout LAYOUT.  First scale: the
+// gradient and k, and for the interleaved record the intensity; k goes to the record's second half
+// together with V (store_ves).
+template <int OUT_DT, int LAYOUT>
+__device__ __forceinline__ void store_grad(const XYArgs &a, uint32_t v, uint32_t N, float I, float gx, float gy,
+                                           float gz, float kap)
+{
+    if constexpr (LAYOUT == DVR_PLANAR) {
+        st<OUT_DT>(a.grad, v, gx);
+        st<OUT_DT>(a.grad, N + v, gy);
+        st<OUT_DT>(a.grad, 2u * N + v, gz);
+        st<OUT_DT>(a.kappa, v, kap);
+    } else {
+        // split: (gx, gy, gz, k) at record v; interleaved: (I, gx, gy, gz) at half-record 2 v
+        const uint32_t r = (LAYOUT == DVR_SPLIT) ? v : 2u * v;
+        const float4 f = (LAYOUT == DVR_SPLIT) ? make_float4(gx, gy, gz, kap) : make_float4(I, gx, gy, gz);
+        if constexpr (OUT_DT == DVR_F32) {
+            reinterpret_cast<float4 *>(a.grad)[r] = f;
+        } else {
+            union { __half h[4]; uint2 u; } rec;
+            rec.h[0] = __float2half_rn(f.x);
+            rec.h[1] = __float2half_rn(f.y);
+            rec.h[2] = __float2half_rn(f.z);
+            rec.h[3] = __float2half_rn(f.w);
+            reinterpret_cast<uint2 *>(a.grad)[r] = rec.u;
+        }
+    }
+}
+
+// V of one voxel after this scale (kap: the first scale's k, written with it by the interleaved record)
+template <int OUT_DT, int LAYOUT>
+__device__ __forceinline__ void store_ves(const XYArgs &a, uint32_t v, float kap, float V)
+{
+    if constexpr (LAYOUT == DVR_PLANAR || LAYOUT == DVR_SPLIT) {
+        st<OUT_DT>(a.ves, v, V);
+    } else if (!a.first) {
+        st<OUT_DT>(a.grad, 8u * v + 5u, V);
+    } else if constexpr (OUT_DT == DVR_F32) {
+        reinterpret_cast<float4 *>(a.grad)[2u * v + 1u] = make_float4(kap, V, 0.f, 0.f);
+    } else {
+        union { __half h[4]; uint2 u; } rec;
+        rec.h[0] = __float2half_rn(kap);
+        rec.h[1] = __float2half_rn(V);
+        rec.h[2] = __float2half_rn(0.f);
+        rec.h[3] = __float2half_rn(0.f);
+        reinterpret_cast<uint2 *>(a.grad)[2u * v + 1u] = rec.u;
+    }
+}
+
+// V of the earlier scales at one voxel
+template <int OUT_DT, int LAYOUT>
+__device__ __forceinline__ float load_ves(const XYArgs &a, uint32_t v)
+{
+    return (LAYOUT == DVR_INTERLEAVED) ? ldo<OUT_DT>(a.grad, 8u * v + 5u) : ldo<OUT_DT>(a.ves, v);
+}
+
+// Calls f(storage type, layout) as compile-time constants: OUT_DT and LAYOUT themselves, or the
+// run-time values of a where LAYOUT is kAnyOut (uniform branches).
+template <int OUT_DT, int LAYOUT, typename F>
+__device__ __forceinline__ void with_out(const XYArgs &a, F &&f)
+{
+    auto go = [&](auto d, auto l) { f(d, l); };
+    using std::integral_constant;
+    if constexpr (LAYOUT != kAnyOut) {
+        go(integral_constant<int, OUT_DT>{}, integral_constant<int, LAYOUT>{});
+    } else {
+        auto lay = [&](auto d) {
+            if (a.layout == DVR_PLANAR) go(d, integral_constant<int, DVR_PLANAR>{});
+            else if (a.layout == DVR_SPLIT) go(d, integral_constant<int, DVR_SPLIT>{});
+            else go(d, integral_constant<int, DVR_INTERLEAVED>{});
+        };
+        if (a.odt == DVR_F32) lay(integral_constant<int, DVR_F32>{});
+        else lay(integral_constant<int, DVR_F16>{});
+    }
+}
 
 // z filters of one voxel: (Gz, D1z, D2z) of I at in-plane index e of slice z.
 template <int DT, typename AT>
@@ -487,37 +566,13 @@ __device__ __forceinline__ void voxels_out(const XYArgs &a, float sigma2, const 
                               2.f * (H[i][3] * u0 * u1 + H[i][4] * u0 * u2 + H[i][5] * u1 * u2);
             kap = num * __builtin_amdgcn_rcpf(u0 * u0 + u1 * u1 + u2 * u2);  // the sum is >= 1
         }
-        const uint32_t vi = v[i];
-        if constexpr (LAYOUT == DVR_PLANAR) {
-            st<OUT_DT>(a.grad, vi, gx_);
-            st<OUT_DT>(a.grad, N + vi, gy_);
-            st<OUT_DT>(a.grad, 2u * N + vi, gz_);
-            st<OUT_DT>(a.kappa, vi, kap);
-        } else if constexpr (LAYOUT == DVR_SPLIT) {
-            if constexpr (OUT_DT == DVR_F32) {
-                reinterpret_cast<float4 *>(a.grad)[vi] = make_float4(gx_, gy_, gz_, kap);
-            } else {
-                union { __half h[4]; uint2 u; } rec;
-                rec.h[0] = __float2half_rn(gx_);
-                rec.h[1] = __float2half_rn(gy_);
-                rec.h[2] = __float2half_rn(gz_);
-                rec.h[3] = __float2half_rn(kap);
-                reinterpret_cast<uint2 *>(a.grad)[vi] = rec.u;
-            }
-        } else {
-            // interleaved: (I, gx, gy, gz) now, (k, V, 0, 0) with V below
-            if constexpr (OUT_DT == DVR_F32) {
-                reinterpret_cast<float4 *>(a.grad)[2u * vi] = make_float4(In[i][0], gx_, gy_, gz_);
-            } else {
-                union { __half h[4]; uint2 u; } rec;
-                rec.h[0] = __float2half_rn(In[i][0]);
-                rec.h[1] = __float2half_rn(gx_);
-                rec.h[2] = __float2half_rn(gy_);
-                rec.h[3] = __float2half_rn(gz_);
-                reinterpret_cast<uint2 *>(a.grad)[2u * vi] = rec.u;
-            }
-            kap_keep[i] = kap;
-        }
+        // the interleaved record's k is rounded to FP32 before it is rounded to FP16 (opaque to the
+        // compiler, which otherwise folds the last product into the conversion or not, kernel by kernel)
+        if constexpr (LAYOUT == DVR_INTERLEAVED || LAYOUT == kAnyOut) asm volatile("" : "+v"(kap));
+        kap_keep[i] = kap;
+        with_out<OUT_DT, LAYOUT>(a, [&](auto d, auto l) {
+            store_grad<decltype(d)::value, decltype(l)::value>(a, v[i], N, In[i][0], gx_, gy_, gz_, kap);
+        });
     }
     __syncthreads();
     if (count > 0) {
@@ -539,26 +594,12 @@ __device__ __forceinline__ void voxels_out(const XYArgs &a, float sigma2, const 
     for (int i = 0; i < NV; ++i) {
         if (!live[i]) continue;
         float V = need[i] ? cw[slot[i]] : 0.f;
-        const uint32_t vi = v[i];
-        // V of the earlier scales: given by the caller (loaded ahead), or read here
-        if constexpr (LAYOUT == DVR_PLANAR || LAYOUT == DVR_SPLIT) {
-            if (!a.first) V = fmaxf(V, Vprev ? (*Vprev)[i] : ldo<OUT_DT>(a.ves, vi));
-            st<OUT_DT>(a.ves, vi, V);
-        } else {
-            if (!a.first) {
-                V = fmaxf(V, Vprev ? (*Vprev)[i] : ldo<OUT_DT>(a.grad, 8u * vi + 5u));
-                st<OUT_DT>(a.grad, 8u * vi + 5u, V);
-            } else if constexpr (OUT_DT == DVR_F32) {
-                reinterpret_cast<float4 *>(a.grad)[2u * vi + 1u] = make_float4(kap_keep[i], V, 0.f, 0.f);
-            } else {
-                union { __half h[4]; uint2 u; } rec;
-                rec.h[0] = __float2half_rn(kap_keep[i]);
-                rec.h[1] = __float2half_rn(V);
-                rec.h[2] = __float2half_rn(0.f);
-                rec.h[3] = __float2half_rn(0.f);
-                reinterpret_cast<uint2 *>(a.grad)[2u * vi + 1u] = rec.u;
-            }
-        }
+        with_out<OUT_DT, LAYOUT>(a, [&](auto d, auto l) {
+            constexpr int OD = decltype(d)::value, L = decltype(l)::value;
+            // V of the earlier scales: given by the caller (loaded ahead), or read here
+            if (!a.first) V = fmaxf(V, Vprev ? (*Vprev)[i] : load_ves<OD, L>(a, v[i]));
+            store_ves<OD, L>(a, v[i], kap_keep[i], V);
+        });
     }
 }
 
@@ -850,11 +891,12 @@ struct XYSlab {
 #pragma unroll
                 for (int k = 0; k < 7; ++k) In[i][k] = 0.f;
                 Vp[i] = 0.f;
-                if constexpr (LAYOUT == DVR_PLANAR || LAYOUT == DVR_SPLIT || LAYOUT == DVR_INTERLEAVED) {
+                if constexpr (LAYOUT != kHessianOut) {
                     const int gy = min(y0 + wv + NW * i, ny - 1);
                     const uint32_t vi = (uint32_t)z * plane + (uint32_t)gy * nx + cx;
-                    if constexpr (LAYOUT == DVR_INTERLEAVED) Vp[i] = ldo<OUT_DT>(a.grad, 8u * vi + 5u);
-                    else Vp[i] = ldo<OUT_DT>(a.ves, vi);
+                    with_out<OUT_DT, LAYOUT>(a, [&](auto d, auto l) {
+                        Vp[i] = load_ves<decltype(d)::value, decltype(l)::value>(a, vi);
+                    });
                 }
             }
         }
