@@ -135,33 +135,126 @@ static hipError_t launch_xy_r(const XYArgs &a, const ScaleTaps &taps, hipStream_
     }
 }
 
-// Brick table: one lane per brick (consecutive lanes on consecutive bricks along x), each reading its
-// (DVR_BRICK + 1)^3 voxels.  SRC: 0 F32 volume, 1 F16 volume, 2 F32 records (I at stride 8), 3 F16
-// records.
-template <int SRC>
-__global__ __launch_bounds__(256) void k_bricks(const void *__restrict__ src, float2 *__restrict__ out, int nx, int ny,
-                                                int nz, int nbx, int nby, int nbz)
+// Brick table: (min, max) of the (DVR_BRICK + 1)^3 voxels of each brick.  Bound by reading the volume
+// once, so lanes run along x and a workgroup walks a run of bricks along z, reading every slice once
+// (the voxel shared by two bricks of a column included) and each row 5/4 times: 0.19 -> 0.06 ms on a
+// 512 x 512 x 400 FP16 volume (210 MB) against one lane per brick that gathers its 125 voxels.
+// SRC: 0 F32 volume, 1 F16 volume, 2 F32 records (I at stride 8), 3 F16 records.
+// V consecutive voxels of x per lane: 4 (one brick, one vector load a row; rows and base aligned to
+// it, which nx % 4 == 0 gives) or 1 (any nx, four lanes a brick).
+template <int SRC, int V>
+__device__ __forceinline__ void brick_load(const void *__restrict__ src, uint32_t v, float (&f)[V])
 {
-    const int i = (int)(blockIdx.x * 256u + threadIdx.x);
-    if (i >= nbx * nby * nbz) return;
-    const int bx = i % nbx, by = (i / nbx) % nby, bz = i / (nbx * nby);
-    const int x0 = bx * DVR_BRICK, y0 = by * DVR_BRICK, z0 = bz * DVR_BRICK;
-    const int x1 = min(x0 + DVR_BRICK, nx - 1), y1 = min(y0 + DVR_BRICK, ny - 1), z1 = min(z0 + DVR_BRICK, nz - 1);
+    if constexpr (V == 4 && SRC == 0) {
+        const float4 q = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(src) + v);
+        f[0] = q.x; f[1] = q.y; f[2] = q.z; f[3] = q.w;
+    } else if constexpr (V == 4) {
+        const uint2 q = *reinterpret_cast<const uint2 *>(reinterpret_cast<const __half *>(src) + v);
+        const f16x4 h = __builtin_bit_cast(f16x4, q);
+        f[0] = (float)h[0]; f[1] = (float)h[1]; f[2] = (float)h[2]; f[3] = (float)h[3];
+    } else if constexpr (SRC == 0) f[0] = reinterpret_cast<const float *>(src)[v];
+    else if constexpr (SRC == 1) f[0] = __half2float(reinterpret_cast<const __half *>(src)[v]);
+    else if constexpr (SRC == 2) f[0] = reinterpret_cast<const float *>(src)[8u * v];
+    else f[0] = __half2float(reinterpret_cast<const __half *>(src)[8u * v]);
+}
+
+// A wave takes 64 V consecutive voxels of x (blockIdx.x) of brick row by (four to a workgroup) over
+// the bricks [run blockIdx.z, ...) of z.
+template <int SRC, int V>
+__global__ __launch_bounds__(256) void k_bricks(const void *__restrict__ src, float2 *__restrict__ out, int nx, int ny,
+                                                int nz, int nbx, int nby, int nbz, int run)
+{
+    static_assert(DVR_BRICK == 4 && (V == 1 || V == 4), "four voxels a brick along x");
+    const int lane = threadIdx.x & 63;
+    const int by = (int)(blockIdx.y * 4u + (threadIdx.x >> 6));
+    if (by >= nby) return;  // uniform over the wave
+    const int xw = (int)blockIdx.x * 64 * V;  // the wave's first voxel
+    const int x = xw + lane * V;
+    const int xc = min(x, nx - V);  // lanes past the row read its last voxels (their results are not stored)
     const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
-    float mn = INFINITY, mx = -INFINITY;
-    for (int z = z0; z <= z1; ++z)
-        for (int y = y0; y <= y1; ++y)
-            for (int x = x0; x <= x1; ++x) {
-                const uint32_t v = (uint32_t)z * plane + (uint32_t)y * nx + x;
-                float f;
-                if constexpr (SRC == 0) f = reinterpret_cast<const float *>(src)[v];
-                else if constexpr (SRC == 1) f = __half2float(reinterpret_cast<const __half *>(src)[v]);
-                else if constexpr (SRC == 2) f = reinterpret_cast<const float *>(src)[8u * v];
-                else f = __half2float(reinterpret_cast<const __half *>(src)[8u * v]);
-                mn = fminf(mn, f);
-                mx = fmaxf(mx, f);
+    // the voxel after the wave's last one belongs to its last brick too
+    const bool tail = lane == 63 && xw + 64 * V < nx;
+    const int bz0 = (int)blockIdx.z * run, bz1 = min(bz0 + run, nbz);
+    const int y0 = by * DVR_BRICK;
+    // min, max over a slice's rows of the lane's voxels, and of the lane's first voxel alone (the last
+    // voxel of the brick before)
+    float cmn = 0.f, cmx = 0.f, emn = 0.f, emx = 0.f, tmn = 0.f, tmx = 0.f;
+    auto slice = [&](int z, float &mn, float &mx, float &fmn, float &fmx, float &lmn, float &lmx) {
+        mn = fmn = lmn = INFINITY;
+        mx = fmx = lmx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r <= DVR_BRICK; ++r) {
+            const uint32_t row = (uint32_t)z * plane + (uint32_t)min(y0 + r, ny - 1) * (uint32_t)nx;
+            float f[V];
+            brick_load<SRC, V>(src, row + (uint32_t)xc, f);
+            fmn = fminf(fmn, f[0]);
+            fmx = fmaxf(fmx, f[0]);
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                mn = fminf(mn, f[e]);
+                mx = fmaxf(mx, f[e]);
             }
-    out[i] = make_float2(mn, mx);
+            if (tail) {
+                float g[1];
+                brick_load<SRC, 1>(src, row + (uint32_t)(xw + 64 * V), g);
+                lmn = fminf(lmn, g[0]);
+                lmx = fmaxf(lmx, g[0]);
+            }
+        }
+    };
+    slice(bz0 * DVR_BRICK, cmn, cmx, emn, emx, tmn, tmx);
+    for (int bz = bz0; bz < bz1; ++bz) {
+        float mn = cmn, mx = cmx, fmn = emn, fmx = emx, lmn = tmn, lmx = tmx;
+#pragma unroll
+        for (int k = 1; k <= DVR_BRICK; ++k) {
+            slice(min(bz * DVR_BRICK + k, nz - 1), cmn, cmx, emn, emx, tmn, tmx);
+            mn = fminf(mn, cmn);
+            mx = fmaxf(mx, cmx);
+            fmn = fminf(fmn, emn);
+            fmx = fmaxf(fmx, emx);
+            lmn = fminf(lmn, tmn);
+            lmx = fmaxf(lmx, tmx);
+        }
+        // the brick's fifth column: the first voxel of the next brick's first lane
+        int bx;
+        float nmn, nmx;
+        if constexpr (V == 4) {
+            bx = x / DVR_BRICK;
+            nmn = __shfl_down(fmn, 1, 64);
+            nmx = __shfl_down(fmx, 1, 64);
+        } else {
+            bx = x / DVR_BRICK;
+            mn = fminf(mn, __shfl_xor(mn, 1, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
+            mn = fminf(mn, __shfl_xor(mn, 2, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
+            nmn = __shfl_down(fmn, 1, 64);  // used by the brick's last lane
+            nmx = __shfl_down(fmx, 1, 64);
+        }
+        if (lane == 63) {
+            nmn = lmn;
+            nmx = lmx;
+        }
+        const bool writer = V == 4 || (lane & 3) == 3;
+        if (writer && bx < nbx) out[((size_t)bz * nby + by) * nbx + bx] = make_float2(fminf(mn, nmn), fmaxf(mx, nmx));
+    }
+}
+
+template <int SRC>
+static void launch_bricks_t(const void *src, float2 *o, const dvr_grid &g, int nbx, int nby, int nbz, hipStream_t st)
+{
+    const bool vec = SRC < 2 && g.nx % 4 == 0;
+    const unsigned bx = (unsigned)((g.nx + (vec ? 255 : 63)) / (vec ? 256 : 64)), by = (unsigned)((nby + 3) / 4);
+    // a run reads 4 run + 1 slices, but only 4096 waves fill the chip: shorter runs on small volumes
+    // (a 353 x 74 x 65 one: runs of 4 cost 6 us more than one brick a lane did)
+    int run = 4;
+    while (run > 1 && (int64_t)bx * nby * ((nbz + run - 1) / run) < 4096) run >>= 1;
+    const dim3 grid(bx, by, (unsigned)((nbz + run - 1) / run));
+    if (vec)
+        hipLaunchKernelGGL((k_bricks<SRC, SRC < 2 ? 4 : 1>), grid, dim3(256), 0, st, src, o, g.nx, g.ny, g.nz, nbx, nby,
+                           nbz, run);
+    else
+        hipLaunchKernelGGL((k_bricks<SRC, 1>), grid, dim3(256), 0, st, src, o, g.nx, g.ny, g.nz, nbx, nby, nbz, run);
 }
 
 // One lane per voxel, x fastest: the four rows are read coalesced (mostly from L2), the quad is
@@ -200,19 +293,15 @@ hipError_t launch_bricks(const void *vol, int vol_dt, const dvr_grid &g, const d
 {
     const int nbx = (g.nx - 1 + DVR_BRICK - 1) / DVR_BRICK, nby = (g.ny - 1 + DVR_BRICK - 1) / DVR_BRICK,
               nbz = (g.nz - 1 + DVR_BRICK - 1) / DVR_BRICK;
-    const int nb = nbx * nby * nbz;
-    dim3 grid((nb + 255) / 256);
     float2 *o = reinterpret_cast<float2 *>(out.bricks);
     // the records' I is the volume itself when the dtypes agree (read the contiguous volume then)
     if (out.layout == DVR_INTERLEAVED && out.dtype != vol_dt) {
-        if (out.dtype == DVR_F32)
-            hipLaunchKernelGGL(k_bricks<2>, grid, dim3(256), 0, st, out.grad, o, g.nx, g.ny, g.nz, nbx, nby, nbz);
-        else
-            hipLaunchKernelGGL(k_bricks<3>, grid, dim3(256), 0, st, out.grad, o, g.nx, g.ny, g.nz, nbx, nby, nbz);
+        if (out.dtype == DVR_F32) launch_bricks_t<2>(out.grad, o, g, nbx, nby, nbz, st);
+        else launch_bricks_t<3>(out.grad, o, g, nbx, nby, nbz, st);
     } else if (vol_dt == DVR_F32) {
-        hipLaunchKernelGGL(k_bricks<0>, grid, dim3(256), 0, st, vol, o, g.nx, g.ny, g.nz, nbx, nby, nbz);
+        launch_bricks_t<0>(vol, o, g, nbx, nby, nbz, st);
     } else {
-        hipLaunchKernelGGL(k_bricks<1>, grid, dim3(256), 0, st, vol, o, g.nx, g.ny, g.nz, nbx, nby, nbz);
+        launch_bricks_t<1>(vol, o, g, nbx, nby, nbz, st);
     }
     return hipGetLastError();
 }
