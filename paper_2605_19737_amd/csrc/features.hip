@@ -402,6 +402,8 @@ hipError_t launch_features_scale(const void *vol, int vol_dt, const dvr_grid &g,
             return launch_xy_r<DVR_F32, DVR_F32, DVR_SPLIT, kRFastMin>(a, taps, st);
         if (vol_dt == DVR_F16 && odt == DVR_F16 && lay == DVR_SPLIT)
             return launch_xy_r<DVR_F16, DVR_F16, DVR_SPLIT, kRFastMin>(a, taps, st);
+        if (vol_dt == DVR_F16 && odt == DVR_F16 && lay == DVR_PLANAR)  // the split layout's values, bit for bit
+            return launch_xy_r<DVR_F16, DVR_F16, DVR_PLANAR, kRFastMin>(a, taps, st);
         return (vol_dt == DVR_F32) ? launch_xy_r<DVR_F32, DVR_F32, kAnyOut, kRFastMin>(a, taps, st)
                                    : launch_xy_r<DVR_F16, DVR_F32, kAnyOut, kRFastMin>(a, taps, st);
     }
