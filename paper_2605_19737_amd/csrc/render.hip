@@ -47,16 +47,19 @@ __device__ __forceinline__ KCam load_cam(const KLaunch &L, uint32_t cam)
     return c;
 }
 
-// MORTON: the 64 lanes of a wave take their 8 x 8 pixels in Morton order (lane bits x0 y0 x1 y1 x2
-// y2), so each quad of lanes is a 2 x 2 pixel block; otherwise row-major.
-template <bool MORTON = false>
-__device__ __forceinline__ void pixel_of(const KLaunch &L, uint32_t &cam, int &pi, int &pj, bool &valid)
+// XCD-aware order: consecutive dispatch slots go to different XCDs, so the tile of slot b is
+// (b % 8) * (slots / 8) + b / 8; each XCD then walks a contiguous range of tiles.
+__device__ __forceinline__ uint32_t tile_of(uint32_t slot, uint32_t slots)
 {
-    // XCD-aware order: consecutive dispatch slots go to different XCDs, so logical tile t is placed
-    // at slot (t % per) * 8 + t / per; each XCD then walks a contiguous range of tiles.
-    const uint32_t b = blockIdx.x;
-    const uint32_t per = gridDim.x / 8u;
-    const uint32_t t = (b & 7u) * per + (b >> 3);
+    return (slot & 7u) * (slots / 8u) + (slot >> 3);
+}
+
+// camera and pixel of this lane in the 16 x 16 pixel tile t (a wave takes 8 x 8 of it).  MORTON: the lanes
+// take their pixels in Morton order (lane bits x0 y0 x1 y1 x2 y2), so each quad of lanes is a 2 x 2
+// pixel block and each row of 16 a 4 x 4 one; otherwise row-major.
+template <bool MORTON = false>
+__device__ __forceinline__ void pixel_of(const KLaunch &L, uint32_t t, uint32_t &cam, int &pi, int &pj, bool &valid)
+{
     const uint32_t tiles_x = (L.W + 15) / 16, tiles_y = (L.H + 15) / 16;
     const uint32_t tpv = tiles_x * tiles_y;
     cam = t / tpv;
@@ -92,7 +95,7 @@ __global__ __launch_bounds__(256, (LAYOUT == DVR_QUAD && DT == DVR_F16) ? 5 : 1)
     uint32_t cam;
     int pi, pj;
     bool valid;
-    pixel_of(L, cam, pi, pj, valid);
+    pixel_of(L, tile_of(blockIdx.x, gridDim.x), cam, pi, pj, valid);
     const float gm = *feat.gmax;
     const float invg = gm > 0.f ? 1.f / gm : 0.f;
     RayGeo r;
@@ -121,7 +124,7 @@ __global__ __launch_bounds__(256) void k_render_gather(KFeat feat, KGrid g, KTF 
     uint32_t cam;
     int pi, pj;
     bool valid;
-    pixel_of(L, cam, pi, pj, valid);
+    pixel_of(L, tile_of(blockIdx.x, gridDim.x), cam, pi, pj, valid);
     const size_t pix = valid ? ((size_t)(L.cam_base + cam) * L.H + pj) * L.W + pi : 0;
     const int kl = valid ? L.k_last[pix] : -1;
     RayGeo r;
@@ -132,21 +135,37 @@ __global__ __launch_bounds__(256) void k_render_gather(KFeat feat, KGrid g, KTF 
     if (L.counters) count_samples<4>(L.counters, o.last, o.shaded);
 }
 
-template <int LAYOUT, int DT, int KMAX, bool FG>
+// value of another lane of the wave
+__device__ __forceinline__ int64_t shfl64(int64_t v, int lane)
+{
+    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)v, lane, 64), hi = (uint32_t)__shfl((int)(v >> 32), lane, 64);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// Adjoint of a 16 x 16 pixel tile per workgroup, 8 x 8 pixels per wave.  G = 1: one lane per ray
+// (march_bwd).  G = 4, 16: G lanes per ray (march_bwd_group), the wave's 64 rays in G blocks of 64 / G
+// (4 x 4 or 2 x 2 pixels) taken one after another; every lane sets one ray up and the blocks read
+// theirs from it, so the set-up is not repeated within a group.  The blocks of a tile may be dealt to
+// several workgroups (gridDim.y).
+// Per call, render adjoint with feature gradients / plain, G = 1 against 4 (pitch in voxels a pixel):
+// head 1024^2 x 2 (0.35) 8.3 -> 9.7 / 3.8 -> 4.4 ms, 128^3 512^2 x 4 (0.43) 11.4 -> 7.4 / 2.3 -> 2.5, head
+// 512^2 x 2 (0.70) 5.7 -> 2.7 / 1.52 -> 1.37, 128^3 256^2 x 4 (0.86) 18.1 -> 2.7 / 2.5 -> 0.79; against 16:
+// 172 x 373 x 89, 231 x 286 x 6 (1.8) 28.0 -> 7.5 / 5.7 -> 1.75, 128^3 128^2 x 2 (1.7) 5.9 -> 1.1 / 2.0 -> 0.30.
+template <int LAYOUT, int DT, int KMAX, bool FG, int G>
 __global__ __launch_bounds__(256) void k_render_bwd(KFeat feat, KGrid g, KTF tf, KRender rp, KLaunch L)
 {
     __shared__ TFShared<KMAX> sh;
     constexpr int kCopies = tf_copies(KMAX);
     __shared__ double tfa[KMAX * 4 * kCopies];
-    using Win = std::conditional_t<FG, DWinF, DWin>;
+    using Win = DWinG<FG, G>;
     __shared__ double win[4][Win::kEntries];  // one accumulation window per wave
     // the ray first, before anything else is live: set up after the TF load (with the knots held in
     // registers across it) the kernel took 182 VGPRs instead of 166, one wave per SIMD fewer
     uint32_t cam;
     int pi, pj;
     bool valid;
-    pixel_of<true>(L, cam, pi, pj, valid);
-    const size_t pix = valid ? ((size_t)(L.cam_base + cam) * L.H + pj) * L.W + pi : 0;
+    pixel_of<true>(L, tile_of(blockIdx.x, gridDim.x), cam, pi, pj, valid);
+    const int pix = valid ? (int)(((size_t)(L.cam_base + cam) * L.H + pj) * L.W + pi) : -1;
     const int kl = valid ? L.k_last[pix] : -1;
     RayGeo r;
     r.N = 0;
@@ -161,16 +180,42 @@ __global__ __launch_bounds__(256) void k_render_bwd(KFeat feat, KGrid g, KTF tf,
     const int K = tf.K;
     const float gm = *feat.gmax;
     const float invg = gm > 0.f ? 1.f / gm : 0.f;
-    float4 gr = make_float4(0.f, 0.f, 0.f, 0.f);
-    float Tl = 0.f;
-    if (kl >= 0) {
-        gr = reinterpret_cast<const float4 *>(L.dout)[pix];
-        Tl = L.T_last[pix];
-    }
-    // every lane of the wave takes part (the dL/dI window is managed wave-wide)
+    double *tfl = tfa + (threadIdx.x % kCopies);
     float gmb = 0.f;
-    march_bwd<LAYOUT, DT, KMAX, FG>(feat, g, sh, kx, rp, invg, r, kl, Tl, gr, K, tfa + (threadIdx.x % kCopies), L.dvol,
-                                    wwin, L.dfeat, gmb);
+    if constexpr (G == 1) {
+        float4 gr = make_float4(0.f, 0.f, 0.f, 0.f);
+        float Tl = 0.f;
+        if (kl >= 0) {
+            gr = reinterpret_cast<const float4 *>(L.dout)[pix];
+            Tl = L.T_last[pix];
+        }
+        // every lane of the wave takes part (the dL/dI window is managed wave-wide)
+        march_bwd<LAYOUT, DT, KMAX, FG>(feat, g, sh, kx, rp, invg, r, kl, Tl, gr, K, tfl, L.dvol, wwin, L.dfeat, gmb);
+    } else {
+        const int nb = G / (int)gridDim.y;  // blocks of this workgroup
+        for (int blk = (int)blockIdx.y * nb; blk < ((int)blockIdx.y + 1) * nb; ++blk) {
+            const int src = blk * (64 / G) + (int)(threadIdx.x & 63u) / G;
+            GroupRay q;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                q.q0[a] = shfl64(r.q0[a], src);
+                q.dq[a] = shfl64(r.dq[a], src);
+                q.ql[a] = shfl64(r.ql[a], src);
+            }
+            q.N = __shfl(r.N, src, 64);
+            q.delta = g.delta_hi;
+            q.dlast = __shfl(r.dlast, src, 64);
+            const int px = __shfl(pix, src, 64), k1 = __shfl(kl, src, 64);
+            float4 gr = make_float4(0.f, 0.f, 0.f, 0.f);
+            float Tl = 0.f;
+            if (k1 >= 0) {
+                gr = reinterpret_cast<const float4 *>(L.dout)[px];
+                Tl = L.T_last[px];
+            }
+            march_bwd_group<LAYOUT, DT, KMAX, FG, G, Win>(feat, g, sh, kx, rp, invg, q, k1, Tl, gr, K, tfl, L.dvol, wwin,
+                                                          L.dfeat, gmb);
+        }
+    }
     if constexpr (FG) {
         for (int o = 32; o > 0; o >>= 1) gmb += __shfl_xor(gmb, o, 64);
         if ((threadIdx.x & 63) == 0 && gmb != 0.f) atomicAdd(L.dgmax, gmb);
@@ -189,27 +234,74 @@ enum { kFwd = 0, kBwd = 1, kGather = 2 };
 
 template <int LAYOUT, int DT, int KMAX>
 static hipError_t launch_fwd_t(const KFeat &f, const KGrid &g, const KTF &tf, const KRender &rp, const KLaunch &L,
-                               uint32_t blocks, hipStream_t st, int mode)
+                               hipStream_t st, int mode, int lanes)
 {
-    const bool bwd = mode == kBwd;
-    if (mode == kGather)
+    const uint32_t tiles = (uint32_t)((L.W + 15) / 16) * (uint32_t)((L.H + 15) / 16) * (uint32_t)L.ncam;
+    const uint32_t blocks = (tiles + 7u) / 8u * 8u;
+    // a tile's blocks are dealt to as many workgroups as evens the load out (about 4096); more would add
+    // to the error of the TF gradient, which every workgroup adds to the same few FP32 words
+    uint32_t split = 1;
+    while (split < (uint32_t)lanes && blocks * split * 2u <= 4096u) split *= 2;
+#define DVR_BWD(FG, G) \
+    hipLaunchKernelGGL((k_render_bwd<LAYOUT, DT, KMAX, FG, G>), dim3(blocks, split), dim3(256), 0, st, f, g, tf, rp, L)
+    if (mode == kGather) {
         hipLaunchKernelGGL((k_render_gather<LAYOUT, DT, KMAX>), dim3(blocks), dim3(256), 0, st, f, g, tf, rp, L);
-    else if (bwd && L.dfeat)
-        hipLaunchKernelGGL((k_render_bwd<LAYOUT, DT, KMAX, true>), dim3(blocks), dim3(256), 0, st, f, g, tf, rp, L);
-    else if (bwd)
-        hipLaunchKernelGGL((k_render_bwd<LAYOUT, DT, KMAX, false>), dim3(blocks), dim3(256), 0, st, f, g, tf, rp, L);
-    else
+    } else if (mode == kFwd) {
         hipLaunchKernelGGL((k_render<LAYOUT, DT, KMAX>), dim3(blocks), dim3(256), 0, st, f, g, tf, rp, L);
+    } else if (L.dfeat) {
+        if (lanes == 16) DVR_BWD(true, 16);
+        else if (lanes == 4) DVR_BWD(true, 4);
+        else DVR_BWD(true, 1);
+    } else {
+        if (lanes == 16) DVR_BWD(false, 16);
+        else if (lanes == 4) DVR_BWD(false, 4);
+        else DVR_BWD(false, 1);
+    }
+#undef DVR_BWD
     return hipGetLastError();
 }
 
 template <int LAYOUT, int DT>
 static hipError_t launch_k(const KFeat &f, const KGrid &g, const KTF &tf, const KRender &rp, const KLaunch &L,
-                           uint32_t blocks, hipStream_t st, int mode)
+                           hipStream_t st, int mode, int lanes)
 {
-    if (tf.K <= 8) return launch_fwd_t<LAYOUT, DT, 8>(f, g, tf, rp, L, blocks, st, mode);
-    if (tf.K <= 16) return launch_fwd_t<LAYOUT, DT, 16>(f, g, tf, rp, L, blocks, st, mode);
-    return launch_fwd_t<LAYOUT, DT, 64>(f, g, tf, rp, L, blocks, st, mode);
+    if (tf.K <= 8) return launch_fwd_t<LAYOUT, DT, 8>(f, g, tf, rp, L, st, mode, lanes);
+    if (tf.K <= 16) return launch_fwd_t<LAYOUT, DT, 16>(f, g, tf, rp, L, st, mode, lanes);
+    return launch_fwd_t<LAYOUT, DT, 64>(f, g, tf, rp, L, st, mode, lanes);
+}
+
+// Lanes per ray of the adjoint for one launch, by the pixel pitch of its views in voxels (the larger
+// of a pixel's two steps, at the box centre for a perspective view) and its number of rays.  Above
+// about 0.4 voxels a pixel the 8 x 8 rays of a wave stop fitting its window (feature gradients; 0.5
+// without them, whose window is larger and whose G = 1 form keeps its corner cache), above about 1.5
+// the 4 x 4 ones do.  Few rays take more lanes whatever the pitch: 64^3 at 256^2 has 1024 waves for
+// 1024 SIMDs with one lane a ray.
+static int bwd_lanes(const KLaunch &L, const KGrid &g)
+{
+    double pitch = 0.0;
+    for (int c = 0; c < L.ncam; ++c) {
+        const KCam &cam = L.cams[c];
+        double scale = 1.0, du = 0.0, dv = 0.0;
+        if (cam.persp) {
+            double dist = 0.0, dir = 0.0;
+            for (int a = 0; a < 3; ++a) {
+                const double to = 0.5 * (g.n[a] - 1) * (double)g.h[a] - cam.o[a];
+                const double d = cam.d0[a] + 0.5 * L.W * (double)cam.du[a] + 0.5 * L.H * (double)cam.dv[a];
+                dist += to * to;
+                dir += d * d;
+            }
+            scale = dir > 0.0 ? sqrt(dist / dir) : 1.0;
+        }
+        for (int a = 0; a < 3; ++a) {
+            du += (cam.du[a] / (double)g.h[a]) * (cam.du[a] / (double)g.h[a]);
+            dv += (cam.dv[a] / (double)g.h[a]) * (cam.dv[a] / (double)g.h[a]);
+        }
+        pitch = fmax(pitch, scale * sqrt(fmax(du, dv)));
+    }
+    const double rays = (double)L.W * L.H * L.ncam;
+    if (pitch > 1.5 || rays <= 32768.0) return 16;
+    if (pitch > (L.dfeat ? 0.39 : 0.5) || rays <= 131072.0) return 4;
+    return 1;
 }
 
 static hipError_t launch_any(const RenderArgs &a, hipStream_t st, int mode)
@@ -219,18 +311,17 @@ static hipError_t launch_any(const RenderArgs &a, hipStream_t st, int mode)
         L.ncam = a.ncam - c0 < kCamChunk ? a.ncam - c0 : kCamChunk;
         L.cam_base = c0;
         for (int i = 0; i < L.ncam; ++i) L.cams[i] = a.cams[c0 + i];
-        const uint32_t tiles = (uint32_t)((L.W + 15) / 16) * (uint32_t)((L.H + 15) / 16) * (uint32_t)L.ncam;
-        const uint32_t blocks = (tiles + 7u) / 8u * 8u;
+        const int lanes = mode == kBwd ? bwd_lanes(L, a.grid) : 1;
         hipError_t e;
         const int lay = a.feat.layout, dt = a.feat.dtype;
-        if (lay == DVR_PLANAR && dt == DVR_F32) e = launch_k<DVR_PLANAR, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, blocks, st, mode);
-        else if (lay == DVR_PLANAR && dt == DVR_F16) e = launch_k<DVR_PLANAR, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, blocks, st, mode);
-        else if (lay == DVR_INTERLEAVED && dt == DVR_F32) e = launch_k<DVR_INTERLEAVED, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, blocks, st, mode);
-        else if (lay == DVR_INTERLEAVED && dt == DVR_F16) e = launch_k<DVR_INTERLEAVED, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, blocks, st, mode);
-        else if (lay == DVR_SPLIT && dt == DVR_F32) e = launch_k<DVR_SPLIT, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, blocks, st, mode);
-        else if (lay == DVR_SPLIT && dt == DVR_F16) e = launch_k<DVR_SPLIT, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, blocks, st, mode);
-        else if (lay == DVR_QUAD && dt == DVR_F32) e = launch_k<DVR_QUAD, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, blocks, st, mode);
-        else if (lay == DVR_QUAD && dt == DVR_F16) e = launch_k<DVR_QUAD, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, blocks, st, mode);
+        if (lay == DVR_PLANAR && dt == DVR_F32) e = launch_k<DVR_PLANAR, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
+        else if (lay == DVR_PLANAR && dt == DVR_F16) e = launch_k<DVR_PLANAR, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
+        else if (lay == DVR_INTERLEAVED && dt == DVR_F32) e = launch_k<DVR_INTERLEAVED, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
+        else if (lay == DVR_INTERLEAVED && dt == DVR_F16) e = launch_k<DVR_INTERLEAVED, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
+        else if (lay == DVR_SPLIT && dt == DVR_F32) e = launch_k<DVR_SPLIT, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
+        else if (lay == DVR_SPLIT && dt == DVR_F16) e = launch_k<DVR_SPLIT, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
+        else if (lay == DVR_QUAD && dt == DVR_F32) e = launch_k<DVR_QUAD, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
+        else if (lay == DVR_QUAD && dt == DVR_F16) e = launch_k<DVR_QUAD, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
         else e = hipErrorInvalidValue;
         if (e != hipSuccess) return e;
     }

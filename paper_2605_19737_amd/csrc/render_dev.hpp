@@ -940,6 +940,130 @@ struct DWinT {
 using DWin = DWinT<kWin0, kWin1, kWin2, 1>;
 using DWinF = DWinT<kFWin0, kFWin1, kFWin2, 6>;
 
+// The window of march_bwd_group: any box of at most VOX voxels, its extents chosen at each placement
+// from the cells of the lanes that need it plus the way they walk in the next steps, x fastest.
+template <int VOX, int CH>
+struct DBoxT {
+    static constexpr int kVox = VOX;
+    static constexpr int kEntries = VOX * CH;  // doubles in LDS
+    static_assert(VOX % 32 == 0, "whole swizzle blocks");
+    __device__ __forceinline__ static int swz(int e) { return e ^ (((e >> 5) & 7) << 1); }  // as DWinT
+    double *w;   // this wave's kEntries in LDS: [channel][voxel]
+    int o[3];    // voxel (x, y, z) of the first entry; wave-uniform, like all that follows
+    int ext[3];  // extents
+    bool live;   // placed (it may hold partial sums)
+
+    __device__ __forceinline__ void flush(float *dvol, float *dfeat, const KGrid &g)
+    {
+        const int lane = threadIdx.x & 63;
+        const int nx = g.n[0], plane = g.n[0] * g.n[1];
+        const int olin = o[0] + o[1] * nx + o[2] * plane;
+        const size_t N = (size_t)plane * (size_t)g.n[2];
+        const int s01 = ext[0] * ext[1], n = s01 * ext[2];
+        const uint32_t m01 = 0xffffffffu / (uint32_t)s01 + 1u, m0 = 0xffffffffu / (uint32_t)ext[0] + 1u;
+        for (int e = lane; e < n; e += 64) {
+            // exact quotients: e, s01 and ext[0] (>= 2) are below 2^16
+            const int u2 = (int)__umulhi((uint32_t)e, m01), e2 = e - u2 * s01;
+            const int u1 = (int)__umulhi((uint32_t)e2, m0), u0 = e2 - u1 * ext[0];
+            const int gi = olin + u0 + u1 * nx + u2 * plane;  // entries are only written for in-bounds voxels
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const double v = w[c * VOX + swz(e)];
+                if (v != 0.0) {
+                    atomicAdd(c == 0 ? dvol + gi : dfeat + (size_t)(c - 1) * N + gi, (float)v);
+                    w[c * VOX + swz(e)] = 0.0;
+                }
+            }
+        }
+    }
+
+    __device__ __forceinline__ bool holds(const int cc[3]) const
+    {
+        return (uint32_t)(cc[0] - o[0]) <= (uint32_t)(ext[0] - 2) && (uint32_t)(cc[1] - o[1]) <= (uint32_t)(ext[1] - 2) &&
+               (uint32_t)(cc[2] - o[2]) <= (uint32_t)(ext[2] - 2);
+    }
+
+    __device__ __forceinline__ int index(const int cc[3]) const
+    {
+        return cc[0] - o[0] + ext[0] * (cc[1] - o[1] + ext[1] * (cc[2] - o[2]));
+    }
+
+    // offset of cell corner e (bit 0 x, bit 1 y, bit 2 z)
+    __device__ __forceinline__ int corner(int e) const
+    {
+        return (e & 1) + ((e >> 1) & 1) * ext[0] + ((e >> 2) & 1) * ext[0] * ext[1];
+    }
+
+    // Places the box around the cells of the lanes with need set; dq_lead is the front-to-back step of
+    // one of them, G the samples a group advances by.  The cells move against dq: the room the box has
+    // beyond them lies on that side, enough for the most steps (4, 3, 2, 1) that fit.  Cells that alone
+    // exceed the box are clipped along its longest axis (those lanes add to global memory).
+    __device__ __forceinline__ void place(bool need, const int cc[3], const int64_t dq_lead[3], int G)
+    {
+        int lo[3], hi[3], n[3], mv[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = __builtin_amdgcn_readfirstlane(wave_min_i(need ? cc[a] : 0x7fffffff));
+            hi[a] = __builtin_amdgcn_readfirstlane(wave_max_i(need ? cc[a] : -0x7fffffff));
+            n[a] = hi[a] - lo[a] + 2;
+            // cells moved per step in 1/256 voxel (at most 64 steps of 64 voxels matter)
+            const int64_t st = dq_lead[a] < 0 ? -dq_lead[a] : dq_lead[a];
+            mv[a] = __builtin_amdgcn_readfirstlane((int)min(st >> 24, (int64_t)16384)) * G;
+            n[a] = min(n[a], VOX);
+        }
+        int t = 4;
+        for (; t >= 0; --t) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) ext[a] = min(n[a] + ((mv[a] * t + 255) >> 8), VOX);
+            if (ext[0] * ext[1] <= VOX && ext[0] * ext[1] * ext[2] <= VOX) break;
+        }
+        if (t < 0) {
+            // clip the longest axis until the box fits (at least two voxels an axis: 8 <= VOX)
+            while (ext[0] * ext[1] > VOX || ext[0] * ext[1] * ext[2] > VOX) {
+                if (ext[0] >= ext[1] && ext[0] >= ext[2]) --ext[0];
+                else if (ext[1] >= ext[2]) --ext[1];
+                else --ext[2];
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) o[a] = dq_lead[a] > 0 ? hi[a] + 2 - ext[a] : lo[a];
+        live = true;
+    }
+};
+
+// The window of G lanes per ray.  With feature gradients the LDS bounds the workgroups of a CU: 384
+// voxels leave two (256, three of them, and 512, one, were 10-40 % slower at 0.7-1.3 voxels a pixel);
+// G = 16 serves pitches where the box of a wave's samples is larger and takes 512 (a 172 x 373 x 89
+// volume at 1.8 voxels a pixel: 7.5 ms against 11.7 with 384).
+template <bool FG, int G>
+using DWinG = std::conditional_t<G == 1, std::conditional_t<FG, DWinF, DWin>,
+                                 std::conditional_t<FG, DBoxT<G == 4 ? 384 : 512, 6>, DBoxT<512, 1>>>;
+
+// dL/d(gx, gy, gz, k, V) of one sample from Mb = dL/dM (not 0), M = m w u of Eq. 4; dL/d|g|_max goes to gmb.
+__device__ __forceinline__ void feature_grads(const KRender &rp, float invg, const Chan &ch, float Mb, float (&fv)[5],
+                                              float &gmb)
+{
+    const float gn = __builtin_amdgcn_sqrtf(ch.g[0] * ch.g[0] + ch.g[1] * ch.g[1] + ch.g[2] * ch.g[2]);
+    const float t = gn * invg;
+    const float m = fmaf(rp.lg, fminf(t, 1.f), rp.omlg);
+    const float ak = fabsf(ch.k);
+    const float rk = 1.f / (ak + rp.k0);
+    const float w = fmaf(rp.lk, ak * rk, rp.omlk);
+    const float u = fmaf(rp.lv, ch.V, 1.f);
+    float gs = 0.f;
+    if (t < 1.f && gn > 0.f) {
+        const float mb = Mb * w * u * rp.lg;
+        gs = mb * invg / gn;
+        gmb -= mb * t * invg;
+    }
+    const float sk = ch.k > 0.f ? 1.f : (ch.k < 0.f ? -1.f : 0.f);
+    fv[0] = gs * ch.g[0];
+    fv[1] = gs * ch.g[1];
+    fv[2] = gs * ch.g[2];
+    fv[3] = Mb * m * u * rp.lk * rp.k0 * sk * rk * rk;
+    fv[4] = Mb * m * w * rp.lv;
+}
+
 // Adjoint (back to front from the stored (T_last, k_last)).  With suffix colour S and suffix
 // transmittance R of the samples behind k:
 //   dL/dalpha_k = T_k (gC . (c_k - S) + gA R),   dL/dc_k = gC T_k alpha_k,
@@ -1089,27 +1213,7 @@ __device__ __forceinline__ void march_bwd(const KFeat &feat, const KGrid &g, con
             vb[3] = dal * o.om * o.M * dk;
             if constexpr (FG) {
                 const float Mb = dal * o.om * o.tau * dk;
-                if (Mb != 0.f) {
-                    const float gn = __builtin_amdgcn_sqrtf(ch.g[0] * ch.g[0] + ch.g[1] * ch.g[1] + ch.g[2] * ch.g[2]);
-                    const float t = gn * invg;
-                    const float m = fmaf(rp.lg, fminf(t, 1.f), rp.omlg);
-                    const float ak = fabsf(ch.k);
-                    const float rk = 1.f / (ak + rp.k0);
-                    const float w = fmaf(rp.lk, ak * rk, rp.omlk);
-                    const float u = fmaf(rp.lv, ch.V, 1.f);
-                    float gs = 0.f;
-                    if (t < 1.f && gn > 0.f) {
-                        const float mb = Mb * w * u * rp.lg;
-                        gs = mb * invg / gn;
-                        gmb -= mb * t * invg;
-                    }
-                    const float sk = ch.k > 0.f ? 1.f : (ch.k < 0.f ? -1.f : 0.f);
-                    fv[0] = gs * ch.g[0];
-                    fv[1] = gs * ch.g[1];
-                    fv[2] = gs * ch.g[2];
-                    fv[3] = Mb * m * u * rp.lk * rp.k0 * sk * rk * rk;
-                    fv[4] = Mb * m * w * rp.lv;
-                }
+                if (Mb != 0.f) feature_grads(rp, invg, ch, Mb, fv, gmb);
             }
             S0 = fmaf(o.om, S0, o.alpha * o.c[0]);
             S1 = fmaf(o.om, S1, o.alpha * o.c[1]);
@@ -1205,6 +1309,238 @@ __device__ __forceinline__ void march_bwd(const KFeat &feat, const KGrid &g, con
         }
     }
     if constexpr (FG) emit_cell(ahas);
+    if ((FG || dvol) && dw.live) dw.flush(dvol, dfeat, g);
+    if (sa.seg != -2) sa.flush(tfa, K);
+}
+
+// ------------------------------------------------------------------------------------------------
+// Lane groups: G consecutive lanes (4 or 16) share a ray and hold G consecutive samples of it.
+struct GroupRay {  // the fields of RayGeo they need
+    int N;
+    int64_t q0[3], dq[3], ql[3];
+    float delta, dlast;
+};
+
+// Values of the lane N below in the group, or ident in the group's first N lanes.
+template <int G, int N>
+__device__ __forceinline__ float group_up(float v, float ident)
+{
+    static_assert((G == 4 && N < 4) || (G == 16 && N < 16), "quads and rows of 16 lanes");
+    if constexpr (G == 16) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, ident), __builtin_bit_cast(int, v),
+                                                                     0x110 | N, 0xF, 0xF, false));  // row_shr:N
+    } else {
+        constexpr int kPerm = N == 1 ? 0x90 : (N == 2 ? 0x40 : 0x00);  // quad_perm [0,0,1,2], [0,0,0,1], [0,0,0,0]
+        const float t = __builtin_bit_cast(
+            float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kPerm, 0xF, 0xF, false));
+        return (int)(threadIdx.x & 3u) >= N ? t : ident;
+    }
+}
+
+// the value of the group's last lane
+template <int G>
+__device__ __forceinline__ float group_last(float v)
+{
+    if constexpr (G == 16)  // lane (l & 16) | 15 of each 32
+        return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x1F0));
+    else  // quad_perm [3,3,3,3]
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xFF, 0xF, 0xF, false));
+}
+
+// inclusive prefix product over the group
+template <int G, int N = 1>
+__device__ __forceinline__ void group_prod(float &a)
+{
+    if constexpr (N < G) {
+        a *= group_up<G, N>(a, 1.f);
+        group_prod<G, 2 * N>(a);
+    }
+}
+
+// inclusive prefix composition of the maps S -> a S + b (the lower lane's map is applied first)
+template <int G, int N = 1>
+__device__ __forceinline__ void group_affine(float &a, float (&b)[3])
+{
+    if constexpr (N < G) {
+        const float al = group_up<G, N>(a, 1.f);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) b[e] = fmaf(a, group_up<G, N>(b[e], 0.f), b[e]);
+        a *= al;
+        group_affine<G, 2 * N>(a, b);
+    }
+}
+
+// The adjoint with G lanes per ray: lane j of a group takes samples kb - j, kb - j - G, ... from the
+// wave's largest k_last kb down, so a wave holds 64 / G rays and G consecutive samples of each.  What
+// march_bwd carries from sample to sample (the transmittance T, the suffix colour S and transmittance
+// R) comes from prefix products and affine prefix scans over the group.  Two things make it pay:
+//   - the rays of a wave span 1 / sqrt(G) of the pixels, so their corners fit the wave's window at
+//     pixel pitches where 8 x 8 rays overflow it and every sample moves the window;
+//   - small images have G times the waves, each 1 / G of the serial samples.
+// A lane's samples lie G steps apart, so it keeps no corner cache and no per-cell sums.
+template <int LAYOUT, int DT, int KMAX, bool FG, int G, typename Win>
+__device__ __forceinline__ void march_bwd_group(const KFeat &feat, const KGrid &g, const TFShared<KMAX> &sh,
+                                                const float (&kx)[KMAX], const KRender &rp, float invg, const GroupRay &r,
+                                                int kl, float T_last, float4 gr, int K, double *tfa, float *dvol,
+                                                double *win, float *dfeat, float &gmb)
+{
+    const float gC0 = gr.x, gC1 = gr.y, gC2 = gr.z, gA = gr.w;
+    float Tc = T_last, S0 = 0.f, S1 = 0.f, S2 = 0.f, R = 1.f;  // of the group: before its next samples
+    Vox<LAYOUT, DT> vx;
+    vx.init(feat, g);
+    const uint32_t esh = (LAYOUT != DVR_INTERLEAVED) ? (DT == DVR_F32 ? 2u : 1u) : (DT == DVR_F32 ? 5u : 4u);
+    SegAcc<tf_copies(KMAX)> sa;
+    sa.seg = -2;
+    for (int e = 0; e < 4; ++e) sa.lo[e] = sa.hi[e] = 0.f;
+    Win dw;
+    dw.w = win;
+    dw.live = false;
+    dw.o[0] = dw.o[1] = dw.o[2] = 0;
+    dw.ext[0] = dw.ext[1] = dw.ext[2] = 2;
+    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(kl));
+    int k = kmax - (int)(threadIdx.x & (G - 1));
+    int64_t q[3];  // q0 + k dq: the position of every sample but the last (wraps harmlessly past it)
+    for (int a = 0; a < 3; ++a) q[a] = (int64_t)((uint64_t)r.q0[a] + (uint64_t)(int64_t)k * (uint64_t)r.dq[a]);
+    for (int kb = kmax; kb >= 0; kb -= G, k -= G) {
+        const bool act = k >= 0 && k <= kl;
+        const float dk = (k == r.N - 1) ? r.dlast : r.delta;
+        Corners c;
+        int cell[3] = {0, 0, 0};
+        Opt o;
+        o.om = 1.f;
+        o.alpha = o.tau = o.M = 0.f;
+        o.c[0] = o.c[1] = o.c[2] = 0.f;
+        o.seg = -1;
+        o.dI = 0.f;
+        Chan ch;
+        if (act) {
+            int64_t p[3];
+            for (int a = 0; a < 3; ++a) p[a] = (k == r.N - 1) ? r.ql[a] : q[a];
+            corner_setup(p, vx.sx, vx.sy, vx.sz, c);
+            cell[0] = (int)(p[0] >> 32);
+            cell[1] = (int)(p[1] >> 32);
+            cell[2] = (int)(p[2] >> 32);
+            CornerCache<LAYOUT, DT> cc;
+            cc.reset();
+            cc.need_I(vx, c);
+            ch.I = cc.interp(c, 0);
+            tf_eval<KMAX>(sh, kx, ch.I, o);
+            cc.need_feat(vx, c);
+            ch.g[0] = cc.interp(c, 1);
+            ch.g[1] = cc.interp(c, 2);
+            ch.g[2] = cc.interp(c, 3);
+            ch.k = cc.interp(c, 4);
+            ch.V = cc.interp(c, 5);
+            eq4(rp, invg, ch, dk, o);
+        }
+        // T before sample k: divided by 1 - alpha of every sample from k_last - 1 down to k
+        float P = k < kl ? o.om : 1.f;
+        group_prod<G>(P);
+        const float T = Tc / P;
+        Tc = group_last<G>(T);
+        // S and R of the samples behind k
+        float a = o.om, b[3] = {o.alpha * o.c[0], o.alpha * o.c[1], o.alpha * o.c[2]};
+        group_affine<G>(a, b);
+        const float I0 = fmaf(a, S0, b[0]), I1 = fmaf(a, S1, b[1]), I2 = fmaf(a, S2, b[2]), IR = a * R;
+        const float E0 = group_up<G, 1>(I0, S0), E1 = group_up<G, 1>(I1, S1), E2 = group_up<G, 1>(I2, S2);
+        const float ER = group_up<G, 1>(IR, R);
+        S0 = group_last<G>(I0);
+        S1 = group_last<G>(I1);
+        S2 = group_last<G>(I2);
+        R = group_last<G>(IR);
+        float Ib = 0.f;
+        float fv[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+        if (act) {
+            const float Ta = T * o.alpha;
+            const float dal = T * (gC0 * (o.c[0] - E0) + gC1 * (o.c[1] - E1) + gC2 * (o.c[2] - E2) + gA * ER);
+            const float vb[4] = {gC0 * Ta, gC1 * Ta, gC2 * Ta, dal * o.om * o.M * dk};
+            if constexpr (FG) {
+                const float Mb = dal * o.om * o.tau * dk;
+                if (Mb != 0.f) feature_grads(rp, invg, ch, Mb, fv, gmb);
+            }
+            const int key = o.seg < 0 ? -1 : o.seg;
+            if (key != sa.seg) {
+                if (sa.seg != -2) sa.flush(tfa, K);
+                sa.seg = key;
+            }
+            if (key < 0 || key >= K - 1) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sa.lo[e] += vb[e];
+            } else {
+                const float t = o.dI * sh.iw[key];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    sa.lo[e] = fmaf(1.f - t, vb[e], sa.lo[e]);
+                    sa.hi[e] = fmaf(t, vb[e], sa.hi[e]);
+                }
+                const float4 s = sh.s[key];
+                Ib = vb[0] * s.x + vb[1] * s.y + vb[2] * s.z + vb[3] * s.w;
+            }
+        }
+        if (FG || dvol) {
+            const float val[6] = {dvol ? Ib : 0.f, fv[0], fv[1], fv[2], fv[3], fv[4]};
+            bool need = act && Ib != 0.f;
+            if constexpr (FG)
+                need = act && (val[0] != 0.f || val[1] != 0.f || val[2] != 0.f || val[3] != 0.f || val[4] != 0.f ||
+                               val[5] != 0.f);
+            float cw[8];
+            if constexpr (!FG) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) cw[e] = need ? c.w[e] * Ib : 0.f;
+                quad_merge(need, need ? (int)(c.off[0] >> esh) : (int)(0x80000000u | threadIdx.x), cw);
+            }
+            bool in = need && dw.live && dw.holds(cell);
+            const uint64_t miss = __ballot(need && !in);
+            if (miss) {
+                const int lead = __ffsll((unsigned long long)miss) - 1;
+                int64_t dql[3];
+                for (int x = 0; x < 3; ++x) dql[x] = __shfl(r.dq[x], lead, 64);
+                if (dw.live) dw.flush(dvol, dfeat, g);
+                dw.place(need, cell, dql, G);
+                in = need && dw.holds(cell);
+            }
+            if (in) {
+                const int w0 = dw.index(cell);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    if constexpr (FG) {
+                        // the four lanes of a quad take the corners in different orders (corner e XOR
+                        // 0, 7, 3, 4), so samples sharing a cell add to different entries at a time
+                        const int c0 = (threadIdx.x & 1u) ? -1 : 0, c1 = (threadIdx.x & 2u) ? -1 : 0;
+                        const int ca = (dw.corner(e) & ~c0) | (dw.corner(e ^ 7) & c0);
+                        const int cb = (dw.corner(e ^ 3) & ~c0) | (dw.corner(e ^ 4) & c0);
+                        const float wa = (threadIdx.x & 1u) ? c.w[e ^ 7] : c.w[e], wb = (threadIdx.x & 1u) ? c.w[e ^ 4] : c.w[e ^ 3];
+                        const float w = (threadIdx.x & 2u) ? wb : wa;
+                        double *pw = win + Win::swz(w0 + ((ca & ~c1) | (cb & c1)));
+#pragma unroll
+                        for (int ch6 = 0; ch6 < 6; ++ch6)
+                            __hip_atomic_fetch_add(pw + ch6 * Win::kVox, (double)(w * val[ch6]), __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    } else {
+                        __hip_atomic_fetch_add(win + Win::swz(w0 + dw.corner(e)), (double)cw[e], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    }
+                }
+            } else if (need) {
+                const uint32_t nx = (uint32_t)g.n[0], plane = nx * (uint32_t)g.n[1];
+                const size_t N = (size_t)plane * (size_t)g.n[2];
+                const uint32_t v0 = (uint32_t)cell[2] * plane + (uint32_t)cell[1] * nx + (uint32_t)cell[0];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const uint32_t vi = v0 + (e & 1) + ((e >> 1) & 1) * nx + ((e >> 2) & 1) * plane;
+                    if constexpr (FG) {
+                        if (dvol && val[0] != 0.f) atomicAdd(dvol + vi, c.w[e] * val[0]);
+#pragma unroll
+                        for (int f = 1; f < 6; ++f)
+                            if (val[f] != 0.f) atomicAdd(dfeat + (size_t)(f - 1) * N + vi, c.w[e] * val[f]);
+                    } else {
+                        atomicAdd(dvol + vi, cw[e]);
+                    }
+                }
+            }
+        }
+        for (int x = 0; x < 3; ++x) q[x] = (int64_t)((uint64_t)q[x] - (uint64_t)G * (uint64_t)r.dq[x]);
+    }
     if ((FG || dvol) && dw.live) dw.flush(dvol, dfeat, g);
     if (sa.seg != -2) sa.flush(tfa, K);
 }
