@@ -54,28 +54,30 @@ __device__ __forceinline__ uint32_t tile_of(uint32_t slot, uint32_t slots)
     return (slot & 7u) * (slots / 8u) + (slot >> 3);
 }
 
-// camera and pixel of this lane in the 16 x 16 pixel tile t (a wave takes 8 x 8 of it).  MORTON: the lanes
-// take their pixels in Morton order (lane bits x0 y0 x1 y1 x2 y2), so each quad of lanes is a 2 x 2
-// pixel block and each row of 16 a 4 x 4 one; otherwise row-major.
-template <bool MORTON = false>
+// Camera and pixel of this lane's ray in tile t: 16 x 16 pixels of which a wave takes 8 x 8, or, with G =
+// 4 or 16 lanes per ray, 8 x 8 and 4 x 4 or 4 x 4 and 2 x 2.  MORTON: a wave's rays take their pixels in
+// Morton order (bits x0 y0 x1 y1 x2 y2), so each quad of lanes (G = 1) is a 2 x 2 pixel block and each
+// row of 16 a 4 x 4 one; otherwise row-major.
+template <bool MORTON = false, int G = 1>
 __device__ __forceinline__ void pixel_of(const KLaunch &L, uint32_t t, uint32_t &cam, int &pi, int &pj, bool &valid)
 {
-    const uint32_t tiles_x = (L.W + 15) / 16, tiles_y = (L.H + 15) / 16;
+    constexpr uint32_t S = G == 1 ? 16 : (G == 4 ? 8 : 4);
+    const uint32_t tiles_x = (L.W + S - 1) / S, tiles_y = (L.H + S - 1) / S;
     const uint32_t tpv = tiles_x * tiles_y;
     cam = t / tpv;
     const uint32_t tt = t - cam * tpv;
     const uint32_t ty = tt / tiles_x, tx = tt - ty * tiles_x;
-    const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
+    const uint32_t lane = (threadIdx.x & 63u) / G, wv = threadIdx.x >> 6;
     uint32_t lx, ly;
     if (MORTON) {
         lx = (lane & 1u) | ((lane >> 1) & 2u) | ((lane >> 2) & 4u);
         ly = ((lane >> 1) & 1u) | ((lane >> 2) & 2u) | ((lane >> 3) & 4u);
     } else {
-        lx = lane & 7u;
-        ly = lane >> 3;
+        lx = lane % (S / 2);
+        ly = lane / (S / 2);
     }
-    pi = (int)(tx * 16u + (wv & 1u) * 8u + lx);
-    pj = (int)(ty * 16u + (wv >> 1) * 8u + ly);
+    pi = (int)(tx * S + (wv & 1u) * (S / 2) + lx);
+    pj = (int)(ty * S + (wv >> 1) * (S / 2) + ly);
     valid = cam < (uint32_t)L.ncam && pi < L.W && pj < L.H;
 }
 
@@ -83,10 +85,10 @@ __device__ __forceinline__ void pixel_of(const KLaunch &L, uint32_t t, uint32_t 
 // per SIMD); held to five waves (96 VGPRs, a few spilled values) it runs 7 % faster on the head
 // (0.296 against 0.318 ms per view).  The FP32 layouts and the other FP16 ones spill far more at
 // five waves and are slower, so they keep the default.
-template <int LAYOUT, int DT, int KMAX>
-__global__ __launch_bounds__(256, (LAYOUT == DVR_QUAD && DT == DVR_F16) ? 5 : 1) void k_render(KFeat feat, KGrid g,
-                                                                                            KTF tf, KRender rp,
-                                                                                            KLaunch L)
+// G: lanes per ray.
+template <int LAYOUT, int DT, int KMAX, int G>
+__global__ __launch_bounds__(256, (LAYOUT == DVR_QUAD && DT == DVR_F16 && G == 1) ? 5 : 1) void k_render(
+    KFeat feat, KGrid g, KTF tf, KRender rp, KLaunch L)
 {
     __shared__ TFShared<KMAX> sh;
     float kx[KMAX];
@@ -95,20 +97,23 @@ __global__ __launch_bounds__(256, (LAYOUT == DVR_QUAD && DT == DVR_F16) ? 5 : 1)
     uint32_t cam;
     int pi, pj;
     bool valid;
-    pixel_of(L, tile_of(blockIdx.x, gridDim.x), cam, pi, pj, valid);
+    pixel_of<false, G>(L, tile_of(blockIdx.x, gridDim.x), cam, pi, pj, valid);
     const float gm = *feat.gmax;
     const float invg = gm > 0.f ? 1.f / gm : 0.f;
     RayGeo r;
     r.N = 0;
     if (valid) r = ray_setup(load_cam(L, cam), pi, pj, g);
-    const RayOut o = march_fwd<LAYOUT, DT, KMAX>(feat, g, sh, kx, rp, invg, r);
-    if (valid) {
+    RayOut o;
+    if constexpr (G == 1) o = march_fwd<LAYOUT, DT, KMAX>(feat, g, sh, kx, rp, invg, r);
+    else o = march_fwd_group<LAYOUT, DT, KMAX, G>(feat, g, sh, kx, rp, invg, r);
+    const bool first = G == 1 || (threadIdx.x & (G - 1)) == 0;  // one lane of the group writes
+    if (valid && first) {
         const size_t pix = ((size_t)(L.cam_base + cam) * L.H + pj) * L.W + pi;
         reinterpret_cast<float4 *>(L.out)[pix] = make_float4(o.C0, o.C1, o.C2, o.A);
         if (L.T_last) L.T_last[pix] = o.Tprev;
         if (L.k_last) L.k_last[pix] = o.last;
     }
-    if (L.counters) count_samples<4>(L.counters, o.last, o.shaded);
+    if (L.counters) count_samples<4>(L.counters, first ? o.last : -1, o.shaded);
 }
 
 // Gather ceiling of k_render (dvr_render_gather): the same rays, samples and loads, without the
@@ -232,12 +237,18 @@ __global__ __launch_bounds__(256) void k_render_bwd(KFeat feat, KGrid g, KTF tf,
 // ------------------------------------------------------------------------------------------------
 enum { kFwd = 0, kBwd = 1, kGather = 2 };
 
+// workgroups of the launch: one per tile, rounded up to the 8 XCDs
+static uint32_t tile_blocks(const KLaunch &L, int side)
+{
+    const uint32_t tiles = (uint32_t)((L.W + side - 1) / side) * (uint32_t)((L.H + side - 1) / side) * (uint32_t)L.ncam;
+    return (tiles + 7u) / 8u * 8u;
+}
+
 template <int LAYOUT, int DT, int KMAX>
 static hipError_t launch_fwd_t(const KFeat &f, const KGrid &g, const KTF &tf, const KRender &rp, const KLaunch &L,
                                hipStream_t st, int mode, int lanes)
 {
-    const uint32_t tiles = (uint32_t)((L.W + 15) / 16) * (uint32_t)((L.H + 15) / 16) * (uint32_t)L.ncam;
-    const uint32_t blocks = (tiles + 7u) / 8u * 8u;
+    const uint32_t blocks = tile_blocks(L, 16);
     // a tile's blocks are dealt to as many workgroups as evens the load out (about 4096); more would add
     // to the error of the TF gradient, which every workgroup adds to the same few FP32 words
     uint32_t split = 1;
@@ -247,7 +258,12 @@ static hipError_t launch_fwd_t(const KFeat &f, const KGrid &g, const KTF &tf, co
     if (mode == kGather) {
         hipLaunchKernelGGL((k_render_gather<LAYOUT, DT, KMAX>), dim3(blocks), dim3(256), 0, st, f, g, tf, rp, L);
     } else if (mode == kFwd) {
-        hipLaunchKernelGGL((k_render<LAYOUT, DT, KMAX>), dim3(blocks), dim3(256), 0, st, f, g, tf, rp, L);
+        if (lanes == 16)
+            hipLaunchKernelGGL((k_render<LAYOUT, DT, KMAX, 16>), dim3(tile_blocks(L, 4)), dim3(256), 0, st, f, g, tf, rp, L);
+        else if (lanes == 4)
+            hipLaunchKernelGGL((k_render<LAYOUT, DT, KMAX, 4>), dim3(tile_blocks(L, 8)), dim3(256), 0, st, f, g, tf, rp, L);
+        else
+            hipLaunchKernelGGL((k_render<LAYOUT, DT, KMAX, 1>), dim3(blocks), dim3(256), 0, st, f, g, tf, rp, L);
     } else if (L.dfeat) {
         if (lanes == 16) DVR_BWD(true, 16);
         else if (lanes == 4) DVR_BWD(true, 4);
@@ -304,6 +320,20 @@ static int bwd_lanes(const KLaunch &L, const KGrid &g)
     return 1;
 }
 
+// Lanes per ray of the forward raymarch, by the number of rays of the launch: with one lane a ray the
+// chip needs about 260 000 rays (four waves a SIMD) to hide a ray's chain of dependent samples.  One
+// view of a 64^3 volume in the quad layout, 1 / 4 / 16 lanes: 128^2 214 / 66 / 66 us, 256^2 201 / 121 /
+// 120, 512^2 393 / 231 / 365, 768^2 404 / 444 / 780; of a head: 398 / 128 / 96, 386 / 182 / 187, 529 /
+// 268 / 568, 543 / 477 / 1204.  16 lanes hold a wave's samples closer together, which pays longer where a
+// sample touches more cache lines: FP32 (64^3 at 256^2, split 174 us with 4 lanes, 134 with 16; FP16
+// interleaved 108, 128) and above all FP32 planes (267, 155; 384^2 328, 299).
+static int fwd_lanes(const KLaunch &L, const KFeat &f)
+{
+    const int64_t rays = (int64_t)L.W * L.H * L.ncam;
+    const int64_t most16 = f.dtype == DVR_F16 ? 40960 : (f.layout == DVR_PLANAR ? 163840 : 81920);
+    return rays <= most16 ? 16 : (rays <= 327680 ? 4 : 1);
+}
+
 static hipError_t launch_any(const RenderArgs &a, hipStream_t st, int mode)
 {
     for (int c0 = 0; c0 < a.ncam; c0 += kCamChunk) {
@@ -311,7 +341,7 @@ static hipError_t launch_any(const RenderArgs &a, hipStream_t st, int mode)
         L.ncam = a.ncam - c0 < kCamChunk ? a.ncam - c0 : kCamChunk;
         L.cam_base = c0;
         for (int i = 0; i < L.ncam; ++i) L.cams[i] = a.cams[c0 + i];
-        const int lanes = mode == kBwd ? bwd_lanes(L, a.grid) : 1;
+        const int lanes = mode == kBwd ? bwd_lanes(L, a.grid) : (mode == kFwd ? fwd_lanes(L, a.feat) : 1);
         hipError_t e;
         const int lay = a.feat.layout, dt = a.feat.dtype;
         if (lay == DVR_PLANAR && dt == DVR_F32) e = launch_k<DVR_PLANAR, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);

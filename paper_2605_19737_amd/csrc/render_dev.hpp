@@ -1545,4 +1545,116 @@ __device__ __forceinline__ void march_bwd_group(const KFeat &feat, const KGrid &
     if (sa.seg != -2) sa.flush(tfa, K);
 }
 
+// the value of lane I of the group
+template <int G, int I>
+__device__ __forceinline__ float group_get(float v)
+{
+    constexpr int kCtrl = G == 16 ? 0x150 + I : I * 0x55;  // row_newbcast:I, quad_perm [I,I,I,I]
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kCtrl, 0xF, 0xF, false));
+}
+
+// What a group of march_fwd_group carries from sample to sample; every lane holds the same values.
+struct GroupAcc {
+    float C0, C1, C2, A, T, Tprev;
+    int last, shaded;
+};
+
+// Composites the samples of lanes I, I + 1, ... of the group in order, exactly as march_fwd does one
+// after another (a transparent sample has al = 0 and om = 1, which change nothing).  k: the sample of
+// lane 0; returns whether the ray goes on.
+template <int G, int I = 0>
+__device__ __forceinline__ bool group_over(GroupAcc &o, int k, int N, float Tstop, float al, float om, const float (&c)[3],
+                                           bool shaded)
+{
+    if constexpr (I == G) {
+        return true;
+    } else {
+        const float ali = group_get<G, I>(al), omi = group_get<G, I>(om);
+        const float c0 = group_get<G, I>(c[0]), c1 = group_get<G, I>(c[1]), c2 = group_get<G, I>(c[2]);
+        if (k + I >= N) return false;  // uniform over the group, like the exit below
+        o.Tprev = o.T;
+        const float ta = o.T * ali;
+        o.C0 = fmaf(ta, c0, o.C0);
+        o.C1 = fmaf(ta, c1, o.C1);
+        o.C2 = fmaf(ta, c2, o.C2);
+        o.A += ta;
+        o.T = o.T * omi;
+        o.last = k + I;
+        if (shaded && (int)(threadIdx.x & (G - 1)) == I) ++o.shaded;
+        if (o.T <= Tstop) return false;
+        return group_over<G, I + 1>(o, k, N, Tstop, al, om, c, shaded);
+    }
+}
+
+// march_fwd with G lanes per ray: lane j of a group evaluates samples j, j + G, ... and the group
+// composites G samples at a time in ray order, the same operations on the same values (the same bits).
+// For images of few rays: each wave holds 64 / G rays and a ray's serial chain is the compositing
+// alone, while the gathers and Eq. 4 of G samples run side by side.
+template <int LAYOUT, int DT, int KMAX, int G>
+__device__ __forceinline__ RayOut march_fwd_group(const KFeat &feat, const KGrid &g, const TFShared<KMAX> &sh,
+                                                  const float (&kx)[KMAX], const KRender &rp, float invg, const RayGeo &r)
+{
+    GroupAcc o_ = {0.f, 0.f, 0.f, 0.f, 1.f, 1.f, -1, 0};
+    if (r.N > 0) {
+        Vox<LAYOUT, DT> vx;
+        vx.init(feat, g);
+        const int j = (int)(threadIdx.x & (G - 1));
+        int64_t q[3];  // q0 + k dq: the position of every sample but the last
+        for (int a = 0; a < 3; ++a) q[a] = r.q0[a] + (int64_t)j * r.dq[a];
+        const bool skip = feat.bricks != nullptr;
+        const int nbt = feat.nb[0] * feat.nb[1] * feat.nb[2];
+        Buf bm;
+        if (skip) bm = make_buf(feat.bricks + 2 * nbt, (uint32_t)((nbt + 31) / 32) * 4u);
+        for (int kb = 0; kb < r.N; kb += G) {
+            const int k = kb + j;
+            float al = 0.f, om = 1.f, c3[3] = {0.f, 0.f, 0.f};
+            bool shaded = false;
+            if (k < r.N) {
+                const bool lastk = k == r.N - 1;
+                int64_t p[3];
+                for (int a = 0; a < 3; ++a) p[a] = lastk ? r.ql[a] : q[a];
+                bool empty = false;
+                if (skip) {
+                    const int bi = ((int)(p[2] >> 34) * feat.nb[1] + (int)(p[1] >> 34)) * feat.nb[0] + (int)(p[0] >> 34);
+                    const uint32_t wd = __builtin_amdgcn_raw_buffer_load_b32(bm.r, (uint32_t)(bi >> 5) * 4u, 0, 0);
+                    empty = ((wd >> (bi & 31)) & 1u) != 0u;
+                }
+                if (!empty) {
+                    Corners c;
+                    corner_setup(p, vx.sx, vx.sy, vx.sz, c);
+                    CornerCache<LAYOUT, DT> cc;
+                    cc.reset();
+                    Chan ch;
+                    cc.need_I(vx, c);
+                    ch.I = cc.interp(c, 0);
+                    Opt o;
+                    tf_eval<KMAX>(sh, kx, ch.I, o);
+                    if (o.tau > 0.f) {
+                        shaded = true;
+                        cc.need_feat(vx, c);
+                        ch.g[0] = cc.interp(c, 1);
+                        ch.g[1] = cc.interp(c, 2);
+                        ch.g[2] = cc.interp(c, 3);
+                        ch.k = cc.interp(c, 4);
+                        ch.V = cc.interp(c, 5);
+                        eq4(rp, invg, ch, lastk ? r.dlast : r.delta, o);
+                        al = o.alpha;
+                        om = o.om;
+                        c3[0] = o.c[0];
+                        c3[1] = o.c[1];
+                        c3[2] = o.c[2];
+                    }
+                }
+            }
+            if (!group_over<G>(o_, kb, r.N, rp.Tstop, al, om, c3, shaded)) break;
+            for (int a = 0; a < 3; ++a) q[a] += (int64_t)G * r.dq[a];
+        }
+    }
+    RayOut o;
+    o.C0 = o_.C0; o.C1 = o_.C1; o.C2 = o_.C2; o.A = o_.A; o.T = o_.T; o.Tprev = o_.Tprev;
+    o.last = o_.last;
+    o.shaded = o_.shaded;
+    return o;
+}
+
 }  // namespace dvr

@@ -74,3 +74,36 @@ def test_adjoint_lane_groups(case, layout):
     errs["gmax"] = abs(float(fg["gmax"]) - rfg["gmax"]) / max(abs(rfg["gmax"]), np.abs(rfg["g"]).sum() * 1e-3)
     print("  " + " ".join(f"{n}={e:.1e}" for n, e in errs.items()), flush=True)
     assert max(errs.values()) <= TOL, errs
+
+
+@pytest.mark.parametrize("layout", [abi.DVR_PLANAR, abi.DVR_INTERLEAVED, abi.DVR_SPLIT, abi.DVR_QUAD])
+@pytest.mark.parametrize("dtype,et,bricks,persp,step", [
+    (torch.float32, 0.99, False, True, 0.5), (torch.float32, 0.0, True, False, 0.37), (torch.float16, 0.9, True, True, 0.5)])
+def test_forward_lane_groups_bit_identical(layout, dtype, et, bricks, persp, step):
+    """The same views in one launch of 32 (one lane per ray), in launches of 4 (4 lanes) and one by one
+    (16 lanes): image, ray state and sample counts agree bit for bit."""
+    w = phantoms.c2(8, 8, views=[0])
+    vol = to_dev(w.vol[40:100:2, 60:160:2, 30:150:2], dtype)
+    h = (2.0, 2.0, 2.0)
+    make = phantoms.persp_camera if persp else phantoms.ortho_camera
+    cams = [make(tuple(vol.shape[::-1]), h, 11.25 * v, 15.0, 129, 101) for v in range(32)]
+    kn, tf = to_dev(w.tf_knots), to_dev(w.tf_rgba)
+    prm = dict(w.params, et_alpha=et, step_vox=step)
+    print(f"[lane groups] forward layout {layout} {dtype} et {et}", flush=True)
+    f = dvr.features(vol, h, [2.0], c=0.4, dtype=dtype, layout=layout)
+    f = f if bricks else f.without_bricks()
+    sampled = vol if layout in (abi.DVR_PLANAR, abi.DVR_SPLIT) else None
+
+    def run(n):
+        parts, total = [], torch.zeros(2, dtype=torch.int64, device="cuda")
+        for i in range(0, 32, n):
+            cnt = torch.zeros(2, dtype=torch.int64, device="cuda")
+            parts.append(dvr.render(sampled, f, kn, tf, prm, cams[i:i + n], counters=cnt))
+            total += cnt
+        return [torch.cat([p[e] for p in parts]) for e in range(3)] + [total]
+
+    one, four, sixteen = run(32), run(4), run(1)
+    assert int(one[2].max()) > 16
+    for other in (four, sixteen):
+        for a, b in zip(one, other):
+            assert torch.equal(a, b)
