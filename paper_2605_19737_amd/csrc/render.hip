@@ -28,6 +28,9 @@
 
 namespace dvr {
 
+// side in pixels of a workgroup's tile with G lanes per ray
+__host__ __device__ constexpr uint32_t tile_side(int G) { return G == 1 ? 16 : (G == 4 ? 8 : 4); }
+
 // ------------------------------------------------------------------------------------------------
 // The camera index is uniform over the workgroup; copying the record field by field keeps the
 // by-value kernel argument block in the constant segment (taking its address would make the
@@ -47,26 +50,43 @@ __device__ __forceinline__ KCam load_cam(const KLaunch &L, uint32_t cam)
     return c;
 }
 
-// XCD-aware order: consecutive dispatch slots go to different XCDs, so the tile of slot b is
-// (b % 8) * (slots / 8) + b / 8; each XCD then walks a contiguous range of tiles.
-__device__ __forceinline__ uint32_t tile_of(uint32_t slot, uint32_t slots)
-{
-    return (slot & 7u) * (slots / 8u) + (slot >> 3);
-}
-
-// Camera and pixel of this lane's ray in tile t: 16 x 16 pixels of which a wave takes 8 x 8, or, with G =
-// 4 or 16 lanes per ray, 8 x 8 and 4 x 4 or 4 x 4 and 2 x 2.  MORTON: a wave's rays take their pixels in
+// Camera and pixel of this lane's ray in the workgroup's tile: 16 x 16 pixels of which a wave takes 8 x 8,
+// or, with G = 4 or 16 lanes per ray, 8 x 8 and 4 x 4 or 4 x 4 and 2 x 2.
+//
+// Which tile a workgroup takes decides what its XCD's L2 holds and how even the XCDs' loads are:
+// consecutive workgroups go to different XCDs, each with an L2 of its own.  Views in multiples of eight:
+// each XCD takes a contiguous eighth of the launch, whole views, row by row.  Otherwise (L.spread) that
+// gives rows of background to some XCDs and the whole object to others, so the tiles are grouped into
+// blocks of 2 x 2, which the XCDs take in turn, rotated from one round of eight to the next so that none
+// keeps a column of the image or the centre of every view: one 1024^2 view of a head 0.81 -> 0.55 ms, two
+// 2048^2 views of a 512 x 512 x 400 volume 14.2 -> 7.9.  (Eight views of the head: 2.65 ms as whole
+// views, 2.76 dealt out; their adjoint on a 128^3 volume 3.85 against 4.23.)
+//
+// MORTON: a wave's rays take their pixels in
 // Morton order (bits x0 y0 x1 y1 x2 y2), so each quad of lanes (G = 1) is a 2 x 2 pixel block and each
 // row of 16 a 4 x 4 one; otherwise row-major.
 template <bool MORTON = false, int G = 1>
-__device__ __forceinline__ void pixel_of(const KLaunch &L, uint32_t t, uint32_t &cam, int &pi, int &pj, bool &valid)
+__device__ __forceinline__ void pixel_of(const KLaunch &L, uint32_t &cam, int &pi, int &pj, bool &valid)
 {
-    constexpr uint32_t S = G == 1 ? 16 : (G == 4 ? 8 : 4);
-    const uint32_t tiles_x = (L.W + S - 1) / S, tiles_y = (L.H + S - 1) / S;
-    const uint32_t tpv = tiles_x * tiles_y;
-    cam = t / tpv;
-    const uint32_t tt = t - cam * tpv;
-    const uint32_t ty = tt / tiles_x, tx = tt - ty * tiles_x;
+    constexpr uint32_t S = tile_side(G);
+    uint32_t tx, ty;
+    if (L.spread) {
+        const uint32_t bx = ((uint32_t)L.W + 2u * S - 1u) / (2u * S), by = ((uint32_t)L.H + 2u * S - 1u) / (2u * S);
+        const uint32_t round = blockIdx.x >> 5, w = (blockIdx.x >> 3) & 3u;  // this XCD's block and tile in it
+        const uint32_t blk = round * 8u + ((blockIdx.x + 5u * round + (round >> 3) + (round >> 6)) & 7u);
+        cam = blk / (bx * by);
+        const uint32_t bb = blk - cam * (bx * by);
+        const uint32_t b_y = bb / bx, b_x = bb - b_y * bx;
+        tx = 2u * b_x + (w & 1u);
+        ty = 2u * b_y + (w >> 1);
+    } else {
+        const uint32_t t = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+        const uint32_t nx = ((uint32_t)L.W + S - 1u) / S, ny = ((uint32_t)L.H + S - 1u) / S;
+        cam = t / (nx * ny);
+        const uint32_t tt = t - cam * (nx * ny);
+        ty = tt / nx;
+        tx = tt - ty * nx;
+    }
     const uint32_t lane = (threadIdx.x & 63u) / G, wv = threadIdx.x >> 6;
     uint32_t lx, ly;
     if (MORTON) {
@@ -97,7 +117,7 @@ __global__ __launch_bounds__(256, (LAYOUT == DVR_QUAD && DT == DVR_F16 && G == 1
     uint32_t cam;
     int pi, pj;
     bool valid;
-    pixel_of<false, G>(L, tile_of(blockIdx.x, gridDim.x), cam, pi, pj, valid);
+    pixel_of<false, G>(L, cam, pi, pj, valid);
     const float gm = *feat.gmax;
     const float invg = gm > 0.f ? 1.f / gm : 0.f;
     RayGeo r;
@@ -129,7 +149,7 @@ __global__ __launch_bounds__(256) void k_render_gather(KFeat feat, KGrid g, KTF 
     uint32_t cam;
     int pi, pj;
     bool valid;
-    pixel_of(L, tile_of(blockIdx.x, gridDim.x), cam, pi, pj, valid);
+    pixel_of(L, cam, pi, pj, valid);
     const size_t pix = valid ? ((size_t)(L.cam_base + cam) * L.H + pj) * L.W + pi : 0;
     const int kl = valid ? L.k_last[pix] : -1;
     RayGeo r;
@@ -169,7 +189,7 @@ __global__ __launch_bounds__(256) void k_render_bwd(KFeat feat, KGrid g, KTF tf,
     uint32_t cam;
     int pi, pj;
     bool valid;
-    pixel_of<true>(L, tile_of(blockIdx.x, gridDim.x), cam, pi, pj, valid);
+    pixel_of<true>(L, cam, pi, pj, valid);
     const int pix = valid ? (int)(((size_t)(L.cam_base + cam) * L.H + pj) * L.W + pi) : -1;
     const int kl = valid ? L.k_last[pix] : -1;
     RayGeo r;
@@ -237,18 +257,19 @@ __global__ __launch_bounds__(256) void k_render_bwd(KFeat feat, KGrid g, KTF tf,
 // ------------------------------------------------------------------------------------------------
 enum { kFwd = 0, kBwd = 1, kGather = 2 };
 
-// workgroups of the launch: one per tile, rounded up to the 8 XCDs
-static uint32_t tile_blocks(const KLaunch &L, int side)
+// Workgroups of a launch with G lanes per ray, rounded up to the 8 XCDs: one a tile, or four a block.
+static uint32_t tile_blocks(const KLaunch &L, int G)
 {
-    const uint32_t tiles = (uint32_t)((L.W + side - 1) / side) * (uint32_t)((L.H + side - 1) / side) * (uint32_t)L.ncam;
-    return (tiles + 7u) / 8u * 8u;
+    const uint32_t side = tile_side(G) * (L.spread ? 2u : 1u);
+    const uint32_t n = (((uint32_t)L.W + side - 1u) / side) * (((uint32_t)L.H + side - 1u) / side) * (uint32_t)L.ncam;
+    return (n + 7u) / 8u * (L.spread ? 32u : 8u);
 }
 
 template <int LAYOUT, int DT, int KMAX>
 static hipError_t launch_fwd_t(const KFeat &f, const KGrid &g, const KTF &tf, const KRender &rp, const KLaunch &L,
                                hipStream_t st, int mode, int lanes)
 {
-    const uint32_t blocks = tile_blocks(L, 16);
+    const uint32_t blocks = tile_blocks(L, mode == kFwd ? lanes : 1);
     // a tile's blocks are dealt to as many workgroups as evens the load out (about 4096); more would add
     // to the error of the TF gradient, which every workgroup adds to the same few FP32 words
     uint32_t split = 1;
@@ -259,9 +280,9 @@ static hipError_t launch_fwd_t(const KFeat &f, const KGrid &g, const KTF &tf, co
         hipLaunchKernelGGL((k_render_gather<LAYOUT, DT, KMAX>), dim3(blocks), dim3(256), 0, st, f, g, tf, rp, L);
     } else if (mode == kFwd) {
         if (lanes == 16)
-            hipLaunchKernelGGL((k_render<LAYOUT, DT, KMAX, 16>), dim3(tile_blocks(L, 4)), dim3(256), 0, st, f, g, tf, rp, L);
+            hipLaunchKernelGGL((k_render<LAYOUT, DT, KMAX, 16>), dim3(blocks), dim3(256), 0, st, f, g, tf, rp, L);
         else if (lanes == 4)
-            hipLaunchKernelGGL((k_render<LAYOUT, DT, KMAX, 4>), dim3(tile_blocks(L, 8)), dim3(256), 0, st, f, g, tf, rp, L);
+            hipLaunchKernelGGL((k_render<LAYOUT, DT, KMAX, 4>), dim3(blocks), dim3(256), 0, st, f, g, tf, rp, L);
         else
             hipLaunchKernelGGL((k_render<LAYOUT, DT, KMAX, 1>), dim3(blocks), dim3(256), 0, st, f, g, tf, rp, L);
     } else if (L.dfeat) {
@@ -286,13 +307,9 @@ static hipError_t launch_k(const KFeat &f, const KGrid &g, const KTF &tf, const 
     return launch_fwd_t<LAYOUT, DT, 64>(f, g, tf, rp, L, st, mode, lanes);
 }
 
-// Lanes per ray of the adjoint for one launch, by the pixel pitch of its views in voxels (the larger
-// of a pixel's two steps, at the box centre for a perspective view) and its number of rays.  Above
-// about 0.4 voxels a pixel the 8 x 8 rays of a wave stop fitting its window (feature gradients; 0.5
-// without them, whose window is larger and whose G = 1 form keeps its corner cache), above about 1.5
-// the 4 x 4 ones do.  Few rays take more lanes whatever the pitch: 64^3 at 256^2 has 1024 waves for
-// 1024 SIMDs with one lane a ray.
-static int bwd_lanes(const KLaunch &L, const KGrid &g)
+// Pixel pitch of a launch's views in voxels: the larger of a pixel's two steps, at the box centre for a
+// perspective view, the largest over the views.
+static double pixel_pitch(const KLaunch &L, const KGrid &g)
 {
     double pitch = 0.0;
     for (int c = 0; c < L.ncam; ++c) {
@@ -314,24 +331,37 @@ static int bwd_lanes(const KLaunch &L, const KGrid &g)
         }
         pitch = fmax(pitch, scale * sqrt(fmax(du, dv)));
     }
+    return pitch;
+}
+
+// Lanes per ray of the adjoint.  Above about 0.4 voxels a pixel the 8 x 8 rays of a wave stop fitting its
+// window (feature gradients; 0.65 without them, whose window is larger and whose G = 1 form keeps its
+// corner cache), above about 1.5 the 4 x 4 ones do.  Few rays take more lanes whatever the pitch: 64^3
+// at 256^2 has 1024 waves for 1024 SIMDs with one lane a ray.
+static int bwd_lanes(const KLaunch &L, double pitch)
+{
     const double rays = (double)L.W * L.H * L.ncam;
     if (pitch > 1.5 || rays <= 32768.0) return 16;
-    if (pitch > (L.dfeat ? 0.39 : 0.5) || rays <= 131072.0) return 4;
+    if (pitch > (L.dfeat ? 0.39 : 0.65) || rays <= 131072.0) return 4;
     return 1;
 }
 
-// Lanes per ray of the forward raymarch, by the number of rays of the launch: with one lane a ray the
-// chip needs about 260 000 rays (four waves a SIMD) to hide a ray's chain of dependent samples.  One
-// view of a 64^3 volume in the quad layout, 1 / 4 / 16 lanes: 128^2 214 / 66 / 66 us, 256^2 201 / 121 /
-// 120, 512^2 393 / 231 / 365, 768^2 404 / 444 / 780; of a head: 398 / 128 / 96, 386 / 182 / 187, 529 /
-// 268 / 568, 543 / 477 / 1204.  16 lanes hold a wave's samples closer together, which pays longer where a
-// sample touches more cache lines: FP32 (64^3 at 256^2, split 174 us with 4 lanes, 134 with 16; FP16
-// interleaved 108, 128) and above all FP32 planes (267, 155; 384^2 328, 299).
-static int fwd_lanes(const KLaunch &L, const KFeat &f)
+// Lanes per ray of the forward raymarch.  Few rays: with one lane a ray the chip needs a million rays to
+// hide a ray's chain of dependent samples and to even out the rays' lengths.  One view of a 64^3 volume
+// in the quad layout, 1 / 4 / 16 lanes: 128^2 214 / 66 / 66 us, 256^2 201 / 121 / 120, 512^2 393 / 231 / 365;
+// of a head: 398 / 128 / 96, 386 / 182 / 187, 529 / 268 / 568, 1024^2 552 / 437 (four such views: 1014 /
+// 989 at 768^2, eight 2654 / 3236 at 1024^2).  16 lanes hold a wave's samples closer together, which pays
+// longer where a sample touches more cache lines: FP32 (64^3 at 256^2, split 174 us with 4 lanes, 134
+// with 16; FP16 interleaved 108, 128) and above all FP32 planes (267, 155; 384^2 328, 299).  Coarse
+// views: 8 x 8 rays spread over many cache lines; a 152 x 229 x 177 volume at 512^2 x 32 (1.35 voxels a
+// pixel) 10.8 ms with one lane, 7.4 with 4, at 180^2 x 20 (3.8) 3.6, 2.05 and with 16 1.19; a 512 x 512 x
+// 400 one at 1024^2 x 2 (0.8) 3.1, 2.4.
+static int fwd_lanes(const KLaunch &L, const KFeat &f, double pitch)
 {
     const int64_t rays = (int64_t)L.W * L.H * L.ncam;
     const int64_t most16 = f.dtype == DVR_F16 ? 40960 : (f.layout == DVR_PLANAR ? 163840 : 81920);
-    return rays <= most16 ? 16 : (rays <= 327680 ? 4 : 1);
+    if (rays <= most16 || (pitch > 2.5 && rays <= 1200000)) return 16;
+    return rays <= 1200000 || pitch > 0.6 ? 4 : 1;
 }
 
 static hipError_t launch_any(const RenderArgs &a, hipStream_t st, int mode)
@@ -341,7 +371,9 @@ static hipError_t launch_any(const RenderArgs &a, hipStream_t st, int mode)
         L.ncam = a.ncam - c0 < kCamChunk ? a.ncam - c0 : kCamChunk;
         L.cam_base = c0;
         for (int i = 0; i < L.ncam; ++i) L.cams[i] = a.cams[c0 + i];
-        const int lanes = mode == kBwd ? bwd_lanes(L, a.grid) : (mode == kFwd ? fwd_lanes(L, a.feat) : 1);
+        L.spread = L.ncam % 8 != 0;
+        const double pitch = pixel_pitch(L, a.grid);
+        const int lanes = mode == kBwd ? bwd_lanes(L, pitch) : (mode == kFwd ? fwd_lanes(L, a.feat, pitch) : 1);
         hipError_t e;
         const int lay = a.feat.layout, dt = a.feat.dtype;
         if (lay == DVR_PLANAR && dt == DVR_F32) e = launch_k<DVR_PLANAR, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);

@@ -45,6 +45,7 @@ struct KRender {
 
 struct KLaunch {
     int32_t W, H, ncam, cam_base;
+    uint32_t spread;        // the XCDs take the launch's blocks of tiles in turn (else whole views)
     float *out;             // [cam][H][W][4]
     float *T_last;          // [cam][H][W] or null
     int32_t *k_last;        // [cam][H][W] or null
