@@ -69,24 +69,17 @@ template <bool MORTON = false, int G = 1>
 __device__ __forceinline__ void pixel_of(const KLaunch &L, uint32_t &cam, int &pi, int &pj, bool &valid)
 {
     constexpr uint32_t S = tile_side(G);
-    uint32_t tx, ty;
-    if (L.spread) {
-        const uint32_t bx = ((uint32_t)L.W + 2u * S - 1u) / (2u * S), by = ((uint32_t)L.H + 2u * S - 1u) / (2u * S);
-        const uint32_t round = blockIdx.x >> 5, w = (blockIdx.x >> 3) & 3u;  // this XCD's block and tile in it
-        const uint32_t blk = round * 8u + ((blockIdx.x + 5u * round + (round >> 3) + (round >> 6)) & 7u);
-        cam = blk / (bx * by);
-        const uint32_t bb = blk - cam * (bx * by);
-        const uint32_t b_y = bb / bx, b_x = bb - b_y * bx;
-        tx = 2u * b_x + (w & 1u);
-        ty = 2u * b_y + (w >> 1);
-    } else {
-        const uint32_t t = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-        const uint32_t nx = ((uint32_t)L.W + S - 1u) / S, ny = ((uint32_t)L.H + S - 1u) / S;
-        cam = t / (nx * ny);
-        const uint32_t tt = t - cam * (nx * ny);
-        ty = tt / nx;
-        tx = tt - ty * nx;
-    }
+    // one form for both (blocks of one tile in contiguous eighths): a branch here, though uniform and not
+    // taken, made the whole kernel 2.5 % slower on eight head views
+    const uint32_t sp = L.spread, lg = (G == 1 ? 4u : (G == 4 ? 3u : 2u)) + sp;
+    const uint32_t bx = ((uint32_t)L.W + (1u << lg) - 1u) >> lg, by = ((uint32_t)L.H + (1u << lg) - 1u) >> lg;
+    const uint32_t i = blockIdx.x >> 3, round = i >> (2u * sp), w = i & ((1u << (2u * sp)) - 1u);
+    const uint32_t turn = round * 8u + ((blockIdx.x + 5u * round + (round >> 3) + (round >> 6)) & 7u);
+    const uint32_t blk = sp ? turn : (blockIdx.x & 7u) * (gridDim.x >> 3) + round;
+    cam = blk / (bx * by);
+    const uint32_t bb = blk - cam * (bx * by);
+    const uint32_t b_y = bb / bx, b_x = bb - b_y * bx;
+    const uint32_t tx = (b_x << sp) + (w & 1u), ty = (b_y << sp) + (w >> 1);
     const uint32_t lane = (threadIdx.x & 63u) / G, wv = threadIdx.x >> 6;
     uint32_t lx, ly;
     if (MORTON) {
