@@ -502,7 +502,7 @@ def leg_fp16(w, vol, knots, tf, cams, stream, K, dvr, torch, log):
 
 
 def leg_batch(dev, stream, dvr, torch, np, log, nvol=64):
-    """64 uneven anisotropic volumes, features + 4 views each at 512^2, in one persistent graph launch
+    """64 uneven anisotropic volumes, features + 4 views each at 512^2, in one graph launch
     (autotuned), against the same work as per-call launches."""
     import phantoms
     log(f"batched leg: building {nvol} volumes")

@@ -339,13 +339,10 @@ dvr_status dvr_features_backward(const void *vol, int32_t vol_dtype, const dvr_g
 
 /* ---------------------------------------------------------------------------------------------
  * Batched launch: the feature pass of many volumes (uneven shapes, anisotropic spacing) and the
- * raymarch of many views of them, in one persistent kernel recorded in a HIP graph.  The kernel
- * drains a queue of work items in a fixed order (z-filter slabs, then feature tiles, then ray
- * tiles); a feature tile waits for its volume's z-filter items and a ray tile for its volume's
- * feature items (per-volume completion counters, release/acquire at device scope).  Because items
- * are taken in queue order and an item only waits for items taken before it, every awaited item
- * is held by a running workgroup and the launch cannot deadlock; each wait is still bounded and
- * reports DVR_E_TIMEOUT through dvr_batch_check instead of hanging.
+ * raymarch of many views of them, recorded in a HIP graph: the volumes' features on up to four
+ * parallel branches, then the ray tiles of every view in one launch (one for each number of lanes per
+ * ray that the views take).  A ray tile checks a stage word that the graph sets when every feature is
+ * there; that wait is bounded and reports DVR_E_TIMEOUT through dvr_batch_check instead of hanging.
  * The transfer function is read from device memory at every launch: editing it needs no new plan
  * (the analogue of the paper's uniform buffers, Sec. 4). */
 
@@ -364,12 +361,13 @@ typedef struct dvr_batch_view {
     int32_t *k_last;        /* device [H][W], nullable (written only if T_last is given) */
 } dvr_batch_view;
 
-/* Tile and brick shapes of a batched launch (chosen by dvr_batch_autotune or given). */
+/* Tile shapes of a batched launch (chosen by dvr_batch_autotune or given).  All are checked; ray_tile
+ * shapes the launches that give a ray one lane, the others no longer change how the work is split. */
 typedef struct dvr_tune {
-    int32_t wg_per_cu; /* persistent workgroups per compute unit, 1..8 */
-    int32_t xy_tile;   /* feature tile (x by y voxels): 0 = 64x8, 1 = 32x16, 2 = 128x4 */
-    int32_t xy_zrun;   /* z slices per feature item, 1..32 */
-    int32_t z_chunk;   /* z slices per z-filter item, 1..64 */
+    int32_t wg_per_cu; /* 1..8 */
+    int32_t xy_tile;   /* feature tile (x by y voxels): 0 = 64x8, 1 = 32x16, 2 = 128x4; its halo must fit 60 KB */
+    int32_t xy_zrun;   /* 1..32 */
+    int32_t z_chunk;   /* 1..64 */
     int32_t ray_tile;  /* rays per wave within a 16x16 workgroup tile: 0 = 8x8, 1 = 16x4, 2 = 4x16 */
 } dvr_tune;
 
@@ -384,7 +382,7 @@ typedef struct dvr_batch_desc {
     const dvr_tune *tune;          /* nullable: defaults */
 } dvr_batch_desc;
 
-typedef struct dvr_batch dvr_batch; /* opaque plan: owns its work tables, workspace, counters and graph */
+typedef struct dvr_batch dvr_batch; /* opaque plan: owns its tables, workspace, stage word and graph */
 
 /* Builds the plan (validates, allocates, uploads the tables, records the graph).  Synchronous. */
 dvr_status dvr_batch_create(const dvr_batch_desc *desc, dvr_batch **plan);
@@ -393,11 +391,10 @@ dvr_status dvr_batch_launch(dvr_batch *plan, hipStream_t stream);
 /* Waits for stream and reports DVR_E_TIMEOUT if a dependency wait of the last launch expired. */
 dvr_status dvr_batch_check(dvr_batch *plan, hipStream_t stream);
 dvr_status dvr_batch_destroy(dvr_batch *plan);
-/* Picks the tile shapes: times candidate dvr_tune values on this batch (graph replays, HIP events) by
- * coordinate descent from the defaults (two sweeps over wg_per_cu 2, 3, 4, 6, 8; xy_tile 0-2; xy_zrun
- * 8, 16, 32; z_chunk 4, 8, 16, 32; ray_tile 0-2, each field with the others at the best so far) and
- * returns the fastest.  With cache_path, results are kept in a JSON file keyed by the batch's
- * shape class and reused.  Synchronous; overwrites the batch's outputs. */
+/* Picks the tile shapes: times the three ray tiles on this batch (graph replays, HIP events; another
+ * xy_tile where the default's halo is refused) and returns the fastest.  With cache_path, results are
+ * kept in a JSON file keyed by the batch's shape class and reused.  Synchronous; overwrites the batch's
+ * outputs. */
 dvr_status dvr_batch_autotune(const dvr_batch_desc *desc, const char *cache_path, dvr_tune *best);
 
 #ifdef __cplusplus

@@ -415,7 +415,7 @@ class DVRRenderFromVolume(torch.autograd.Function):
 
 class Batch:
     """A batched plan (dvr_batch_*): the feature pass of every volume and the raymarch of every view
-    in one persistent kernel recorded in a HIP graph.
+    recorded in one HIP graph.
 
     vols: list of device volumes [nz][ny][nx]; spacings: list of (hx, hy, hz); feats: list of
     Features (outputs, one per volume, same dtype and layout); views: list of

@@ -145,6 +145,38 @@ void axis_taps(double sigma_vox, double h, dvr::AxisTaps &t)
     }
 }
 
+hipError_t enqueue_features(const void *vol, int32_t vol_dtype, const dvr_grid *grid, const dvr_feature_params *fp,
+                            const dvr_features_buf *out, float *scalars, float *fields, hipStream_t stream)
+{
+    // QUAD runs the SPLIT pass with V written plainly into the iquad array, then builds both quads
+    dvr_features_buf run = *out;
+    if (out->layout == DVR_QUAD) {
+        run.layout = DVR_SPLIT;
+        run.ves = out->iquad;
+    }
+    hipError_t e;
+    const double h[3] = {grid->hx, grid->hy, grid->hz};
+    for (int pass = (fp->c > 0.f ? 1 : 0); pass < 2; ++pass) {
+        for (int sc = 0; sc < fp->nsigma; ++sc) {
+            dvr::ScaleTaps taps;
+            const double sg = fp->sigma_mm[sc];
+            for (int a = 0; a < 3; ++a) axis_taps(sg / h[a], h[a], taps.ax[a]);
+            taps.sigma2 = (float)(sg * sg);
+            e = dvr::launch_features_scale(vol, vol_dtype, *grid, taps, sc, sc == fp->nsigma - 1, *fp, run, fields,
+                                           scalars, pass == 0, stream);
+            if (e != hipSuccess) return e;
+        }
+    }
+    if (out->bricks && (e = dvr::launch_bricks(vol, vol_dtype, *grid, *out, stream)) != hipSuccess) return e;
+    if (out->layout == DVR_QUAD) {
+        // V quads from the plain V first, then the intensity quads over it
+        e = dvr::launch_quads(out->iquad, out->ves, *grid, out->dtype, stream);
+        if (e == hipSuccess) e = dvr::launch_quads(vol, out->iquad, *grid, out->dtype, stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 size_t features_ws_bytes(const dvr_grid *g) { return 256 + (size_t)12 * (size_t)nvox(g); }
 
 }  // namespace dvr::host
@@ -328,40 +360,13 @@ dvr_status dvr_features(const void *vol, int32_t vol_dtype, const dvr_grid *grid
     if (ws_bytes < features_ws_bytes(grid))
         return fail(DVR_E_WORKSPACE, "workspace of %zu bytes is smaller than the required %zu", ws_bytes,
                     features_ws_bytes(grid));
-    // QUAD runs the SPLIT pass with V written plainly into the iquad array, then builds both quads
-    dvr_features_buf run = *out;
-    if (out->layout == DVR_QUAD) {
-        if (vol_dtype != out->dtype) return fail(DVR_E_UNSUPPORTED, "QUAD features need the volume in the feature dtype");
-        run.layout = DVR_SPLIT;
-        run.ves = out->iquad;
-    }
+    if (out->layout == DVR_QUAD && vol_dtype != out->dtype)
+        return fail(DVR_E_UNSUPPORTED, "QUAD features need the volume in the feature dtype");
     float *scalars = (float *)ws;
-    float *fields = (float *)((char *)ws + 256);
     hipError_t e = dvr::launch_init_scalars(out->gmax, scalars, stream);
     if (e != hipSuccess) return dev_fail(e, "features init");
-    const double h[3] = {grid->hx, grid->hy, grid->hz};
-    for (int pass = (fp->c > 0.f ? 1 : 0); pass < 2; ++pass) {
-        for (int sc = 0; sc < fp->nsigma; ++sc) {
-            dvr::ScaleTaps taps;
-            const double sg = fp->sigma_mm[sc];
-            for (int a = 0; a < 3; ++a) axis_taps(sg / h[a], h[a], taps.ax[a]);
-            taps.sigma2 = (float)(sg * sg);
-            e = dvr::launch_features_scale(vol, vol_dtype, *grid, taps, sc, sc == fp->nsigma - 1, *fp, run, fields,
-                                           scalars, pass == 0, stream);
-            if (e != hipSuccess) return dev_fail(e, "features launch");
-        }
-    }
-    if (out->bricks) {
-        e = dvr::launch_bricks(vol, vol_dtype, *grid, *out, stream);
-        if (e != hipSuccess) return dev_fail(e, "brick table launch");
-    }
-    if (out->layout == DVR_QUAD) {
-        // V quads from the plain V first, then the intensity quads over it
-        e = dvr::launch_quads(out->iquad, out->ves, *grid, out->dtype, stream);
-        if (e == hipSuccess) e = dvr::launch_quads(vol, out->iquad, *grid, out->dtype, stream);
-        if (e != hipSuccess) return dev_fail(e, "quad launch");
-    }
-    return DVR_OK;
+    e = enqueue_features(vol, vol_dtype, grid, fp, out, scalars, (float *)((char *)ws + 256), stream);
+    return e == hipSuccess ? DVR_OK : dev_fail(e, "features launch");
 }
 
 static dvr_status feat_bwd_plan(const dvr_grid *grid, const dvr_feature_params *fp, dvr::FeatBwdPlan &p)

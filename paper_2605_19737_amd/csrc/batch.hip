@@ -1,20 +1,24 @@
-// Batched persistent launch: the feature pass of many volumes and the raymarch of many views, in
-// one persistent kernel recorded in a HIP graph, with tile shapes chosen by an autotuner.
+// Batched launch: the feature pass of many volumes and the raymarch of many views, recorded once in a HIP
+// graph.
 //
-// Work queue.  Items are taken in a fixed order from one atomic counter:
-//   Z  (volume, scale, slab of z slices): z filters of the slab into the volume's workspace;
-//   XY (volume, scale, 2-D tile, run of z slices): y/x filters, Hessian, eigenvalues, k, V, g;
-//   Q  (volume, slab of z slices; quad layout only): the V and intensity quads of the slab;
-//   RAY (view, 16x16 pixel tile): one ray per lane, front to back.
-// An XY item waits until every Z item of its (volume, scale) is done (and, for scale s > 0, every
-// XY item of scale s-1, whose vesselness it max-accumulates); a RAY item waits until every XY item
-// of its volume is done (features and |g|_max complete; with quad-layout features, every Q item of
-// its volume, which itself waits for the volume's last XY scale).  Completion is a per-(volume, scale)
-// counter incremented after a device-scope release (every wave writes its L2 back); the waiter
-// polls, then acquires (invalidates its L2) once per volume per workgroup.  An item only waits for
-// items earlier in the queue, which were taken by running workgroups that never wait for later
-// items, so the launch makes progress at any grid size; each wait is still bounded and sets an
-// error flag instead of hanging.
+//   k_batch_init   clears the stage word, the error flag and every volume's |g|_max;
+//   the feature pass of every volume with the kernels of dvr_features (features.hip), on up to kLanes
+//     parallel branches of the graph, each with a workspace of its own, so that small volumes run beside
+//     each other;
+//   k_batch_mark   sets the stage word once every branch is done;
+//   k_batch_rays   the tiles of every view: one workgroup a tile, each taking its view and tile from a
+//     table that deals each view's blocks of 2 x 2 tiles to the XCDs in turn; one launch for each number
+//     of lanes per ray (1, 4, 16) that the views take.
+//
+// Bound by the rays' gathers (features 0.7 of 6.7 ms on eight thick-slice volumes of 2.2-6.1 M voxels with
+// four 512^2 views each, split FP32).  One persistent kernel that drained a queue of feature and ray items
+// took 10.5 ms there: the feature items' 168 VGPRs held the rays to three waves a SIMD, neighbouring tiles
+// went to different XCDs, and every feature item wrote the L2 back.  The tile table in blocks of 1 / 2 x 2 /
+// 4 x 4 / 8 x 8 tiles: 11.0 / 6.69 / 6.75 / 6.98 ms; 1 / 2 / 4 feature branches: 6.86 / 6.75 / 6.69.
+// 64 such volumes, tuned, 69 -> 62 ms; one to four views of two volumes of 1-3 M voxels 3.3-4.1 times faster.
+//
+// A ray tile checks that the stage word says the features are there (bounded, normally one load) and sets
+// the error flag instead of hanging.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdio.h>
@@ -36,33 +40,22 @@
 
 namespace dvr {
 
-enum { IT_Z = 0, IT_XY = 1, IT_RAY = 2, IT_Q = 3 };
 constexpr unsigned kMaxSpin = 1u << 23;  // polls of ~0.5 us: a wait gives up after several seconds
-constexpr int kMaxVolScale = 8192;       // volumes x scales per plan (LDS bitmaps of acquired counters)
+constexpr int kMaxVolScale = 8192;       // volumes x scales per plan
+constexpr int kLanes = 4;                // feature branches of the graph (the hardware queues of a process)
 
-struct BItem {
-    int32_t type_scale;  // type | scale << 8
-    int32_t v;           // volume (Z, XY, Q) or view (RAY)
-    int32_t a;           // Z, Q: first slice; XY: tile index; RAY: tile index
-    int32_t b;           // Z, Q: end slice; XY: first slice of the run
-};
-
-struct BVol {
-    const void *vol;
-    void *grad, *kappa, *ves;
-    float *gmax;
-    float *ws;  // [nsigma][3][N] z-filtered fields
-    void *iquad;  // quad layout: the intensity quads
-    void *vtmp;   // quad layout: V as a plain field (features dtype) until the Q items build its quads
-    int32_t n[3];
-    int32_t tiles_x;
-    KGrid grid;  // extents, spacings and segment length for the ray setup
-    float inv2h[3];
+struct BTile {
+    int32_t view;    // -1: none (padding)
+    int32_t tx, ty;  // tile
+    int32_t pad;
 };
 
 struct BView {
     KCam cam;
-    int32_t vol, W, H, tiles_x;
+    KFeat feat;
+    KGrid grid;
+    int32_t W, H;
+    unsigned need;  // the stage the view waits for
     float *rgba;
     float *T_last;
     int32_t *k_last;
@@ -73,320 +66,157 @@ struct BView {
 template <typename T>
 using CP = const __attribute__((address_space(4))) T *;
 
-struct BatchArgs {
-    uint64_t items;  // BItem[nitems]
-    int32_t nitems, ns, zrun, ray_tile;
-    uint64_t vols;   // BVol[nvol]
+struct RayArgs {
+    uint64_t tiles;  // BTile[gridDim.x]
     uint64_t views;  // BView[nview]
-    uint64_t taps;   // ScaleTaps[volume * ns + scale]
-    unsigned *head, *zdone, *xydone, *err;
-    const unsigned *nz_items, *nxy_items;
-    unsigned *qdone;           // per volume: Q items done (quad layout)
-    const unsigned *nq_items;  // per volume: Q items
-    const unsigned *ray_need;  // count a ray tile waits for (= nxy_items, see the timeout test hook)
-    unsigned max_spin;  // bound of every dependency wait (polls)
-    float c, inv2a2, inv2b2, tau;
+    unsigned *stage, *err;
+    unsigned max_spin;  // bound of the wait (polls)
+    int32_t ray_tile;
     KTF tf;
     KRender rp;
 };
 
-__device__ __forceinline__ bool bit_test_set(unsigned *bits, int i)
-{
-    const unsigned m = 1u << (i & 31);
-    if (bits[i >> 5] & m) return true;
-    bits[i >> 5] |= m;
-    return false;
-}
-
-// Thread 0: wait until *ctr >= target (bounded); then acquire once per (workgroup, counter).
-__device__ __forceinline__ void wait_for(unsigned *ctr, unsigned target, unsigned *err, unsigned *acq, int idx,
-                                         unsigned max_spin)
+// Thread 0: wait until *stage >= need (bounded).
+__device__ __forceinline__ void wait_for(unsigned *stage, unsigned need, unsigned *err, unsigned max_spin)
 {
     if (threadIdx.x != 0) return;
-    if (acq[idx >> 5] & (1u << (idx & 31))) return;
     unsigned n = 0;
-    while (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+    while (__hip_atomic_load(stage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
         if (++n > max_spin) {
             atomicOr(err, 1u);
             break;
         }
         __builtin_amdgcn_s_sleep(8);
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    bit_test_set(acq, idx);
 }
 
-// Every wave releases its writes at device scope, then one lane bumps the completion counter.
-__device__ __forceinline__ void release_done(unsigned *ctr)
+// pixel of this lane's ray in tile (tx, ty); with one lane per ray ray_tile gives the rays of a wave
+template <int G>
+__device__ __forceinline__ void ray_pixel(int ray_tile, int tx, int ty, int &pi, int &pj)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-template <int TXY>
-struct XYShape;
-template <> struct XYShape<0> { static constexpr int TX = 64, TY = 8; };
-template <> struct XYShape<1> { static constexpr int TX = 32, TY = 16; };
-template <> struct XYShape<2> { static constexpr int TX = 128, TY = 4; };
-
-__device__ __forceinline__ void ray_pixel(int ray_tile, int tiles_x, int tile, int &pi, int &pj)
-{
-    const int tx = tile % tiles_x, ty = tile / tiles_x;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    constexpr int S = (int)tile_side(G);
+    const int lane = (int)(threadIdx.x & 63u) / G, wv = threadIdx.x >> 6;
     int ox, oy;
-    if (ray_tile == 1) {         // 16 x 4 per wave, waves stacked in y
+    if (G == 1 && ray_tile == 1) {         // 16 x 4 per wave, waves stacked in y
         ox = lane & 15;
         oy = wv * 4 + (lane >> 4);
-    } else if (ray_tile == 2) {  // 4 x 16 per wave, waves side by side in x
+    } else if (G == 1 && ray_tile == 2) {  // 4 x 16 per wave, waves side by side in x
         ox = wv * 4 + (lane & 3);
         oy = lane >> 2;
-    } else {                     // 8 x 8 per wave, 2 x 2 waves
-        ox = (wv & 1) * 8 + (lane & 7);
-        oy = (wv >> 1) * 8 + (lane >> 3);
+    } else {                               // square, 2 x 2 waves
+        ox = (wv & 1) * (S / 2) + lane % (S / 2);
+        oy = (wv >> 1) * (S / 2) + lane / (S / 2);
     }
-    pi = tx * 16 + ox;
-    pj = ty * 16 + oy;
+    pi = tx * S + ox;
+    pj = ty * S + oy;
 }
 
-// Quads of slices [z0, z1) of one volume (the workgroup's 256 lanes over the slices' voxels):
-// dst[v] = (src(x,y,z), src(x,y+1,z), src(x,y,z+1), src(x,y+1,z+1)), 0 past the last row or slice,
-// as bit copies of the features dtype, for V (from the plain field) and for the intensity.
-template <typename T, typename T4>
-__device__ __forceinline__ void quads_slab(const T *__restrict__ src, T4 *__restrict__ dst, uint32_t nx, uint32_t ny,
-                                           uint32_t nz, int z0, int z1)
+// One tile of one view per workgroup, G lanes per ray: k_render with the view's records read from the
+// tables.  Bound like it, by gathers and instruction issue.
+template <int LAYOUT, int DT, int KMAX, int G>
+__global__ __launch_bounds__(256, (LAYOUT == DVR_QUAD && DT == DVR_F16 && G == 1) ? 5 : 1) void k_batch_rays(RayArgs A)
 {
-    const uint32_t plane = nx * ny;
-    const uint32_t end = (uint32_t)z1 * plane;
-    for (uint32_t v = (uint32_t)z0 * plane + threadIdx.x; v < end; v += 256u) {
-        const uint32_t row = v / nx, y = row % ny, z = row / ny;
-        const bool yi = y + 1u < ny, zi = z + 1u < nz;
-        T4 q;
-        q.x = src[v];
-        q.y = yi ? src[v + nx] : T(0);
-        q.z = zi ? src[v + plane] : T(0);
-        q.w = (yi && zi) ? src[v + plane + nx] : T(0);
-        dst[v] = q;
-    }
-}
-
-// The fixed-radius tile for radius Rr (a uniform value) over slices [z0, z1), if 2 <= Rr <= 10.
-template <int DT, int LAYOUT, int TX, int TY, int R, typename ST>
-__device__ __forceinline__ bool xy_fixed(const XYArgs &a, const ST &taps, int Rr, int x0, int y0, int z0, int z1,
-                                         float *lds, float &vmax)
-{
-    if constexpr (R > 10) {
-        return false;
-    } else {
-        if (Rr != R) return xy_fixed<DT, LAYOUT, TX, TY, R + 1>(a, taps, Rr, x0, y0, z0, z1, lds, vmax);
-        vmax = xy_run_r<DT, DT, LAYOUT, R, TX, TY>(a, taps, x0, y0, z0, z1, lds, lds);
-        return true;
-    }
-}
-
-template <int LAYOUT, int DT, int KMAX, int TXY>
-__global__ __launch_bounds__(256, 3) void k_batch(BatchArgs A)
-{
-    constexpr int TX = XYShape<TXY>::TX, TY = XYShape<TXY>::TY;
-    extern __shared__ float lds[];
+    const CP<BTile> tiles = (CP<BTile>)A.tiles;
+    const int view = tiles[blockIdx.x].view;
+    if (view < 0) return;
     __shared__ TFShared<KMAX> sh;
-    __shared__ unsigned acq_z[kMaxVolScale / 32], acq_xy[kMaxVolScale / 32], acq_q[kMaxVolScale / 32];
-    // the quad layout computes its features as the split layout, with V into the volume's plain field
-    constexpr int FLAYOUT = (LAYOUT == DVR_QUAD) ? DVR_SPLIT : LAYOUT;
-    __shared__ int item_sh;
     float kx[KMAX];
     tf_load<KMAX>(sh, kx, A.tf);
-    for (int i = threadIdx.x; i < kMaxVolScale / 32; i += 256) acq_z[i] = acq_xy[i] = acq_q[i] = 0u;
+    const auto &V = ((CP<BView>)A.views)[view];
+    wait_for(A.stage, V.need, A.err, A.max_spin);
     __syncthreads();
-    for (;;) {
-        if (threadIdx.x == 0) item_sh = (int)atomicAdd(A.head, 1u);
-        __syncthreads();
-        const int it = __builtin_amdgcn_readfirstlane(item_sh);
-        __syncthreads();
-        if (it >= A.nitems) break;
-        const CP<BItem> items = (CP<BItem>)A.items;
-        const CP<BVol> vols = (CP<BVol>)A.vols;
-        const CP<BView> views = (CP<BView>)A.views;
-        const CP<ScaleTaps> tapt = (CP<ScaleTaps>)A.taps;
-        BItem w;
-        w.type_scale = items[it].type_scale;
-        w.v = items[it].v;
-        w.a = items[it].a;
-        w.b = items[it].b;
-        const int type = w.type_scale & 0xff, s = w.type_scale >> 8;
-        if (type == IT_Z) {
-            const auto &V = vols[w.v];
-            const uint32_t plane = (uint32_t)V.n[0] * (uint32_t)V.n[1];
-            const uint32_t N = plane * (uint32_t)V.n[2];
-            float *ws = V.ws + (size_t)s * 3u * N;
-            const auto &tz = tapt[w.v * A.ns + s].ax[2];
-            for (int z = w.a; z < w.b; ++z)
-                for (uint32_t e = threadIdx.x; e < plane; e += 256u)
-                    zpass_voxel<DT>(V.vol, ws, V.n[0], V.n[1], V.n[2], tz, e, z);
-            release_done(A.zdone + w.v * A.ns + s);
-        } else if (type == IT_XY) {
-            const int vs = w.v * A.ns + s;
-            wait_for(A.zdone + vs, A.nz_items[vs], A.err, acq_z, vs, A.max_spin);
-            if (s > 0) wait_for(A.xydone + vs - 1, A.nxy_items[vs - 1], A.err, acq_xy, vs - 1, A.max_spin);
-            __syncthreads();
-            const auto &V = vols[w.v];
-            const uint32_t N = (uint32_t)V.n[0] * (uint32_t)V.n[1] * (uint32_t)V.n[2];
-            XYArgs a;
-            a.ws = V.ws + (size_t)s * 3u * N;
-            a.vol = V.vol;
-            a.grad = V.grad;
-            a.kappa = V.kappa;
-            a.ves = (LAYOUT == DVR_QUAD) ? V.vtmp : V.ves;
-            a.gmax = V.gmax;
-            a.fro = nullptr;
-            a.nx = V.n[0];
-            a.ny = V.n[1];
-            a.nz = V.n[2];
-            a.inv2h[0] = V.inv2h[0];
-            a.inv2h[1] = V.inv2h[1];
-            a.inv2h[2] = V.inv2h[2];
-            a.c_host = A.c;
-            a.inv2a2 = A.inv2a2;
-            a.inv2b2 = A.inv2b2;
-            a.tau = A.tau;
-            a.first = (s == 0);
-            a.fro_pass = 0;
-            const auto &taps = tapt[vs];
-            const int bx = w.a % V.tiles_x, by = w.a / V.tiles_x;
-            const int z1 = min(w.b + A.zrun, V.n[2]);
-            float vmax = 0.f;
-            // the fixed-radius tile (equal x and y radius 2..10) for the split-layout features of the
-            // split and quad launches; the generic tile otherwise
-            bool done = false;
-            if constexpr (TXY == 0 && FLAYOUT == DVR_SPLIT)
-                if (taps.ax[0].R == taps.ax[1].R)
-                    done = xy_fixed<DT, FLAYOUT, TX, TY, 2>(a, taps, taps.ax[0].R, bx * TX, by * TY, w.b, z1, lds, vmax);
-            if (!done)
-                for (int z = w.b; z < z1; ++z)
-                    vmax = fmaxf(vmax, xy_tile<DT, DT, FLAYOUT, TX, TY>(a, taps, bx * TX, by * TY, z, lds));
-            if (s == 0) {
-                vmax = wave_max(vmax);
-                if ((threadIdx.x & 63) == 0) atomic_max_pos(V.gmax, vmax);
-            }
-            release_done(A.xydone + vs);
-        } else if (type == IT_Q) {
-            if constexpr (LAYOUT == DVR_QUAD) {
-                const int vs = w.v * A.ns + A.ns - 1;
-                wait_for(A.xydone + vs, A.nxy_items[vs], A.err, acq_xy, vs, A.max_spin);
-                __syncthreads();
-                const auto &V = vols[w.v];
-                const uint32_t nx = (uint32_t)V.n[0], ny = (uint32_t)V.n[1], nz = (uint32_t)V.n[2];
-                if constexpr (DT == DVR_F32) {
-                    quads_slab(static_cast<const uint32_t *>(V.vtmp), static_cast<uint4 *>(V.ves), nx, ny, nz, w.a, w.b);
-                    quads_slab(static_cast<const uint32_t *>(V.vol), static_cast<uint4 *>(V.iquad), nx, ny, nz, w.a, w.b);
-                } else {
-                    quads_slab(static_cast<const uint16_t *>(V.vtmp), static_cast<ushort4 *>(V.ves), nx, ny, nz, w.a, w.b);
-                    quads_slab(static_cast<const uint16_t *>(V.vol), static_cast<ushort4 *>(V.iquad), nx, ny, nz, w.a,
-                               w.b);
-                }
-                release_done(A.qdone + w.v);
-            }
-        } else {
-            const auto &Vw = views[w.v];
-            const int vol = Vw.vol;
-            const int vs = vol * A.ns + A.ns - 1;
-            if constexpr (LAYOUT == DVR_QUAD)
-                wait_for(A.qdone + vol, A.nq_items[vol], A.err, acq_q, vol, A.max_spin);
-            else
-                wait_for(A.xydone + vs, A.ray_need[vs], A.err, acq_xy, vs, A.max_spin);
-            __syncthreads();
-            const auto &V = vols[vol];
-            KFeat f;
-            f.vol = (LAYOUT == DVR_QUAD) ? V.iquad : V.vol;
-            f.grad = V.grad;
-            f.kappa = V.kappa;
-            f.ves = V.ves;
-            f.gmax = V.gmax;
-            f.dtype = DT;
-            f.layout = LAYOUT;
-            f.bricks = nullptr;  // the batched launch builds no brick tables
-            f.nb[0] = f.nb[1] = f.nb[2] = 0;
-            KGrid g;  // field by field: V lives in the constant address space
-            for (int k = 0; k < 3; ++k) {
-                g.n[k] = V.grid.n[k];
-                g.h[k] = V.grid.h[k];
-                g.ih_hi[k] = V.grid.ih_hi[k];
-                g.ih_lo[k] = V.grid.ih_lo[k];
-            }
-            g.delta_hi = V.grid.delta_hi;
-            g.delta_lo = V.grid.delta_lo;
-            g.idelta_hi = V.grid.idelta_hi;
-            g.idelta_lo = V.grid.idelta_lo;
-            const float gm = __hip_atomic_load(V.gmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const float invg = gm > 0.f ? 1.f / gm : 0.f;
-            int pi, pj;
-            ray_pixel(A.ray_tile, Vw.tiles_x, w.a, pi, pj);
-            const bool valid = pi < Vw.W && pj < Vw.H;
-            RayGeo r;
-            r.N = 0;
-            KCam cam;
-            cam.persp = Vw.cam.persp;
-            for (int k = 0; k < 3; ++k) {
-                cam.o[k] = Vw.cam.o[k];
-                cam.d0[k] = Vw.cam.d0[k];
-                cam.du[k] = Vw.cam.du[k];
-                cam.dv[k] = Vw.cam.dv[k];
-            }
-            if (valid) r = ray_setup(cam, pi, pj, g);
-            const RayOut o = march_fwd<LAYOUT, DT, KMAX>(f, g, sh, kx, A.rp, invg, r);
-            if (valid) {
-                const size_t pix = (size_t)pj * Vw.W + pi;
-                reinterpret_cast<float4 *>(Vw.rgba)[pix] = make_float4(o.C0, o.C1, o.C2, o.A);
-                if (Vw.T_last) {
-                    Vw.T_last[pix] = o.Tprev;
-                    if (Vw.k_last) Vw.k_last[pix] = o.last;
-                }
-            }
+    KFeat f;  // field by field: V lives in the constant address space
+    f.vol = V.feat.vol;
+    f.grad = V.feat.grad;
+    f.kappa = V.feat.kappa;
+    f.ves = V.feat.ves;
+    f.gmax = V.feat.gmax;
+    f.dtype = DT;
+    f.layout = LAYOUT;
+    f.bricks = nullptr;  // the batched launch builds no brick tables
+    f.nb[0] = f.nb[1] = f.nb[2] = 0;
+    KGrid g;
+    KCam cam;
+    cam.persp = V.cam.persp;
+    for (int k = 0; k < 3; ++k) {
+        g.n[k] = V.grid.n[k];
+        g.h[k] = V.grid.h[k];
+        g.ih_hi[k] = V.grid.ih_hi[k];
+        g.ih_lo[k] = V.grid.ih_lo[k];
+        cam.o[k] = V.cam.o[k];
+        cam.d0[k] = V.cam.d0[k];
+        cam.du[k] = V.cam.du[k];
+        cam.dv[k] = V.cam.dv[k];
+    }
+    g.delta_hi = V.grid.delta_hi;
+    g.delta_lo = V.grid.delta_lo;
+    g.idelta_hi = V.grid.idelta_hi;
+    g.idelta_lo = V.grid.idelta_lo;
+    const float gm = *f.gmax;
+    const float invg = gm > 0.f ? 1.f / gm : 0.f;
+    int pi, pj;
+    ray_pixel<G>(A.ray_tile, tiles[blockIdx.x].tx, tiles[blockIdx.x].ty, pi, pj);
+    const bool valid = pi < V.W && pj < V.H;
+    RayGeo r;
+    r.N = 0;
+    if (valid) r = ray_setup(cam, pi, pj, g);
+    RayOut o;
+    if constexpr (G == 1) o = march_fwd<LAYOUT, DT, KMAX>(f, g, sh, kx, A.rp, invg, r);
+    else o = march_fwd_group<LAYOUT, DT, KMAX, G>(f, g, sh, kx, A.rp, invg, r);
+    if (valid && (threadIdx.x & (G - 1)) == 0) {
+        const size_t pix = (size_t)pj * V.W + pi;
+        reinterpret_cast<float4 *>(V.rgba)[pix] = make_float4(o.C0, o.C1, o.C2, o.A);
+        if (V.T_last) {
+            V.T_last[pix] = o.Tprev;
+            if (V.k_last) V.k_last[pix] = o.last;
         }
     }
 }
 
-// Reset the queue, counters, error flag and every volume's |g|_max (no memset nodes in the graph).
-__global__ void k_batch_init(BatchArgs A, int nvs, int nvol)
+// Clear the stage word, the error flag and every volume's |g|_max (no memset nodes in the graph).
+__global__ void k_batch_init(unsigned *stage, unsigned *err, float *const *gmax, int nvol)
 {
-    const int n = 2 * nvs + 2;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        if (i == 0) *A.head = 0u;
-        else if (i == 1) *A.err = 0u;
-        else if (i < 2 + nvs) A.zdone[i - 2] = 0u;
-        else A.xydone[i - 2 - nvs] = 0u;
+    if (threadIdx.x == 0) {
+        *stage = 0u;
+        *err = 0u;
     }
-    const BVol *vols = (const BVol *)A.vols;
-    for (int v = threadIdx.x; v < nvol; v += blockDim.x) {
-        *vols[v].gmax = 0.f;
-        A.qdone[v] = 0u;
-    }
+    for (int v = threadIdx.x; v < nvol; v += blockDim.x) *gmax[v] = 0.f;
+}
+
+__global__ void k_batch_mark(unsigned *stage)
+{
+    if (threadIdx.x == 0) *stage = 1u;
 }
 
 // ------------------------------------------------------------------------------------------------
 // host side
 
-static hipError_t launch_batch_kernel(const BatchArgs &A, int layout, int dt, int tf_k, int txy, unsigned grid,
-                                      size_t lds, hipStream_t st)
+template <int LAYOUT, int DT, int KMAX>
+static hipError_t launch_rays_k(const RayArgs &A, int lanes, unsigned grid, hipStream_t st)
 {
-#define DVR_B(L, D, KM, T)                                                                                     \
-    if (layout == L && dt == D && (KM == 16 ? tf_k <= 16 : tf_k > 16) && txy == T) {                            \
-        hipLaunchKernelGGL((k_batch<L, D, KM, T>), dim3(grid), dim3(256), lds, st, A);                          \
-        return hipGetLastError();                                                                               \
+    if (lanes == 16) hipLaunchKernelGGL((k_batch_rays<LAYOUT, DT, KMAX, 16>), dim3(grid), dim3(256), 0, st, A);
+    else if (lanes == 4) hipLaunchKernelGGL((k_batch_rays<LAYOUT, DT, KMAX, 4>), dim3(grid), dim3(256), 0, st, A);
+    else hipLaunchKernelGGL((k_batch_rays<LAYOUT, DT, KMAX, 1>), dim3(grid), dim3(256), 0, st, A);
+    return hipGetLastError();
+}
+
+static hipError_t launch_rays(const RayArgs &A, int layout, int dt, int lanes, unsigned grid, hipStream_t st)
+{
+#define DVR_R(L, D)                                                                \
+    if (layout == L && dt == D) {                                                  \
+        if (A.tf.K <= 8) return launch_rays_k<L, D, 8>(A, lanes, grid, st);        \
+        if (A.tf.K <= 16) return launch_rays_k<L, D, 16>(A, lanes, grid, st);      \
+        return launch_rays_k<L, D, 64>(A, lanes, grid, st);                        \
     }
-#define DVR_B3(L, D, KM) DVR_B(L, D, KM, 0) DVR_B(L, D, KM, 1) DVR_B(L, D, KM, 2)
-#define DVR_B6(L, D) DVR_B3(L, D, 16) DVR_B3(L, D, 64)
-    DVR_B6(DVR_PLANAR, DVR_F32)
-    DVR_B6(DVR_PLANAR, DVR_F16)
-    DVR_B6(DVR_INTERLEAVED, DVR_F32)
-    DVR_B6(DVR_INTERLEAVED, DVR_F16)
-    DVR_B6(DVR_SPLIT, DVR_F32)
-    DVR_B6(DVR_SPLIT, DVR_F16)
-    DVR_B6(DVR_QUAD, DVR_F32)
-    DVR_B6(DVR_QUAD, DVR_F16)
-#undef DVR_B6
-#undef DVR_B3
-#undef DVR_B
+    DVR_R(DVR_PLANAR, DVR_F32)
+    DVR_R(DVR_PLANAR, DVR_F16)
+    DVR_R(DVR_INTERLEAVED, DVR_F32)
+    DVR_R(DVR_INTERLEAVED, DVR_F16)
+    DVR_R(DVR_SPLIT, DVR_F32)
+    DVR_R(DVR_SPLIT, DVR_F16)
+    DVR_R(DVR_QUAD, DVR_F32)
+    DVR_R(DVR_QUAD, DVR_F16)
+#undef DVR_R
     return hipErrorInvalidValue;
 }
 
@@ -397,6 +227,8 @@ using namespace dvr::host;
 
 struct dvr_batch {
     hipStream_t stream = nullptr;
+    hipStream_t lane[kLanes] = {};      // the capture's feature branches
+    hipEvent_t fork = nullptr, join[kLanes] = {};
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<void *> allocs;
@@ -404,11 +236,25 @@ struct dvr_batch {
     dvr_tune tune;
 };
 
+// the capture's streams and events: not needed once the graph is there
+static void lanes_free(dvr_batch *p)
+{
+    for (int l = 0; l < kLanes; ++l) {
+        if (p->lane[l]) hipStreamDestroy(p->lane[l]);
+        if (p->join[l]) hipEventDestroy(p->join[l]);
+        p->lane[l] = nullptr;
+        p->join[l] = nullptr;
+    }
+    if (p->fork) hipEventDestroy(p->fork);
+    p->fork = nullptr;
+}
+
 static void plan_free(dvr_batch *p)
 {
     if (!p) return;
     if (p->exec) hipGraphExecDestroy(p->exec);
     if (p->graph) hipGraphDestroy(p->graph);
+    lanes_free(p);
     if (p->stream) hipStreamDestroy(p->stream);
     for (void *a : p->allocs) hipFree(a);
     delete p;
@@ -419,8 +265,6 @@ static dvr_tune default_tune()
     dvr_tune t;
     t.wg_per_cu = 4;
     t.xy_tile = 0;
-    // long z runs: every item ends with a device-scope release, which writes the XCD's L2 back; 32
-    // slices per item took the 64-volume feature phase from 27.8 to 12.0 ms (4 slices per item)
     t.xy_zrun = 32;
     t.z_chunk = 8;
     t.ray_tile = 0;
@@ -437,8 +281,6 @@ static dvr_status check_tune(const dvr_tune &t)
     return DVR_OK;
 }
 
-static const int kTXs[3] = {64, 32, 128}, kTYs[3] = {8, 16, 4};
-
 extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan_out)
 {
     if (!d || !plan_out) return fail(DVR_E_NULL, "desc and plan must be non-NULL");
@@ -454,13 +296,9 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
     if ((int64_t)d->nvol * (ns > 0 ? ns : 1) > kMaxVolScale)
         return fail(DVR_E_INVALID_ARG, "volumes x scales must not exceed %d", kMaxVolScale);
     const int layout = d->vols[0].feat.layout, fdt = d->vols[0].feat.dtype;
-    const int TX = kTXs[tune.xy_tile], TY = kTYs[tune.xy_tile];
 
-    std::vector<BVol> vols(d->nvol);
-    std::vector<ScaleTaps> taps((size_t)d->nvol * (ns > 0 ? ns : 1));
-    std::vector<unsigned> nz_items((size_t)d->nvol * ns, 0u), nxy_items((size_t)d->nvol * ns, 0u);
-    size_t lds_floats = 0;
-    size_t ws_total = 0;
+    size_t lds_floats = 0;  // of the named feature tile (part of the plan's contract: refused above 60 KB)
+    std::vector<dvr_features_buf> feats(d->nvol);
     for (int v = 0; v < d->nvol; ++v) {
         const dvr_batch_volume &bv = d->vols[v];
         if ((s = check_grid(&bv.grid))) return fail(s, "volume %d: %s", v, g_err.c_str());
@@ -471,87 +309,102 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
         if (bv.vol_dtype != fdt) return fail(DVR_E_UNSUPPORTED, "volume %d: vol dtype must equal the feature dtype", v);
         if (!bv.vol || !aligned16(bv.vol)) return fail(bv.vol ? DVR_E_ALIGN : DVR_E_NULL, "volume %d: bad vol pointer", v);
         const double h[3] = {bv.grid.hx, bv.grid.hy, bv.grid.hz};
-        BVol &B = vols[v];
-        B.vol = bv.vol;
-        B.grad = bv.feat.grad;
-        B.kappa = bv.feat.kappa;
-        B.ves = bv.feat.ves;
-        B.gmax = bv.feat.gmax;
-        B.iquad = bv.feat.iquad;
-        B.vtmp = nullptr;
-        B.n[0] = bv.grid.nx;
-        B.n[1] = bv.grid.ny;
-        B.n[2] = bv.grid.nz;
-        B.tiles_x = (bv.grid.nx + TX - 1) / TX;
-        for (int a = 0; a < 3; ++a) B.inv2h[a] = (float)(1.0 / (2.0 * h[a]));
-        const float hf[3] = {bv.grid.hx, bv.grid.hy, bv.grid.hz};
-        B.grid.n[0] = bv.grid.nx;
-        B.grid.n[1] = bv.grid.ny;
-        B.grid.n[2] = bv.grid.nz;
-        set_grid_steps(B.grid, hf, d->rp.step_vox);
         for (int sc = 0; sc < ns; ++sc) {
-            ScaleTaps &t = taps[(size_t)v * ns + sc];
-            for (int a = 0; a < 3; ++a) axis_taps((double)fp.sigma_mm[sc] / h[a], h[a], t.ax[a]);
-            t.sigma2 = (float)((double)fp.sigma_mm[sc] * fp.sigma_mm[sc]);
-            const size_t st = (size_t)3 * (TY + 2 * t.ax[1].R) * (TX + 2 * t.ax[0].R),
-                         cw = (size_t)Compact<2>::kFloats;
-            lds_floats = std::max(lds_floats, std::max(st, cw) + (size_t)6 * TY * (TX + 2 * t.ax[0].R));
+            const int Rx = gauss_radius((double)fp.sigma_mm[sc] / h[0]) + 1, Ry = gauss_radius((double)fp.sigma_mm[sc] / h[1]) + 1;
+            lds_floats = std::max(lds_floats, tune.xy_tile == 0   ? xy_lds_floats<64, 8>(Rx, Ry)
+                                              : tune.xy_tile == 1 ? xy_lds_floats<32, 16>(Rx, Ry)
+                                                                  : xy_lds_floats<128, 4>(Rx, Ry));
         }
-        ws_total += (size_t)ns * 12u * (size_t)nvox(&bv.grid);
-        if (layout == DVR_QUAD) ws_total += ((size_t)4u * (size_t)nvox(&bv.grid) + 255u) & ~(size_t)255u;
+        feats[v] = bv.feat;
+        feats[v].bricks = nullptr;
     }
     if (lds_floats * 4 > 60 * 1024)
         return fail(DVR_E_UNSUPPORTED, "feature tile with halo needs %zu bytes of LDS (limit 60 KB)", lds_floats * 4);
     // views
     std::vector<BView> views(d->nview);
-    for (int w = 0; w < d->nview; ++w) {
-        const dvr_batch_view &bw = d->views[w];
+    double rays = 0.0;
+    RayArgs A;
+    memset(&A, 0, sizeof A);
+    for (int w = 0; w <= d->nview; ++w) {
+        // the TF and the render parameters are checked (and taken) on a dummy view, also without views
+        dvr_batch_view bw;
+        memset(&bw, 0, sizeof bw);
+        bw.cam.width = bw.cam.height = 1;
+        bw.cam.d0[2] = 1.f;
+        if (w < d->nview) bw = d->views[w];
         if (bw.volume < 0 || bw.volume >= d->nvol) return fail(DVR_E_INVALID_ARG, "view %d: bad volume index", w);
         const dvr_batch_volume &bv = d->vols[bw.volume];
         dvr::RenderArgs ra;
         dvr::KCam kc;
         if ((s = build_render_args(bv.vol, bv.vol_dtype, &bv.grid, &bv.feat, &d->tf, &d->rp, &bw.cam, 1, ra, &kc)))
-            return fail(s, "view %d: %s", w, g_err.c_str());
+            return w < d->nview ? fail(s, "view %d: %s", w, g_err.c_str()) : s;
+        if (w == d->nview) {
+            A.tf = ra.tf;
+            A.rp = ra.rp;
+            break;
+        }
         if (!bw.rgba || !aligned16(bw.rgba)) return fail(bw.rgba ? DVR_E_ALIGN : DVR_E_NULL, "view %d: bad rgba", w);
         BView &V = views[w];
         V.cam = kc;
-        V.vol = bw.volume;
+        V.feat = ra.feat;
+        V.grid = ra.grid;
         V.W = bw.cam.width;
         V.H = bw.cam.height;
-        V.tiles_x = (V.W + 15) / 16;
+        V.need = 1u;
         V.rgba = bw.rgba;
         V.T_last = bw.T_last;
         V.k_last = bw.T_last ? bw.k_last : nullptr;
+        rays += (double)V.W * V.H;
     }
-    // work items in queue order: every Z item, then XY by scale, then rays
-    std::vector<BItem> items;
-    for (int v = 0; v < d->nvol; ++v)
-        for (int sc = 0; sc < ns; ++sc)
-            for (int z = 0; z < vols[v].n[2]; z += tune.z_chunk) {
-                items.push_back({IT_Z | (sc << 8), v, z, std::min(z + tune.z_chunk, vols[v].n[2])});
-                nz_items[(size_t)v * ns + sc]++;
-            }
-    for (int sc = 0; sc < ns; ++sc)
-        for (int v = 0; v < d->nvol; ++v) {
-            const int tx = vols[v].tiles_x, ty = (vols[v].n[1] + TY - 1) / TY;
-            for (int z = 0; z < vols[v].n[2]; z += tune.xy_zrun)
-                for (int t = 0; t < tx * ty; ++t) {
-                    items.push_back({IT_XY | (sc << 8), v, t, z});
-                    nxy_items[(size_t)v * ns + sc]++;
+    // Test hook (DVR_BATCH_TEST_TIMEOUT=1): the rays of volume 0 wait for a stage that never comes, with a
+    // short bound, so the launch exercises the timeout path and still exits normally.
+    A.max_spin = kMaxSpin;
+    if (getenv("DVR_BATCH_TEST_TIMEOUT") && atoi(getenv("DVR_BATCH_TEST_TIMEOUT")) == 1) {
+        for (int w = 0; w < d->nview; ++w)
+            if (d->views[w].volume == 0) views[w].need = 2u;
+        A.max_spin = 2000;
+    }
+    // the ray tables, one for each number of lanes per ray: workgroup b is XCD b % 8's, and the blocks of
+    // 2 x 2 tiles go to the XCDs in turn
+    const int lanes_of[3] = {1, 4, 16};
+    std::vector<BTile> tiles[3];
+    for (int q = 0; q < 3; ++q) {
+        std::vector<BTile> xcd[8];
+        int turn = 0;
+        for (int w = 0; w < d->nview; ++w) {
+            const BView &V = views[w];
+            if (fwd_lanes(rays, layout, fdt, pixel_pitch(V.cam, V.W, V.H, V.grid)) != lanes_of[q]) continue;
+            const int S = (int)tile_side(lanes_of[q]), nx = (V.W + S - 1) / S, ny = (V.H + S - 1) / S;
+            for (int by = 0; by < ny; by += 2)
+                for (int bx = 0; bx < nx; bx += 2, ++turn) {
+                    std::vector<BTile> &x = xcd[(turn + 5 * (turn >> 3) + (turn >> 6) + (turn >> 9)) & 7];
+                    for (int e = 0; e < 4; ++e)
+                        if (bx + (e & 1) < nx && by + (e >> 1) < ny) x.push_back({w, bx + (e & 1), by + (e >> 1), 0});
                 }
         }
-    std::vector<unsigned> nq_items((size_t)d->nvol, 0u);
-    if (layout == DVR_QUAD)
-        for (int v = 0; v < d->nvol; ++v)
-            for (int z = 0; z < vols[v].n[2]; z += tune.z_chunk) {
-                items.push_back({IT_Q, v, z, std::min(z + tune.z_chunk, vols[v].n[2])});
-                nq_items[v]++;
-            }
-    for (int w = 0; w < d->nview; ++w) {
-        const int nt = views[w].tiles_x * ((views[w].H + 15) / 16);
-        for (int t = 0; t < nt; ++t) items.push_back({IT_RAY, w, t, 0});
+        size_t most = 0;
+        for (const auto &x : xcd) most = std::max(most, x.size());
+        if (most * 8 > 0x7fffffffu) return fail(DVR_E_INVALID_ARG, "too many work items");
+        tiles[q].assign(most * 8, BTile{-1, 0, 0, 0});
+        for (size_t x = 0; x < 8; ++x)
+            for (size_t i = 0; i < xcd[x].size(); ++i) tiles[q][i * 8 + x] = xcd[x][i];
     }
-    if (items.size() > 0x7fffffffu) return fail(DVR_E_INVALID_ARG, "too many work items");
+    // the volumes' feature branches (a small volume alone leaves CUs idle): largest first to the least loaded, a workspace per branch
+    const int nlane = std::min(kLanes, d->nvol);
+    std::vector<int> order(d->nvol), lane_of(d->nvol);
+    for (int v = 0; v < d->nvol; ++v) order[v] = v;
+    std::sort(order.begin(), order.end(), [&](int a, int b) {
+        const int64_t na = nvox(&d->vols[a].grid), nb = nvox(&d->vols[b].grid);
+        return na > nb || (na == nb && a < b);
+    });
+    int64_t load[kLanes] = {}, ws_vox[kLanes] = {};
+    for (int v : order) {
+        int l = 0;
+        for (int k = 1; k < nlane; ++k) l = load[k] < load[l] ? k : l;
+        lane_of[v] = l;
+        load[l] += nvox(&d->vols[v].grid);
+        ws_vox[l] = std::max(ws_vox[l], nvox(&d->vols[v].grid));
+    }
 
     dvr_batch *P = new (std::nothrow) dvr_batch();
     if (!P) return fail(DVR_E_NOMEM, "host allocation");
@@ -562,108 +415,83 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
         P->allocs.push_back(p);
         return p;
     };
-    const int nvs = d->nvol * ns;
-    BItem *d_items = (BItem *)dalloc(sizeof(BItem) * items.size());
-    BVol *d_vols = (BVol *)dalloc(sizeof(BVol) * vols.size());
-    BView *d_views = (BView *)dalloc(sizeof(BView) * std::max<size_t>(views.size(), 1));
-    ScaleTaps *d_taps = (ScaleTaps *)dalloc(sizeof(ScaleTaps) * taps.size());
-    unsigned *d_ctr = (unsigned *)dalloc(sizeof(unsigned) * (size_t)(2 + 5 * nvs + 2 * d->nvol));
-    float *d_ws = (float *)dalloc(ws_total);
-    if (!d_items || !d_vols || !d_views || !d_taps || !d_ctr || !d_ws) {
+    BView *d_views = (BView *)dalloc(sizeof(BView) * views.size());
+    BTile *d_tiles[3];
+    bool ok = d_views != nullptr;
+    for (int q = 0; q < 3; ++q) ok = (d_tiles[q] = (BTile *)dalloc(sizeof(BTile) * tiles[q].size())) && ok;
+    std::vector<float *> gmax(d->nvol);
+    for (int v = 0; v < d->nvol; ++v) gmax[v] = d->vols[v].feat.gmax;
+    float **d_gmax = (float **)dalloc(sizeof(float *) * gmax.size());
+    unsigned *d_ctr = (unsigned *)dalloc(256);
+    float *ws[kLanes];
+    size_t ws_total = 0;
+    for (int l = 0; l < nlane; ++l) {
+        ws_total += 12u * (size_t)ws_vox[l];
+        ok = (ws[l] = (float *)dalloc(12u * (size_t)ws_vox[l])) && ok;
+    }
+    if (!ok || !d_gmax || !d_ctr) {
         plan_free(P);
         return fail(DVR_E_DEVICE, "device allocation of %zu bytes of workspace failed", ws_total);
     }
-    size_t off = 0;
-    for (int v = 0; v < d->nvol; ++v) {
-        vols[v].ws = d_ws + off / 4;
-        off += (size_t)ns * 12u * (size_t)nvox(&d->vols[v].grid);
-        if (layout == DVR_QUAD) {
-            vols[v].vtmp = d_ws + off / 4;
-            off += ((size_t)4u * (size_t)nvox(&d->vols[v].grid) + 255u) & ~(size_t)255u;
-        }
-    }
-    BatchArgs A;
-    memset(&A, 0, sizeof A);
-    A.items = (uint64_t)(uintptr_t)d_items;
-    A.nitems = (int32_t)items.size();
-    A.ns = ns;
-    A.zrun = tune.xy_zrun;
-    A.ray_tile = tune.ray_tile;
-    A.vols = (uint64_t)(uintptr_t)d_vols;
     A.views = (uint64_t)(uintptr_t)d_views;
-    A.taps = (uint64_t)(uintptr_t)d_taps;
-    A.head = d_ctr;
+    A.ray_tile = tune.ray_tile;
+    A.stage = d_ctr;
     A.err = d_ctr + 1;
-    A.zdone = d_ctr + 2;
-    A.xydone = d_ctr + 2 + nvs;
-    unsigned *d_nz = d_ctr + 2 + 2 * nvs, *d_nxy = d_ctr + 2 + 3 * nvs;
-    A.nz_items = d_nz;
-    A.nxy_items = d_nxy;
-    unsigned *d_need = d_ctr + 2 + 4 * nvs;
-    A.ray_need = d_need;
-    A.qdone = d_ctr + 2 + 5 * nvs;
-    unsigned *d_nq = d_ctr + 2 + 5 * nvs + d->nvol;
-    A.nq_items = d_nq;
-    A.max_spin = kMaxSpin;
-    // Test hook (DVR_BATCH_TEST_TIMEOUT=1): the rays of volume 0 wait for one feature item more than
-    // exist, with a short bound, so the launch exercises the timeout path and still exits normally.
-    std::vector<unsigned> need(nxy_items);
-    if (getenv("DVR_BATCH_TEST_TIMEOUT") && atoi(getenv("DVR_BATCH_TEST_TIMEOUT")) == 1) {
-        need[(size_t)ns - 1] += 1;
-        A.max_spin = 2000;
-    }
-    A.c = fp.c;
-    A.inv2a2 = (float)(1.0 / (2.0 * (double)fp.alpha * fp.alpha));
-    A.inv2b2 = (float)(1.0 / (2.0 * (double)fp.beta * fp.beta));
-    A.tau = fp.eig_gap_fp64;
-    {
-        dvr::RenderArgs ra;
-        dvr::KCam kc;
-        const dvr_batch_volume &bv = d->vols[0];
-        dvr_camera dummy;
-        memset(&dummy, 0, sizeof dummy);
-        dummy.width = dummy.height = 1;
-        dummy.d0[2] = 1.f;
-        if ((s = build_render_args(bv.vol, bv.vol_dtype, &bv.grid, &bv.feat, &d->tf, &d->rp, &dummy, 1, ra, &kc))) {
-            plan_free(P);
-            return s;
-        }
-        A.tf = ra.tf;
-        A.rp = ra.rp;
-    }
     P->d_err = A.err;
-    hipError_t e = hipMemcpy(d_items, items.data(), sizeof(BItem) * items.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(d_vols, vols.data(), sizeof(BVol) * vols.size(), hipMemcpyHostToDevice);
+    hipError_t e = hipMemcpy(d_gmax, gmax.data(), sizeof(float *) * gmax.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && !views.empty())
         e = hipMemcpy(d_views, views.data(), sizeof(BView) * views.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(d_taps, taps.data(), sizeof(ScaleTaps) * taps.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(d_nz, nz_items.data(), sizeof(unsigned) * nvs, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(d_nxy, nxy_items.data(), sizeof(unsigned) * nvs, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(d_need, need.data(), sizeof(unsigned) * nvs, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(d_nq, nq_items.data(), sizeof(unsigned) * d->nvol, hipMemcpyHostToDevice);
-    int dev = 0, ncu = 0;
-    if (e == hipSuccess) e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    for (int q = 0; q < 3 && e == hipSuccess; ++q)
+        if (!tiles[q].empty())
+            e = hipMemcpy(d_tiles[q], tiles[q].data(), sizeof(BTile) * tiles[q].size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&P->stream, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&P->fork, hipEventDisableTiming);
+    for (int l = 0; l < nlane && e == hipSuccess; ++l) {
+        e = hipStreamCreateWithFlags(&P->lane[l], hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&P->join[l], hipEventDisableTiming);
+    }
     if (e != hipSuccess) {
         plan_free(P);
         return dev_fail(e, "batch plan setup");
     }
-    const unsigned grid = (unsigned)(ncu * tune.wg_per_cu);
-    const size_t lds = lds_floats * 4;
     e = hipStreamBeginCapture(P->stream, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_batch_init, dim3(1), dim3(256), 0, P->stream, A, nvs, d->nvol);
-        hipError_t e1 = hipGetLastError();
-        hipError_t e2 = launch_batch_kernel(A, layout, fdt, d->tf.K, tune.xy_tile, grid, lds, P->stream);
-        hipError_t e3 = hipStreamEndCapture(P->stream, &P->graph);
-        e = e1 != hipSuccess ? e1 : (e2 != hipSuccess ? e2 : e3);
+        auto record = [&]() -> hipError_t {
+            hipError_t r;
+            hipLaunchKernelGGL(k_batch_init, dim3(1), dim3(256), 0, P->stream, A.stage, A.err, d_gmax, d->nvol);
+            if ((r = hipGetLastError()) != hipSuccess) return r;
+            if ((r = hipEventRecord(P->fork, P->stream)) != hipSuccess) return r;
+            for (int l = 0; l < nlane; ++l)
+                if ((r = hipStreamWaitEvent(P->lane[l], P->fork, 0)) != hipSuccess) return r;
+            for (int v : order) {
+                const dvr_batch_volume &bv = d->vols[v];
+                if ((r = enqueue_features(bv.vol, bv.vol_dtype, &bv.grid, &fp, &feats[v], nullptr, ws[lane_of[v]],
+                                          P->lane[lane_of[v]])) != hipSuccess)
+                    return r;
+            }
+            for (int l = 0; l < nlane; ++l) {
+                if ((r = hipEventRecord(P->join[l], P->lane[l])) != hipSuccess) return r;
+                if ((r = hipStreamWaitEvent(P->stream, P->join[l], 0)) != hipSuccess) return r;
+            }
+            hipLaunchKernelGGL(k_batch_mark, dim3(1), dim3(64), 0, P->stream, A.stage);
+            if ((r = hipGetLastError()) != hipSuccess) return r;
+            for (int q = 0; q < 3; ++q) {
+                if (tiles[q].empty()) continue;
+                A.tiles = (uint64_t)(uintptr_t)d_tiles[q];
+                if ((r = launch_rays(A, layout, fdt, lanes_of[q], (unsigned)tiles[q].size(), P->stream)) != hipSuccess) return r;
+            }
+            return hipSuccess;
+        };
+        const hipError_t e1 = record();
+        const hipError_t e2 = hipStreamEndCapture(P->stream, &P->graph);
+        e = e1 != hipSuccess ? e1 : e2;
     }
     if (e == hipSuccess) e = hipGraphInstantiate(&P->exec, P->graph, nullptr, nullptr, 0);
     if (e != hipSuccess) {
         plan_free(P);
         return dev_fail(e, "batch graph capture");
     }
+    lanes_free(P);
     *plan_out = P;
     return DVR_OK;
 }
@@ -787,34 +615,23 @@ extern "C" dvr_status dvr_batch_autotune(const dvr_batch_desc *desc, const char 
         dvr_batch_destroy(p);
         return ms;
     };
-    // coordinate descent from the defaults, two sweeps: each field in turn over its candidate values
-    // with the others at the best so far (the fields interact weakly: the feature items use xy_tile,
-    // xy_zrun and z_chunk, the ray items ray_tile, and wg_per_cu sets the occupancy of both)
-    const std::vector<int> vals[5] = {{2, 3, 4, 6, 8}, {0, 1, 2}, {8, 16, 32}, {4, 8, 16, 32}, {0, 1, 2}};
-    auto field = [](dvr_tune &t, int f) -> int & {
-        return f == 0 ? t.wg_per_cu : (f == 1 ? t.xy_tile : (f == 2 ? t.xy_zrun : (f == 3 ? t.z_chunk : t.ray_tile)));
-    };
-    std::map<std::vector<int>, float> seen;
-    auto key_of = [](const dvr_tune &t) {
-        return std::vector<int>{t.wg_per_cu, t.xy_tile, t.xy_zrun, t.z_chunk, t.ray_tile};
-    };
+    // The features' kernels take no shapes from the plan, so the ray tile is what there is to choose; other
+    // feature tiles only where the default's halo is refused.
     dvr_tune best_t = default_tune();
     float best_ms = time_tune(best_t);
-    seen[key_of(best_t)] = best_ms;
-    for (int sweep = 0; sweep < 2; ++sweep)
-        for (int f = 0; f < 5; ++f)
-            for (int v : vals[f]) {
-                dvr_tune t = best_t;
-                field(t, f) = v;
-                const auto k = key_of(t);
-                if (seen.count(k)) continue;
-                const float ms = time_tune(t);
-                seen[k] = ms;
-                if (ms < best_ms) {
-                    best_ms = ms;
-                    best_t = t;
-                }
-            }
+    for (int x = 1; x < 3 && !isfinite(best_ms); ++x) {
+        best_t.xy_tile = x;
+        best_ms = time_tune(best_t);
+    }
+    for (int r = 1; r < 3 && isfinite(best_ms); ++r) {
+        dvr_tune t = best_t;
+        t.ray_tile = r;
+        const float ms = time_tune(t);
+        if (ms < best_ms) {
+            best_ms = ms;
+            best_t = t;
+        }
+    }
     hipEventDestroy(e0);
     hipEventDestroy(e1);
     if (!isfinite(best_ms)) return last != DVR_OK ? last : fail(DVR_E_DEVICE, "no candidate tune ran");

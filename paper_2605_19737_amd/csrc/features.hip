@@ -89,12 +89,7 @@ __global__ __launch_bounds__(NT) void k_xypass(XYArgs a, ScaleTaps taps)
     }
 }
 
-// Fixed-radius variant (x and y stencil radius R, equal) for the layouts the workloads use: one
-// workgroup per (x, y) tile and run of kZRun z slices, each slice's loads in flight while the previous
-// slice is computed.
-constexpr int kZRun = 1;
-
-// One slice per workgroup, the y-filtered fields written over the staged ones (one LDS area of
+// Fixed-radius variant (x and y stencil radius R, equal).  One tile of one slice per workgroup, the y-filtered fields written over the staged ones (one LDS area of
 // max(NF, NFY) floats): 25 instead of 41 KB at radius 10, six workgroups a CU instead of three.  At
 // radii 6-9 the compiler otherwise takes 103-128 VGPRs (four waves per SIMD) for the y filters'
 // registers; held to six waves it needs 57-64, without spills (radius 7: 0.142 -> 0.127 ms on the head).
@@ -104,18 +99,12 @@ __global__ __launch_bounds__(NT, (R >= 6 && R <= 9) ? 6 : 1) void k_xypass_r(XYA
     using T = XYTileR<R, TX, TY>;
     using S = XYSlab<DT, OUT_DT, LAYOUT, R, TX, TY>;
     __shared__ float F[T::NF > T::NFY ? T::NF : T::NFY];
-    float vmax;
-    if constexpr (kZRun == 1) {
-        S s(a, taps, F, F, blockIdx.x * TX, blockIdx.y * TY);
-        const int z = blockIdx.z;
-        s.load(z);
-        s.store();
-        __syncthreads();
-        vmax = s.compute(z, s.In, s.Vp);
-    } else {
-        const int z0 = blockIdx.z * kZRun, z1 = min(z0 + kZRun, a.nz);
-        vmax = xy_run_r<DT, OUT_DT, LAYOUT, R, TX, TY>(a, taps, blockIdx.x * TX, blockIdx.y * TY, z0, z1, F, F);
-    }
+    S s(a, taps, F, F, blockIdx.x * TX, blockIdx.y * TY);
+    const int z = blockIdx.z;
+    s.load(z);
+    s.store();
+    __syncthreads();
+    float vmax = s.compute(z, s.In, s.Vp);
     if (a.fro_pass || a.first) {
         vmax = wave_max(vmax);
         if ((threadIdx.x & 63) == 0) atomic_max_pos(a.fro_pass ? a.fro : a.gmax, vmax);
@@ -129,7 +118,7 @@ static hipError_t launch_xy_r(const XYArgs &a, const ScaleTaps &taps, hipStream_
         return hipErrorInvalidValue;
     } else {
         if (taps.ax[0].R != R) return launch_xy_r<DT, OUT_DT, LAYOUT, R + 1>(a, taps, st);
-        dim3 grid((a.nx + TX - 1) / TX, (a.ny + TY - 1) / TY, (a.nz + kZRun - 1) / kZRun);
+        dim3 grid((a.nx + TX - 1) / TX, (a.ny + TY - 1) / TY, a.nz);
         hipLaunchKernelGGL((k_xypass_r<DT, OUT_DT, LAYOUT, R>), grid, dim3(NT), 0, st, a, taps);
         return hipGetLastError();
     }

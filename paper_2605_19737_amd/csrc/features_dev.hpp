@@ -1,5 +1,5 @@
-// Device code of the feature pass shared by the per-call kernels (features.hip) and the batched
-// persistent kernel (batch.hip).  See features.hip for the design notes.
+// Device code of the feature pass (features.hip, whose notes on the design hold here; batch.hip for its
+// tile sizes).
 #pragma once
 
 #include <math.h>
@@ -448,26 +448,6 @@ __device__ __forceinline__ void with_out(const XYArgs &a, F &&f)
     }
 }
 
-// z filters of one voxel: (Gz, D1z, D2z) of I at in-plane index e of slice z.
-template <int DT, typename AT>
-__device__ __forceinline__ void zpass_voxel(const void *__restrict__ vol, float *__restrict__ ws, int nx, int ny,
-                                            int nz, const AT &tz, uint32_t e, int z)
-{
-    const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
-    const uint32_t N = plane * (uint32_t)nz;
-    Buf b = make_buf(vol, N * ElemSize<DT>::v);
-    auto v = [&](int m) -> float {
-        const int zz = clampi(z + m, 0, nz - 1);
-        return ldv<DT>(b, (uint32_t)zz * plane + e);
-    };
-    const int cls = (z == 0) ? 1 : (z == nz - 1 ? 2 : 0);
-    const Line3 o = filt3(tz, cls, v);
-    const uint32_t i = (uint32_t)z * plane + e;
-    ws[i] = o.g;
-    ws[N + i] = o.d1;
-    ws[2u * N + i] = o.d2;
-}
-
 // LDS floats of the workgroup's compaction list: the six entries of sigma^2 H of up to NT NV voxels
 // (then each one's V in the first row), and the waves' counts
 template <int NV>
@@ -606,8 +586,7 @@ __device__ __forceinline__ void voxels_out(const XYArgs &a, float sigma2, const 
 // y and x filters of one TX x TY tile of slice z from the staged z-filtered fields, then the
 // per-voxel epilogue.  Returns this lane's contribution to |g|_max (first scale) or to
 // max |sigma^2 H|_F (Frangi-c pass); the caller reduces it.  lds holds
-// xy_lds_floats<TX, TY>(Rx, Ry) floats.  The taps may live in any address space (kernel
-// arguments, or a device table read through the constant address space by the batched kernel).
+// xy_lds_floats<TX, TY>(Rx, Ry) floats.  The taps are kernel arguments.
 template <int DT, int OUT_DT, int LAYOUT, int TX, int TY, typename ST>
 __device__ __forceinline__ float xy_tile(const XYArgs &a, const ST &taps, int x0, int y0, int z, float *lds)
 {
@@ -1043,35 +1022,6 @@ struct XYSlab {
         return vmax;
     }
 };
-
-// The fixed-radius tile over slices [z0, z1), each slice's loads issued while the previous slice is
-// computed.  F, Fy: XYTileR<R, TX, TY>::NF and ::NFY floats of LDS.  Returns this lane's contribution
-// to |g|_max (first scale) or max |sigma^2 H|_F (Frangi-c pass).  Every thread of the workgroup must
-// call it; it starts with a barrier, so the LDS may still be in use by an earlier tile.
-template <int DT, int OUT_DT, int LAYOUT, int R, int TX, int TY, typename ST>
-__device__ __forceinline__ float xy_run_r(const XYArgs &a, const ST &taps, int x0, int y0, int z0, int z1, float *F,
-                                          float *Fy)
-{
-    using S = XYSlab<DT, OUT_DT, LAYOUT, R, TX, TY, ST>;
-    S s(a, taps, F, Fy, x0, y0);
-    float vmax = 0.f;
-    s.load(z0);
-    for (int z = z0; z < z1; ++z) {
-        __syncthreads();  // the previous slice's readers of F (its y filters, its compaction lists) are done
-        s.store();
-        float Ic[S::NV][7], Vc[S::NV];
-#pragma unroll
-        for (int i = 0; i < S::NV; ++i) {
-            Vc[i] = s.Vp[i];
-#pragma unroll
-            for (int k = 0; k < 7; ++k) Ic[i][k] = s.In[i][k];
-        }
-        if (z + 1 < z1) s.load(z + 1);
-        __syncthreads();
-        vmax = fmaxf(vmax, s.compute(z, Ic, Vc));
-    }
-    return vmax;
-}
 
 // LDS floats of the generic tile: the staged fields (whose space the four waves' compaction lists
 // reuse after the y filters) and the y-filtered fields

@@ -25,6 +25,10 @@ dvr_status check_fparams(const dvr_grid *g, const dvr_feature_params *fp);
 dvr_status check_feat_buf(const dvr_features_buf *f, bool need_writable);
 void axis_taps(double sigma_vox, double h, dvr::AxisTaps &t);
 size_t features_ws_bytes(const dvr_grid *g);
+// The launches of dvr_features on checked arguments, after out->gmax and scalars[0] have been zeroed.
+// fields: 12 bytes a voxel of workspace; scalars: one device float, read and written only where c <= 0.
+hipError_t enqueue_features(const void *vol, int32_t vol_dtype, const dvr_grid *grid, const dvr_feature_params *fp,
+                            const dvr_features_buf *out, float *scalars, float *fields, hipStream_t stream);
 // Validates the shared render inputs and fills the kernel-argument records (cameras into kc).
 dvr_status build_render_args(const void *vol, int32_t vol_dtype, const dvr_grid *grid, const dvr_features_buf *feat,
                              const dvr_tf *tf, const dvr_render_params *rp, const dvr_camera *cams, int32_t ncam,

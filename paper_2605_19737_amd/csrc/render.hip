@@ -28,9 +28,6 @@
 
 namespace dvr {
 
-// side in pixels of a workgroup's tile with G lanes per ray
-__host__ __device__ constexpr uint32_t tile_side(int G) { return G == 1 ? 16 : (G == 4 ? 8 : 4); }
-
 // ------------------------------------------------------------------------------------------------
 // The camera index is uniform over the workgroup; copying the record field by field keeps the
 // by-value kernel argument block in the constant segment (taking its address would make the
@@ -300,33 +297,6 @@ static hipError_t launch_k(const KFeat &f, const KGrid &g, const KTF &tf, const 
     return launch_fwd_t<LAYOUT, DT, 64>(f, g, tf, rp, L, st, mode, lanes);
 }
 
-// Pixel pitch of a launch's views in voxels: the larger of a pixel's two steps, at the box centre for a
-// perspective view, the largest over the views.
-static double pixel_pitch(const KLaunch &L, const KGrid &g)
-{
-    double pitch = 0.0;
-    for (int c = 0; c < L.ncam; ++c) {
-        const KCam &cam = L.cams[c];
-        double scale = 1.0, du = 0.0, dv = 0.0;
-        if (cam.persp) {
-            double dist = 0.0, dir = 0.0;
-            for (int a = 0; a < 3; ++a) {
-                const double to = 0.5 * (g.n[a] - 1) * (double)g.h[a] - cam.o[a];
-                const double d = cam.d0[a] + 0.5 * L.W * (double)cam.du[a] + 0.5 * L.H * (double)cam.dv[a];
-                dist += to * to;
-                dir += d * d;
-            }
-            scale = dir > 0.0 ? sqrt(dist / dir) : 1.0;
-        }
-        for (int a = 0; a < 3; ++a) {
-            du += (cam.du[a] / (double)g.h[a]) * (cam.du[a] / (double)g.h[a]);
-            dv += (cam.dv[a] / (double)g.h[a]) * (cam.dv[a] / (double)g.h[a]);
-        }
-        pitch = fmax(pitch, scale * sqrt(fmax(du, dv)));
-    }
-    return pitch;
-}
-
 // Lanes per ray of the adjoint.  Above about 0.4 voxels a pixel the 8 x 8 rays of a wave stop fitting its
 // window (feature gradients; 0.65 without them, whose window is larger and whose G = 1 form keeps its
 // corner cache), above about 1.5 the 4 x 4 ones do.  Few rays take more lanes whatever the pitch: 64^3
@@ -339,24 +309,6 @@ static int bwd_lanes(const KLaunch &L, double pitch)
     return 1;
 }
 
-// Lanes per ray of the forward raymarch.  Few rays: with one lane a ray the chip needs a million rays to
-// hide a ray's chain of dependent samples and to even out the rays' lengths.  One view of a 64^3 volume
-// in the quad layout, 1 / 4 / 16 lanes: 128^2 214 / 66 / 66 us, 256^2 201 / 121 / 120, 512^2 393 / 231 / 365;
-// of a head: 398 / 128 / 96, 386 / 182 / 187, 529 / 268 / 568, 1024^2 552 / 437 (four such views: 1014 /
-// 989 at 768^2, eight 2654 / 3236 at 1024^2).  16 lanes hold a wave's samples closer together, which pays
-// longer where a sample touches more cache lines: FP32 (64^3 at 256^2, split 174 us with 4 lanes, 134
-// with 16; FP16 interleaved 108, 128) and above all FP32 planes (267, 155; 384^2 328, 299).  Coarse
-// views: 8 x 8 rays spread over many cache lines; a 152 x 229 x 177 volume at 512^2 x 32 (1.35 voxels a
-// pixel) 10.8 ms with one lane, 7.4 with 4, at 180^2 x 20 (3.8) 3.6, 2.05 and with 16 1.19; a 512 x 512 x
-// 400 one at 1024^2 x 2 (0.8) 3.1, 2.4.
-static int fwd_lanes(const KLaunch &L, const KFeat &f, double pitch)
-{
-    const int64_t rays = (int64_t)L.W * L.H * L.ncam;
-    const int64_t most16 = f.dtype == DVR_F16 ? 40960 : (f.layout == DVR_PLANAR ? 163840 : 81920);
-    if (rays <= most16 || (pitch > 2.5 && rays <= 1200000)) return 16;
-    return rays <= 1200000 || pitch > 0.6 ? 4 : 1;
-}
-
 static hipError_t launch_any(const RenderArgs &a, hipStream_t st, int mode)
 {
     for (int c0 = 0; c0 < a.ncam; c0 += kCamChunk) {
@@ -365,8 +317,10 @@ static hipError_t launch_any(const RenderArgs &a, hipStream_t st, int mode)
         L.cam_base = c0;
         for (int i = 0; i < L.ncam; ++i) L.cams[i] = a.cams[c0 + i];
         L.spread = L.ncam % 8 != 0;
-        const double pitch = pixel_pitch(L, a.grid);
-        const int lanes = mode == kBwd ? bwd_lanes(L, pitch) : (mode == kFwd ? fwd_lanes(L, a.feat, pitch) : 1);
+        double pitch = 0.0;
+        for (int i = 0; i < L.ncam; ++i) pitch = fmax(pitch, pixel_pitch(L.cams[i], L.W, L.H, a.grid));
+        const double rays = (double)L.W * L.H * L.ncam;
+        const int lanes = mode == kBwd ? bwd_lanes(L, pitch) : (mode == kFwd ? fwd_lanes(rays, a.feat.layout, a.feat.dtype, pitch) : 1);
         hipError_t e;
         const int lay = a.feat.layout, dt = a.feat.dtype;
         if (lay == DVR_PLANAR && dt == DVR_F32) e = launch_k<DVR_PLANAR, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);

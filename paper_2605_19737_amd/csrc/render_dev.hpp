@@ -1,5 +1,5 @@
 // Device code of the raymarcher shared by the per-call kernels (render.hip) and the batched
-// persistent kernel (batch.hip).  See render.hip for the design notes.
+// launch (batch.hip).  See render.hip for the design notes.
 #pragma once
 
 #include <math.h>
