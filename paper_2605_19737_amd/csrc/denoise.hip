@@ -6,8 +6,11 @@
 //               the largest of the kept values to the ends, drop both and take in the next neighbour;
 //               the median of the last three is the answer).  All indices are compile-time, so the
 //               values stay in registers.  The result is one of the inputs (exact).
-//   k_smooth    one axis of the separable sampled, normalized Gaussian (radius floor(3 sigma/h + 1/2),
-//               clamp-to-edge), FP32 accumulation; three launches (x, y, z) through FP32 workspaces.
+//   k_gauss     the separable sampled, normalized Gaussian (radius floor(3 sigma/h + 1/2), clamp-to-edge),
+//               FP32 accumulation, in one pass: radii up to 8 on volumes of enough tiles.
+//   k_smooth    one axis of it; three launches (x, y, z) through FP32 workspaces.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace dvr {
@@ -261,6 +264,134 @@ struct GaussTaps {
     float w[DVR_MAX_RADIUS + 1];
 };
 
+// The three axes in one pass, radii up to P in the plane and RZ in z.  A workgroup walks a 64 x 16 tile
+// along z: each slice (with halo, clamped to the edge, the next one's loads in flight) is staged, filtered
+// along x into a second LDS array and along y into registers, where the last 2 RZ + 1 slices' values wait
+// for the z filter.  The sums are k_smooth's, in its order, so the result is the same bits.  Bound by the
+// LDS reads of the two filters; the volume is read and written once where three passes through FP32
+// workspaces moved 20 bytes a voxel.  P (the halo's room) makes every LDS offset a constant.
+template <int DT, int P, int RZ>
+__global__ __launch_bounds__(256) void k_gauss(const void *__restrict__ in, void *__restrict__ out, int nx, int ny, int nz,
+                                               GaussTaps tx, GaussTaps ty, GaussTaps tz, int run)
+{
+    constexpr int TX = 64, TY = 16, W = TX + 2 * P, HH = TY + 2 * P, NR = (HH + 3) / 4;
+    __shared__ float F[HH * W], M[HH * TX];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int x0 = (int)blockIdx.x * TX, y0 = (int)blockIdx.y * TY;
+    const int z0 = (int)blockIdx.z * run, z1 = min(z0 + run, nz);
+    const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
+    const int rx = tx.r, ry = ty.r;
+    const int xm = min(x0 + lane, nx - 1);                              // this lane's column,
+    const int hc = lane < rx ? P - rx + lane : P + TX + (lane - rx);    // and its halo column of the staged rows
+    const int xh = min(max(x0 - P + hc, 0), nx - 1);
+    using E = std::conditional_t<DT == DVR_F32, float, __half>;  // widened when stored: a conversion here would wait
+    const E *src = reinterpret_cast<const E *>(in);
+    E a[NR], h[NR];
+    auto load = [&](int z) {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const int j = wv + 4 * i;
+            if (j < P - ry || j >= P + TY + ry) continue;
+            const uint32_t row = (uint32_t)z * plane + (uint32_t)min(max(y0 - P + j, 0), ny - 1) * (uint32_t)nx;
+            a[i] = src[row + xm];
+            if (lane < 2 * rx) h[i] = src[row + xh];
+        }
+    };
+    float ring[4][2 * RZ + 1];
+    load(max(z0 - RZ, 0));
+    for (int s = z0 - RZ; s < z1 + RZ; ++s) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int k = 0; k < 2 * RZ; ++k) ring[i][k] = ring[i][k + 1];
+        const int z = min(max(s, 0), nz - 1);
+        if (s == z0 - RZ || (s > 0 && s < nz)) {  // else the clamped slice once more
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                const int j = wv + 4 * i;
+                if (j < P - ry || j >= P + TY + ry) continue;
+                F[j * W + P + lane] = ld_any<DT>(&a[i], 0);
+                if (lane < 2 * rx) F[j * W + hc] = ld_any<DT>(&h[i], 0);
+            }
+            __syncthreads();  // F is staged, and M's readers of the slice before are done
+            if (z + 1 < min(z1 + RZ, nz)) load(z + 1);
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                const int j = wv + 4 * i;
+                if (j < P - ry || j >= P + TY + ry) continue;
+                const float *f = F + j * W + lane;
+                float acc = tx.w[0] * f[P];
+#pragma unroll
+                for (int m = 1; m <= P; ++m)
+                    if (m <= rx) acc = fmaf(tx.w[m], f[P + m] + f[P - m], acc);
+                M[j * TX + lane] = acc;
+            }
+            __syncthreads();  // M is there, and F's readers are done
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float *f = M + (wv * 4 + i) * TX + lane;
+                float acc = ty.w[0] * f[P * TX];
+#pragma unroll
+                for (int m = 1; m <= P; ++m)
+                    if (m <= ry) acc = fmaf(ty.w[m], f[(P + m) * TX] + f[(P - m) * TX], acc);
+                ring[i][2 * RZ] = acc;
+            }
+        }
+        if (s >= z0 + RZ) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float acc = tz.w[0] * ring[i][RZ];
+#pragma unroll
+                for (int m = 1; m <= RZ; ++m)
+                    if (m <= tz.r) acc = fmaf(tz.w[m], ring[i][RZ + m] + ring[i][RZ - m], acc);
+                const int y = y0 + wv * 4 + i;
+                if (x0 + lane < nx && y < ny)
+                    st_any<DT>(out, (uint32_t)(s - RZ) * plane + (uint32_t)y * (uint32_t)nx + x0 + lane, acc);
+            }
+        }
+    }
+}
+
+// Slices per run of the one-pass Gaussian, 0 for three passes.  A run filters 2 RZ slices more than it
+// writes and its slices follow each other (1.3-2 us each up to radius 4, 3.4-4.6 above), so long runs are for
+// volumes that fill the chip with them, and one that cannot be cut into enough runs is left to the three
+// passes.  us, radius 2 / 3 / 4 / 5 / 8 (FP16; FP32 is within 10 %): 512 x 512 x 400 (3328 workgroups at 32)
+// 186 / 248 / 342 / 601 / 1111, three passes 1165 / 1360 / 1543 / 1711 / 2191; 400 x 300 x 100 (931 at 16)
+// 46 / 59 / 71 / 119 / 277, 123 / 147 / 168 / 192 / 264; 220 x 200 x 180 (1196 at 8) 32 / 43 / 54, 74 / 89 /
+// 104; 256 x 256 x 40 (640 at 4) 20 / 29 / 36, 34 / 39 / 44; 97 x 113 x 61 (256 at 4) 18 / 26 / 34, 18 / 20 / 22.
+static int gauss_run(const dvr_grid &g, int r)
+{
+    if (r > 8) return 0;
+    auto groups = [&](int run) {
+        return (int64_t)((g.nx + 63) / 64) * ((g.ny + 15) / 16) * ((g.nz + run - 1) / run);
+    };
+    if (groups(32) >= 1536) return 32;
+    if (groups(16) >= 900 && r <= 6) return 16;
+    if (r > 4) return 0;
+    return groups(8) >= 700 ? 8 : (groups(4) >= 600 ? 4 : 0);
+}
+
+template <int DT, int P>
+static hipError_t launch_gauss(const void *vol, const dvr_grid &g, const GaussTaps (&t)[3], int run, void *out,
+                               hipStream_t st)
+{
+    const unsigned bx = (unsigned)((g.nx + 63) / 64), by = (unsigned)((g.ny + 15) / 16);
+    const dim3 grid(bx, by, (unsigned)((g.nz + run - 1) / run));
+#define DVR_G(RZ)                                                                                                     \
+    if (t[2].r <= RZ) {                                                                                               \
+        hipLaunchKernelGGL((k_gauss<DT, P, RZ>), grid, dim3(256), 0, st, vol, out, g.nx, g.ny, g.nz, t[0], t[1], t[2], run); \
+        return hipGetLastError();                                                                                     \
+    }
+    DVR_G(1)
+    DVR_G(2)
+    DVR_G(3)
+    DVR_G(4)
+    DVR_G(6)
+    DVR_G(8)
+#undef DVR_G
+    return hipErrorInvalidValue;
+}
+
 // out = G_axis * in along one axis (stride in elements, n the axis length)
 template <int DTI, int DTO>
 __global__ __launch_bounds__(256) void k_smooth(const void *__restrict__ in, void *__restrict__ out, int nx, int ny,
@@ -298,6 +429,14 @@ hipError_t launch_denoise(const void *vol, int dt, const dvr_grid &g, int mode, 
         t[a].r = r[a];
         for (int j = 0; j <= DVR_MAX_RADIUS; ++j) t[a].w[j] = w[a][j];
     }
+    if (const int run = gauss_run(g, max(t[0].r, max(t[1].r, t[2].r)))) {
+        if (t[0].r <= 4 && t[1].r <= 4)
+            return dt == DVR_F32 ? launch_gauss<DVR_F32, 4>(vol, g, t, run, out, st)
+                                 : launch_gauss<DVR_F16, 4>(vol, g, t, run, out, st);
+        return dt == DVR_F32 ? launch_gauss<DVR_F32, 8>(vol, g, t, run, out, st)
+                             : launch_gauss<DVR_F16, 8>(vol, g, t, run, out, st);
+    }
+    // one axis a launch
     const size_t N = (size_t)plane * g.nz;
     float *w0 = ws, *w1 = ws + N;
     if (dt == DVR_F32)
