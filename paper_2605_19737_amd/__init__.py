@@ -325,7 +325,7 @@ def histogram(vol, floor=0.0):
     h = torch.empty(256, dtype=torch.int32, device=vol.device)
     used = torch.empty(1, dtype=torch.int32, device=vol.device)
     abi.check(lib().dvr_histogram(_ptr(vol), _dt(vol), vol.numel(), float(floor), _ptr(h), _ptr(used), _stream()))
-    return h.long() & 0xFFFFFFFF, int(used.long().item() & 0xFFFFFFFF)
+    return h.view(torch.uint32).long(), int(used.item()) & 0xFFFFFFFF
 
 
 def tissue_peaks(hist, min_sep=2):
