@@ -35,6 +35,7 @@
 #include "common.hpp"
 #include "features_dev.hpp"
 #include "host.hpp"
+#include "lanes.hpp"
 #include "render_args.hpp"
 #include "render_dev.hpp"
 

@@ -23,6 +23,7 @@
 #include <math.h>
 
 #include "common.hpp"
+#include "lanes.hpp"
 #include "render_args.hpp"
 #include "render_dev.hpp"
 

@@ -2,7 +2,6 @@
 // so a launch records into a HIP graph with nothing else to copy).
 #pragma once
 
-#include <math.h>
 #include <stdint.h>
 
 #include "dvr.h"
@@ -89,49 +88,6 @@ inline void set_grid_steps(KGrid &g, const float h[3], float step_vox)
         g.h[a] = h[a];
         split2(1.0 / (double)h[a], g.ih_hi[a], g.ih_lo[a]);
     }
-}
-
-// Host: pixel pitch of a view in voxels, the larger of a pixel's two steps (at the box centre for a
-// perspective view).
-inline double pixel_pitch(const KCam &cam, int W, int H, const KGrid &g)
-{
-    double scale = 1.0, du = 0.0, dv = 0.0;
-    if (cam.persp) {
-        double dist = 0.0, dir = 0.0;
-        for (int a = 0; a < 3; ++a) {
-            const double to = 0.5 * (g.n[a] - 1) * (double)g.h[a] - cam.o[a];
-            const double d = cam.d0[a] + 0.5 * W * (double)cam.du[a] + 0.5 * H * (double)cam.dv[a];
-            dist += to * to;
-            dir += d * d;
-        }
-        scale = dir > 0.0 ? sqrt(dist / dir) : 1.0;
-    }
-    for (int a = 0; a < 3; ++a) {
-        du += (cam.du[a] / (double)g.h[a]) * (cam.du[a] / (double)g.h[a]);
-        dv += (cam.dv[a] / (double)g.h[a]) * (cam.dv[a] / (double)g.h[a]);
-    }
-    return scale * sqrt(du > dv ? du : dv);
-}
-
-// Side in pixels of a workgroup's tile with G lanes per ray.
-__host__ __device__ constexpr uint32_t tile_side(int G) { return G == 1 ? 16 : (G == 4 ? 8 : 4); }
-
-// Host: lanes per ray of the forward raymarch, by the rays of the launch and the pitch. Few rays: with
-// one lane a ray the chip needs a million rays to hide a ray's chain of dependent samples and to even
-// out the rays' lengths. One view of a 64^3 volume in the quad layout, 1 / 4 / 16 lanes: 128^2 214 / 66
-// / 66 us, 256^2 201 / 121 / 120, 512^2 393 / 231 / 365; of a head: 398 / 128 / 96, 386 / 182 / 187,
-// 529 / 268 / 568, 1024^2 552 / 437 (four such views: 1014 / 989 at 768^2, eight 2654 / 3236 at
-// 1024^2). 16 lanes hold a wave's samples closer together, which pays longer where a sample touches
-// more cache lines: FP32 (64^3 at 256^2, split 174 us with 4 lanes, 134 with 16; FP16 interleaved 108,
-// 128) and above all FP32 planes (267, 155; 384^2 328, 299). Coarse views: 8 x 8 rays spread over many
-// cache lines; a 152 x 229 x 177 volume at 512^2 x 32 (1.35 voxels a pixel) 10.8 ms with one lane, 7.4
-// with 4, at 180^2 x 20 (3.8) 3.6, 2.05 and with 16 1.19; a 512 x 512 x 400 one at 1024^2 x 2 (0.8)
-// 3.1, 2.4.
-inline int fwd_lanes(double rays, int layout, int dtype, double pitch)
-{
-    const double most16 = dtype == DVR_F16 ? 40960 : (layout == DVR_PLANAR ? 163840 : 81920);
-    if (rays <= most16 || (pitch > 2.5 && rays <= 1200000)) return 16;
-    return rays <= 1200000 || pitch > 0.6 ? 4 : 1;
 }
 
 }  // namespace dvr
