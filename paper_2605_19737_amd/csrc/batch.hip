@@ -228,8 +228,6 @@ using namespace dvr::host;
 
 struct dvr_batch {
     hipStream_t stream = nullptr;
-    hipStream_t lane[kLanes] = {};      // the capture's feature branches
-    hipEvent_t fork = nullptr, join[kLanes] = {};
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<void *> allocs;
@@ -237,17 +235,17 @@ struct dvr_batch {
     dvr_tune tune;
 };
 
-// the capture's streams and events: not needed once the graph is there
-static void lanes_free(dvr_batch *p)
+// appends the nodes that the next one recorded on the capturing stream would follow
+static hipError_t capture_tail(hipStream_t st, std::vector<hipGraphNode_t> &nodes)
 {
-    for (int l = 0; l < kLanes; ++l) {
-        if (p->lane[l]) hipStreamDestroy(p->lane[l]);
-        if (p->join[l]) hipEventDestroy(p->join[l]);
-        p->lane[l] = nullptr;
-        p->join[l] = nullptr;
-    }
-    if (p->fork) hipEventDestroy(p->fork);
-    p->fork = nullptr;
+    hipStreamCaptureStatus status;
+    const hipGraphNode_t *deps = nullptr;
+    size_t n = 0;
+    const hipError_t e = hipStreamGetCaptureInfo_v2(st, &status, nullptr, nullptr, &deps, &n);
+    if (e != hipSuccess) return e;
+    if (status != hipStreamCaptureStatusActive || n == 0) return hipErrorStreamCaptureInvalidated;
+    nodes.insert(nodes.end(), deps, deps + n);
+    return hipSuccess;
 }
 
 static void plan_free(dvr_batch *p)
@@ -255,7 +253,6 @@ static void plan_free(dvr_batch *p)
     if (!p) return;
     if (p->exec) hipGraphExecDestroy(p->exec);
     if (p->graph) hipGraphDestroy(p->graph);
-    lanes_free(p);
     if (p->stream) hipStreamDestroy(p->stream);
     for (void *a : p->allocs) hipFree(a);
     delete p;
@@ -446,11 +443,6 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
         if (!tiles[q].empty())
             e = hipMemcpy(d_tiles[q], tiles[q].data(), sizeof(BTile) * tiles[q].size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&P->stream, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&P->fork, hipEventDisableTiming);
-    for (int l = 0; l < nlane && e == hipSuccess; ++l) {
-        e = hipStreamCreateWithFlags(&P->lane[l], hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&P->join[l], hipEventDisableTiming);
-    }
     if (e != hipSuccess) {
         plan_free(P);
         return dev_fail(e, "batch plan setup");
@@ -461,19 +453,26 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
             hipError_t r;
             hipLaunchKernelGGL(k_batch_init, dim3(1), dim3(256), 0, P->stream, A.stage, A.err, d_gmax, d->nvol);
             if ((r = hipGetLastError()) != hipSuccess) return r;
-            if ((r = hipEventRecord(P->fork, P->stream)) != hipSuccess) return r;
-            for (int l = 0; l < nlane; ++l)
-                if ((r = hipStreamWaitEvent(P->lane[l], P->fork, 0)) != hipSuccess) return r;
-            for (int v : order) {
-                const dvr_batch_volume &bv = d->vols[v];
-                if ((r = enqueue_features(bv.vol, bv.vol_dtype, &bv.grid, &fp, &feats[v], nullptr, ws[lane_of[v]],
-                                          P->lane[lane_of[v]])) != hipSuccess)
-                    return r;
-            }
+            // the branches are recorded one after the other on the one capturing stream, each from the
+            // init node on; then the stream goes on from their last nodes
+            std::vector<hipGraphNode_t> head, tails;
+            if ((r = capture_tail(P->stream, head)) != hipSuccess) return r;
             for (int l = 0; l < nlane; ++l) {
-                if ((r = hipEventRecord(P->join[l], P->lane[l])) != hipSuccess) return r;
-                if ((r = hipStreamWaitEvent(P->stream, P->join[l], 0)) != hipSuccess) return r;
+                if ((r = hipStreamUpdateCaptureDependencies(P->stream, head.data(), head.size(),
+                                                            hipStreamSetCaptureDependencies)) != hipSuccess)
+                    return r;
+                for (int v : order) {
+                    if (lane_of[v] != l) continue;
+                    const dvr_batch_volume &bv = d->vols[v];
+                    if ((r = enqueue_features(bv.vol, bv.vol_dtype, &bv.grid, &fp, &feats[v], nullptr, ws[l],
+                                              P->stream)) != hipSuccess)
+                        return r;
+                }
+                if ((r = capture_tail(P->stream, tails)) != hipSuccess) return r;
             }
+            if ((r = hipStreamUpdateCaptureDependencies(P->stream, tails.data(), tails.size(),
+                                                        hipStreamSetCaptureDependencies)) != hipSuccess)
+                return r;
             hipLaunchKernelGGL(k_batch_mark, dim3(1), dim3(64), 0, P->stream, A.stage);
             if ((r = hipGetLastError()) != hipSuccess) return r;
             for (int q = 0; q < 3; ++q) {
@@ -492,7 +491,6 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
         plan_free(P);
         return dev_fail(e, "batch graph capture");
     }
-    lanes_free(P);
     *plan_out = P;
     return DVR_OK;
 }
