@@ -7,7 +7,7 @@
 //     each other;
 //   k_batch_mark   sets the stage word once every branch is done;
 //   k_batch_rays   the tiles of every view: one workgroup a tile, each taking its view and tile from a
-//     table that deals each view's blocks of 2 x 2 tiles to the XCDs in turn; one launch for each number
+//     table of blocks of 2 x 2 tiles, each view's dealt to the XCDs in turn; one launch for each number
 //     of lanes per ray (1, 4, 16) that the views take.
 //
 // Bound by the rays' gathers (features 0.7 of 6.7 ms on eight thick-slice volumes of 2.2-6.1 M voxels with
@@ -45,9 +45,9 @@ constexpr unsigned kMaxSpin = 1u << 23;  // polls of ~0.5 us: a wait gives up af
 constexpr int kMaxVolScale = 8192;       // volumes x scales per plan
 constexpr int kLanes = 4;                // feature branches of the graph (the hardware queues of a process)
 
-struct BTile {
+struct BBlock {      // 2 x 2 tiles
     int32_t view;    // -1: none (padding)
-    int32_t tx, ty;  // tile
+    int32_t tx, ty;  // its first tile
     int32_t pad;
 };
 
@@ -68,7 +68,7 @@ template <typename T>
 using CP = const __attribute__((address_space(4))) T *;
 
 struct RayArgs {
-    uint64_t tiles;  // BTile[gridDim.x]
+    uint64_t blocks;  // BBlock[gridDim.x / 4]
     uint64_t views;  // BView[nview]
     unsigned *stage, *err;
     unsigned max_spin;  // bound of the wait (polls)
@@ -117,8 +117,9 @@ __device__ __forceinline__ void ray_pixel(int ray_tile, int tx, int ty, int &pi,
 template <int LAYOUT, int DT, int KMAX, int G>
 __global__ __launch_bounds__(256, (LAYOUT == DVR_QUAD && DT == DVR_F16 && G == 1) ? 5 : 1) void k_batch_rays(RayArgs A)
 {
-    const CP<BTile> tiles = (CP<BTile>)A.tiles;
-    const int view = tiles[blockIdx.x].view;
+    // workgroup b runs on XCD b % 8; the four tiles of a block are neighbours there
+    const auto &B = ((CP<BBlock>)A.blocks)[(blockIdx.x >> 5) * 8u + (blockIdx.x & 7u)];
+    const int view = B.view;
     if (view < 0) return;
     __shared__ TFShared<KMAX> sh;
     float kx[KMAX];
@@ -156,7 +157,8 @@ __global__ __launch_bounds__(256, (LAYOUT == DVR_QUAD && DT == DVR_F16 && G == 1
     const float gm = *f.gmax;
     const float invg = gm > 0.f ? 1.f / gm : 0.f;
     int pi, pj;
-    ray_pixel<G>(A.ray_tile, tiles[blockIdx.x].tx, tiles[blockIdx.x].ty, pi, pj);
+    const int e = (int)(blockIdx.x >> 3) & 3;
+    ray_pixel<G>(A.ray_tile, B.tx + (e & 1), B.ty + (e >> 1), pi, pj);
     const bool valid = pi < V.W && pj < V.H;
     RayGeo r;
     r.N = 0;
@@ -365,27 +367,24 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
     // the ray tables, one for each number of lanes per ray: workgroup b is XCD b % 8's, and the blocks of
     // 2 x 2 tiles go to the XCDs in turn
     const int lanes_of[3] = {1, 4, 16};
-    std::vector<BTile> tiles[3];
+    std::vector<BBlock> blocks[3];
     for (int q = 0; q < 3; ++q) {
-        std::vector<BTile> xcd[8];
+        std::vector<BBlock> xcd[8];
         int turn = 0;
         for (int w = 0; w < d->nview; ++w) {
             const BView &V = views[w];
             if (fwd_lanes(rays, layout, fdt, pixel_pitch(V.cam, V.W, V.H, V.grid)) != lanes_of[q]) continue;
             const int S = (int)tile_side(lanes_of[q]), nx = (V.W + S - 1) / S, ny = (V.H + S - 1) / S;
             for (int by = 0; by < ny; by += 2)
-                for (int bx = 0; bx < nx; bx += 2, ++turn) {
-                    std::vector<BTile> &x = xcd[(turn + 5 * (turn >> 3) + (turn >> 6) + (turn >> 9)) & 7];
-                    for (int e = 0; e < 4; ++e)
-                        if (bx + (e & 1) < nx && by + (e >> 1) < ny) x.push_back({w, bx + (e & 1), by + (e >> 1), 0});
-                }
+                for (int bx = 0; bx < nx; bx += 2, ++turn)
+                    xcd[(turn + 5 * (turn >> 3) + (turn >> 6) + (turn >> 9)) & 7].push_back({w, bx, by, 0});
         }
         size_t most = 0;
         for (const auto &x : xcd) most = std::max(most, x.size());
-        if (most * 8 > 0x7fffffffu) return fail(DVR_E_INVALID_ARG, "too many work items");
-        tiles[q].assign(most * 8, BTile{-1, 0, 0, 0});
+        if (most * 32 > 0x7fffffffu) return fail(DVR_E_INVALID_ARG, "too many work items");
+        blocks[q].assign(most * 8, BBlock{-1, 0, 0, 0});
         for (size_t x = 0; x < 8; ++x)
-            for (size_t i = 0; i < xcd[x].size(); ++i) tiles[q][i * 8 + x] = xcd[x][i];
+            for (size_t i = 0; i < xcd[x].size(); ++i) blocks[q][i * 8 + x] = xcd[x][i];
     }
     // the volumes' feature branches (a small volume alone leaves CUs idle): largest first to the least loaded, a workspace per branch
     const int nlane = std::min(kLanes, d->nvol);
@@ -414,9 +413,9 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
         return p;
     };
     BView *d_views = (BView *)dalloc(sizeof(BView) * views.size());
-    BTile *d_tiles[3];
+    BBlock *d_blocks[3];
     bool ok = d_views != nullptr;
-    for (int q = 0; q < 3; ++q) ok = (d_tiles[q] = (BTile *)dalloc(sizeof(BTile) * tiles[q].size())) && ok;
+    for (int q = 0; q < 3; ++q) ok = (d_blocks[q] = (BBlock *)dalloc(sizeof(BBlock) * blocks[q].size())) && ok;
     std::vector<float *> gmax(d->nvol);
     for (int v = 0; v < d->nvol; ++v) gmax[v] = d->vols[v].feat.gmax;
     float **d_gmax = (float **)dalloc(sizeof(float *) * gmax.size());
@@ -440,8 +439,8 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
     if (e == hipSuccess && !views.empty())
         e = hipMemcpy(d_views, views.data(), sizeof(BView) * views.size(), hipMemcpyHostToDevice);
     for (int q = 0; q < 3 && e == hipSuccess; ++q)
-        if (!tiles[q].empty())
-            e = hipMemcpy(d_tiles[q], tiles[q].data(), sizeof(BTile) * tiles[q].size(), hipMemcpyHostToDevice);
+        if (!blocks[q].empty())
+            e = hipMemcpy(d_blocks[q], blocks[q].data(), sizeof(BBlock) * blocks[q].size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&P->stream, hipStreamNonBlocking);
     if (e != hipSuccess) {
         plan_free(P);
@@ -476,9 +475,9 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
             hipLaunchKernelGGL(k_batch_mark, dim3(1), dim3(64), 0, P->stream, A.stage);
             if ((r = hipGetLastError()) != hipSuccess) return r;
             for (int q = 0; q < 3; ++q) {
-                if (tiles[q].empty()) continue;
-                A.tiles = (uint64_t)(uintptr_t)d_tiles[q];
-                if ((r = launch_rays(A, layout, fdt, lanes_of[q], (unsigned)tiles[q].size(), P->stream)) != hipSuccess) return r;
+                if (blocks[q].empty()) continue;
+                A.blocks = (uint64_t)(uintptr_t)d_blocks[q];
+                if ((r = launch_rays(A, layout, fdt, lanes_of[q], (unsigned)(4 * blocks[q].size()), P->stream)) != hipSuccess) return r;
             }
             return hipSuccess;
         };
