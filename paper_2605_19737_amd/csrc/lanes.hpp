@@ -35,6 +35,33 @@ inline double pixel_pitch(const KCam &cam, int W, int H, const KGrid &g)
 // Side in pixels of a workgroup's tile with G lanes per ray.
 __host__ __device__ constexpr uint32_t tile_side(int G) { return G == 1 ? 16 : (G == 4 ? 8 : 4); }
 
+// Workgroups that a launch of 256 threads each may have: HIP refuses gridDim.x * blockDim.x >= 2^32.
+constexpr uint64_t kMaxGroups = (1u << 24) - 1;
+
+// Host: workgroups of ncam W x H views with G lanes per ray, rounded up to the 8 XCDs: one a tile, or
+// (spread) four a block of 2 x 2 tiles.
+inline uint64_t tile_groups(int W, int H, int ncam, int G, uint32_t spread)
+{
+    const uint64_t side = (uint64_t)tile_side(G) * (spread ? 2u : 1u);
+    const uint64_t n = (((uint64_t)W + side - 1u) / side) * (((uint64_t)H + side - 1u) / side) * (uint64_t)ncam;
+    return (n + 7u) / 8u * (spread ? 32u : 8u);
+}
+
+struct RaySplit {
+    int lanes;        // per ray
+    uint32_t spread;  // the XCDs take blocks of 2 x 2 tiles in turn (KLaunch::spread)
+};
+
+// Host: the split s with fewer lanes per ray, then with the XCDs' contiguous tiles, as far as the launch
+// needs it to fit in one grid (more than 2^30 pixels with 4 lanes; images of a few columns or rows, where
+// blocks of 2 x 2 tiles are mostly padding).  The adjoint's grid is that of one lane per ray.
+inline RaySplit fit_split(RaySplit s, int W, int H, int ncam, bool adjoint)
+{
+    while (!adjoint && s.lanes > 1 && tile_groups(W, H, ncam, s.lanes, s.spread) > kMaxGroups) s.lanes /= 4;
+    if (tile_groups(W, H, ncam, adjoint ? 1 : s.lanes, s.spread) > kMaxGroups) s.spread = 0;
+    return s;
+}
+
 // Host: lanes per ray of the forward raymarch, by the rays of the launch and the pitch. Few rays: with
 // one lane a ray the chip needs a million rays to hide a ray's chain of dependent samples and to even
 // out the rays' lengths. One view of a 64^3 volume in the quad layout, 1 / 4 / 16 lanes: 128^2 214 / 66

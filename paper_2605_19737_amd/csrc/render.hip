@@ -248,19 +248,11 @@ __global__ __launch_bounds__(256) void k_render_bwd(KFeat feat, KGrid g, KTF tf,
 // ------------------------------------------------------------------------------------------------
 enum { kFwd = 0, kBwd = 1, kGather = 2 };
 
-// Workgroups of a launch with G lanes per ray, rounded up to the 8 XCDs: one a tile, or four a block.
-static uint32_t tile_blocks(const KLaunch &L, int G)
-{
-    const uint32_t side = tile_side(G) * (L.spread ? 2u : 1u);
-    const uint32_t n = (((uint32_t)L.W + side - 1u) / side) * (((uint32_t)L.H + side - 1u) / side) * (uint32_t)L.ncam;
-    return (n + 7u) / 8u * (L.spread ? 32u : 8u);
-}
-
 template <int LAYOUT, int DT, int KMAX>
 static hipError_t launch_fwd_t(const KFeat &f, const KGrid &g, const KTF &tf, const KRender &rp, const KLaunch &L,
                                hipStream_t st, int mode, int lanes)
 {
-    const uint32_t blocks = tile_blocks(L, mode == kFwd ? lanes : 1);
+    const uint32_t blocks = (uint32_t)tile_groups(L.W, L.H, L.ncam, mode == kFwd ? lanes : 1, L.spread);
     // a tile's blocks are dealt to as many workgroups as evens the load out (about 4096); more would add
     // to the error of the TF gradient, which every workgroup adds to the same few FP32 words
     uint32_t split = 1;
@@ -317,11 +309,13 @@ static hipError_t launch_any(const RenderArgs &a, hipStream_t st, int mode)
         L.ncam = a.ncam - c0 < kCamChunk ? a.ncam - c0 : kCamChunk;
         L.cam_base = c0;
         for (int i = 0; i < L.ncam; ++i) L.cams[i] = a.cams[c0 + i];
-        L.spread = L.ncam % 8 != 0;
         double pitch = 0.0;
         for (int i = 0; i < L.ncam; ++i) pitch = fmax(pitch, pixel_pitch(L.cams[i], L.W, L.H, a.grid));
         const double rays = (double)L.W * L.H * L.ncam;
-        const int lanes = mode == kBwd ? bwd_lanes(L, pitch) : (mode == kFwd ? fwd_lanes(rays, a.feat.layout, a.feat.dtype, pitch) : 1);
+        const int want = mode == kBwd ? bwd_lanes(L, pitch) : (mode == kFwd ? fwd_lanes(rays, a.feat.layout, a.feat.dtype, pitch) : 1);
+        const RaySplit split = fit_split({want, L.ncam % 8 != 0 ? 1u : 0u}, L.W, L.H, L.ncam, mode == kBwd);
+        const int lanes = split.lanes;
+        L.spread = split.spread;
         hipError_t e;
         const int lay = a.feat.layout, dt = a.feat.dtype;
         if (lay == DVR_PLANAR && dt == DVR_F32) e = launch_k<DVR_PLANAR, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
