@@ -370,7 +370,7 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
     std::vector<BBlock> blocks[3];
     for (int q = 0; q < 3; ++q) {
         std::vector<BBlock> xcd[8];
-        int turn = 0;
+        int64_t turn = 0;
         for (int w = 0; w < d->nview; ++w) {
             const BView &V = views[w];
             if (fwd_lanes(rays, layout, fdt, pixel_pitch(V.cam, V.W, V.H, V.grid)) != lanes_of[q]) continue;
@@ -381,7 +381,7 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
         }
         size_t most = 0;
         for (const auto &x : xcd) most = std::max(most, x.size());
-        if (most * 32 > 0x7fffffffu) return fail(DVR_E_INVALID_ARG, "too many work items");
+        if (most * 8 > 0x7fffffffu) return fail(DVR_E_INVALID_ARG, "too many work items");
         blocks[q].assign(most * 8, BBlock{-1, 0, 0, 0});
         for (size_t x = 0; x < 8; ++x)
             for (size_t i = 0; i < xcd[x].size(); ++i) blocks[q][i * 8 + x] = xcd[x][i];
@@ -475,9 +475,14 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
             hipLaunchKernelGGL(k_batch_mark, dim3(1), dim3(64), 0, P->stream, A.stage);
             if ((r = hipGetLastError()) != hipSuccess) return r;
             for (int q = 0; q < 3; ++q) {
-                if (blocks[q].empty()) continue;
-                A.blocks = (uint64_t)(uintptr_t)d_blocks[q];
-                if ((r = launch_rays(A, layout, fdt, lanes_of[q], (unsigned)(4 * blocks[q].size()), P->stream)) != hipSuccess) return r;
+                // a table of more tiles than one grid holds takes several launches, each of whole rounds of
+                // the 8 XCDs
+                const size_t per = kMaxGroups / 32 * 8;
+                for (size_t b = 0; b < blocks[q].size(); b += per) {
+                    A.blocks = (uint64_t)(uintptr_t)(d_blocks[q] + b);
+                    const size_t n = std::min(per, blocks[q].size() - b);
+                    if ((r = launch_rays(A, layout, fdt, lanes_of[q], (unsigned)(4 * n), P->stream)) != hipSuccess) return r;
+                }
             }
             return hipSuccess;
         };

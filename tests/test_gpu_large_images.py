@@ -49,3 +49,18 @@ def test_render_of_2_30_pixels():
     print(f"[large] render {SIDE}^2", flush=True)
     img, T, k = dvr.render(None, f, kn, tf, w.params, [cam])
     _check(vol, f, w, cam, img[0], T[0], k[0], "2^30 pixels")
+
+
+def test_batch_view_of_2_30_pixels():
+    w, vol, kn, tf = _scene()
+    cam = _camera()
+    f = dvr.alloc_features(SHAPE, SP, layout=abi.DVR_QUAD, bricks=False)
+    img = torch.full((SIDE, SIDE, 4), -1.0, dtype=torch.float32, device="cuda")
+    T = torch.empty((SIDE, SIDE), dtype=torch.float32, device="cuda")
+    k = torch.empty((SIDE, SIDE), dtype=torch.int32, device="cuda")
+    print(f"[large] batched view {SIDE}^2", flush=True)
+    b = dvr.Batch([vol], [SP], [f], [(0, cam, img, T, k)], [1.0], kn, tf, w.params, c=w.c)
+    b.launch()
+    b.check()
+    _check(vol, f, w, cam, img, T, k, "2^30 pixels, batched")
+    b.close()
