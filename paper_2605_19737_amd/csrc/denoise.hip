@@ -192,13 +192,13 @@ __device__ __forceinline__ void med_slice(const void *__restrict__ in, const uin
 // selection instead (median27), whose answer then depends on its own order of comparisons.
 template <int DT>
 __global__ __launch_bounds__(256) void k_median3(const void *__restrict__ in, void *__restrict__ out, int nx, int ny,
-                                                 int nz, int run)
+                                                 int nz, int run, unsigned by0)
 {
     using V = typename Med<DT>::V;
     constexpr int kY = Med<DT>::kY;
     const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
     const int x = (int)(blockIdx.x * 64u + (threadIdx.x & 63u));
-    const int y0 = (int)(blockIdx.y * 4u + (threadIdx.x >> 6)) * kY;
+    const int y0 = (int)((by0 + blockIdx.y) * 4u + (threadIdx.x >> 6)) * kY;
     if (x >= nx || y0 >= ny) return;
     const int z0 = (int)blockIdx.z * run, z1 = min(z0 + run, nz);
     uint32_t row[kY + 2];
@@ -247,6 +247,8 @@ __global__ __launch_bounds__(256) void k_median3(const void *__restrict__ in, vo
     }
 }
 
+constexpr unsigned kMaxGridYZ = 65535;  // workgroups of a grid along y or z
+
 template <int DT>
 static void launch_median(const void *vol, const dvr_grid &g, void *out, hipStream_t st)
 {
@@ -255,8 +257,9 @@ static void launch_median(const void *vol, const dvr_grid &g, void *out, hipStre
     // a run sorts run + 2 slices for run voxels; short runs where long ones would not fill the chip
     int run = 16;
     while (run > 1 && (int64_t)bx * by * ((g.nz + run - 1) / run) < 2048) run >>= 1;
-    hipLaunchKernelGGL(k_median3<DT>, dim3(bx, by, (unsigned)((g.nz + run - 1) / run)), dim3(256), 0, st, vol, out, g.nx,
-                       g.ny, g.nz, run);
+    for (unsigned b = 0; b < by; b += kMaxGridYZ)
+        hipLaunchKernelGGL(k_median3<DT>, dim3(bx, min(by - b, kMaxGridYZ), (unsigned)((g.nz + run - 1) / run)), dim3(256),
+                           0, st, vol, out, g.nx, g.ny, g.nz, run, b);
 }
 
 struct GaussTaps {
@@ -361,7 +364,7 @@ __global__ __launch_bounds__(256) void k_gauss(const void *__restrict__ in, void
 // 104; 256 x 256 x 40 (640 at 4) 20 / 29 / 36, 34 / 39 / 44; 97 x 113 x 61 (256 at 4) 18 / 26 / 34, 18 / 20 / 22.
 static int gauss_run(const dvr_grid &g, int r)
 {
-    if (r > 8) return 0;
+    if (r > 8 || (unsigned)(g.ny + 15) / 16 > kMaxGridYZ) return 0;
     auto groups = [&](int run) {
         return (int64_t)((g.nx + 63) / 64) * ((g.ny + 15) / 16) * ((g.nz + run - 1) / run);
     };
