@@ -185,20 +185,22 @@ __device__ __forceinline__ void med_slice(const void *__restrict__ in, const uin
     }
 }
 
-// A wave takes 64 consecutive voxels of x; a lane walks a run of z, sorting each slice's 3 x 3
+// A wave takes 64 consecutive voxels of x, or on rows of at most 32 voxels 1 << lw columns of 64 >> lw groups
+// of rows (8 x 512 x 512: FP32 68 -> 13 us, FP16 78 -> 13; one lane a voxel with 27 loads took 29 and 28); a lane walks a run of z, sorting each slice's 3 x 3
 // neighbours once for the three voxels that share them.  Bound by VALU issue: per voxel 107 minimum and
 // maximum instructions in FP32 and 77 in FP16 (two voxels an instruction) against 388 for a selection
 // from 27 unsorted values: 512 x 512 x 400 FP16 1.30 -> 0.37 ms, FP32 1.30 -> 0.44.  The waves that meet a NaN take that
 // selection instead (median27), whose answer then depends on its own order of comparisons.
 template <int DT>
 __global__ __launch_bounds__(256) void k_median3(const void *__restrict__ in, void *__restrict__ out, int nx, int ny,
-                                                 int nz, int run, unsigned by0)
+                                                 int nz, int run, int lw, unsigned by0)
 {
     using V = typename Med<DT>::V;
     constexpr int kY = Med<DT>::kY;
     const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
-    const int x = (int)(blockIdx.x * 64u + (threadIdx.x & 63u));
-    const int y0 = (int)((by0 + blockIdx.y) * 4u + (threadIdx.x >> 6)) * kY;
+    const uint32_t lane = threadIdx.x & 63u;
+    const int x = (int)((blockIdx.x << lw) + (lane & ((1u << lw) - 1u)));
+    const int y0 = (int)((((by0 + blockIdx.y) * 4u + (threadIdx.x >> 6)) << (6 - lw)) + (lane >> lw)) * kY;
     if (x >= nx || y0 >= ny) return;
     const int z0 = (int)blockIdx.z * run, z1 = min(z0 + run, nz);
     uint32_t row[kY + 2];
@@ -252,14 +254,16 @@ constexpr unsigned kMaxGridYZ = 65535;  // workgroups of a grid along y or z
 template <int DT>
 static void launch_median(const void *vol, const dvr_grid &g, void *out, hipStream_t st)
 {
-    const int per = 4 * Med<DT>::kY;
-    const unsigned bx = (unsigned)((g.nx + 63) / 64), by = (unsigned)((g.ny + per - 1) / per);
+    int lw = 6;
+    while (lw > 1 && (1 << (lw - 1)) >= g.nx) --lw;
+    const int per = (256 >> lw) * Med<DT>::kY;
+    const unsigned bx = (unsigned)((g.nx + (1 << lw) - 1) >> lw), by = (unsigned)((g.ny + per - 1) / per);
     // a run sorts run + 2 slices for run voxels; short runs where long ones would not fill the chip
     int run = 16;
     while (run > 1 && (int64_t)bx * by * ((g.nz + run - 1) / run) < 2048) run >>= 1;
     for (unsigned b = 0; b < by; b += kMaxGridYZ)
         hipLaunchKernelGGL(k_median3<DT>, dim3(bx, min(by - b, kMaxGridYZ), (unsigned)((g.nz + run - 1) / run)), dim3(256),
-                           0, st, vol, out, g.nx, g.ny, g.nz, run, b);
+                           0, st, vol, out, g.nx, g.ny, g.nz, run, lw, b);
 }
 
 struct GaussTaps {
