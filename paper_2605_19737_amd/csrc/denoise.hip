@@ -366,12 +366,16 @@ __global__ __launch_bounds__(256) void k_gauss(const void *__restrict__ in, void
 // 186 / 248 / 342 / 601 / 1111, three passes 1165 / 1360 / 1543 / 1711 / 2191; 400 x 300 x 100 (931 at 16)
 // 46 / 59 / 71 / 119 / 277, 123 / 147 / 168 / 192 / 264; 220 x 200 x 180 (1196 at 8) 32 / 43 / 54, 74 / 89 /
 // 104; 256 x 256 x 40 (640 at 4) 20 / 29 / 36, 34 / 39 / 44; 97 x 113 x 61 (256 at 4) 18 / 26 / 34, 18 / 20 / 22.
+// Tiles filled to less than half (0.6 above radius 3) are left to the three passes too, radius 2 / 3 / 4 / 6:
+// 8 x 512 x 512 (an eighth) 43 / 56 / 69 / 126, three passes 20 / 22 / 24 / 31; 20 x 512 x 512 (0.31) 43 / 57 /
+// 70 / 126, 47 / 53 / 62 / 76; 512 x 8 x 512 (0.5) 19 / 27 / 35, 26 / 30 / 31; 66 x 300 x 300 (0.51) 32 / 43 /
+// 83, 58 / 67 / 76; 40 x 300 x 300 (0.62) 26 / 35 / 45, 40 / 47 / 53.
 static int gauss_run(const dvr_grid &g, int r)
 {
     if (r > 8 || (unsigned)(g.ny + 15) / 16 > kMaxGridYZ) return 0;
-    auto groups = [&](int run) {
-        return (int64_t)((g.nx + 63) / 64) * ((g.ny + 15) / 16) * ((g.nz + run - 1) / run);
-    };
+    const int64_t tiles = (int64_t)((g.nx + 63) / 64) * ((g.ny + 15) / 16);
+    if ((double)g.nx * g.ny < (r <= 3 ? 0.5 : 0.6) * 1024.0 * (double)tiles) return 0;
+    auto groups = [&](int run) { return tiles * ((g.nz + run - 1) / run); };
     if (groups(32) >= 1536) return 32;
     if (groups(16) >= 900 && r <= 6) return 16;
     if (r > 4) return 0;
