@@ -373,7 +373,7 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
         int64_t turn = 0;
         for (int w = 0; w < d->nview; ++w) {
             const BView &V = views[w];
-            if (fwd_lanes(rays, layout, fdt, pixel_pitch(V.cam, V.W, V.H, V.grid)) != lanes_of[q]) continue;
+            if (fwd_lanes(rays, layout, fdt, d->tf.K, view_geo(V.cam, V.W, V.H, V.grid)) != lanes_of[q]) continue;
             const int S = (int)tile_side(lanes_of[q]), nx = (V.W + S - 1) / S, ny = (V.H + S - 1) / S;
             for (int by = 0; by < ny; by += 2)
                 for (int bx = 0; bx < nx; bx += 2, ++turn)

@@ -10,26 +10,43 @@
 
 namespace dvr {
 
-// Host: pixel pitch of a view in voxels, the larger of a pixel's two steps (at the box centre for a
-// perspective view).
-inline double pixel_pitch(const KCam &cam, int W, int H, const KGrid &g)
+// Host: how a view samples the volume.
+struct ViewGeo {
+    double pitch;  // pixel pitch in voxels, the larger of a pixel's two steps
+    double chord;  // samples of a mean ray through the box
+    double hit;    // share of the pixels whose ray meets the box, at most
+};
+
+// (at the box centre for a perspective view; a box partly outside the image is counted whole)
+inline ViewGeo view_geo(const KCam &cam, int W, int H, const KGrid &g)
 {
-    double scale = 1.0, du = 0.0, dv = 0.0;
-    if (cam.persp) {
-        double dist = 0.0, dir = 0.0;
-        for (int a = 0; a < 3; ++a) {
-            const double to = 0.5 * (g.n[a] - 1) * (double)g.h[a] - cam.o[a];
-            const double d = cam.d0[a] + 0.5 * W * (double)cam.du[a] + 0.5 * H * (double)cam.dv[a];
-            dist += to * to;
-            dir += d * d;
-        }
-        scale = dir > 0.0 ? sqrt(dist / dir) : 1.0;
-    }
+    double scale = 1.0, du = 0.0, dv = 0.0, d[3], ext[3], dist = 0.0, dir = 0.0;
     for (int a = 0; a < 3; ++a) {
+        ext[a] = (g.n[a] - 1) * (double)g.h[a];
+        const double to = 0.5 * ext[a] - cam.o[a];
+        d[a] = cam.d0[a];
+        if (cam.persp) d[a] += 0.5 * W * (double)cam.du[a] + 0.5 * H * (double)cam.dv[a];
+        dist += to * to;
+        dir += d[a] * d[a];
         du += (cam.du[a] / (double)g.h[a]) * (cam.du[a] / (double)g.h[a]);
         dv += (cam.dv[a] / (double)g.h[a]) * (cam.dv[a] / (double)g.h[a]);
     }
-    return scale * sqrt(du > dv ? du : dv);
+    if (cam.persp && dir > 0.0) scale = sqrt(dist / dir);
+    ViewGeo v;
+    v.pitch = scale * sqrt(du > dv ? du : dv);
+    // the box's shadow along the view, and a pixel's area, in mm^2
+    const double area = (fabs(d[0]) * ext[1] * ext[2] + fabs(d[1]) * ext[0] * ext[2] + fabs(d[2]) * ext[0] * ext[1]) /
+                        (dir > 0.0 ? sqrt(dir) : 1.0);
+    double px = 0.0;
+    for (int a = 0; a < 3; ++a) {
+        const int b = (a + 1) % 3, c = (a + 2) % 3;
+        const double x = (double)cam.du[b] * cam.dv[c] - (double)cam.du[c] * cam.dv[b];
+        px += x * x;
+    }
+    px = scale * scale * sqrt(px);
+    v.chord = area > 0.0 ? ext[0] * ext[1] * ext[2] / (area * (double)g.delta_hi) : 0.0;
+    v.hit = px > 0.0 && area < px * W * H ? area / (px * W * H) : 1.0;
+    return v;
 }
 
 // Side in pixels of a workgroup's tile with G lanes per ray.
@@ -48,8 +65,9 @@ inline uint64_t tile_groups(int W, int H, int ncam, int G, uint32_t spread)
 }
 
 struct RaySplit {
-    int lanes;        // per ray
-    uint32_t spread;  // the XCDs take blocks of 2 x 2 tiles in turn (KLaunch::spread)
+    int lanes;           // per ray
+    uint32_t spread;     // the XCDs take blocks of 2 x 2 tiles in turn (KLaunch::spread)
+    uint32_t parts = 1;  // adjoint: workgroups that share a tile's blocks of rays
 };
 
 // Host: the split s with fewer lanes per ray, then with the XCDs' contiguous tiles, as far as the launch
@@ -73,11 +91,12 @@ inline RaySplit fit_split(RaySplit s, int W, int H, int ncam, bool adjoint)
 // cache lines; a 152 x 229 x 177 volume at 512^2 x 32 (1.35 voxels a pixel) 10.8 ms with one lane, 7.4
 // with 4, at 180^2 x 20 (3.8) 3.6, 2.05 and with 16 1.19; a 512 x 512 x 400 one at 1024^2 x 2 (0.8)
 // 3.1, 2.4.
-inline int fwd_lanes(double rays, int layout, int dtype, double pitch)
+inline int fwd_lanes(double rays, int layout, int dtype, int K, const ViewGeo &v)
 {
+    (void)K;
     const double most16 = dtype == DVR_F16 ? 40960 : (layout == DVR_PLANAR ? 163840 : 81920);
-    if (rays <= most16 || (pitch > 2.5 && rays <= 1200000)) return 16;
-    return rays <= 1200000 || pitch > 0.6 ? 4 : 1;
+    if (rays <= most16 || (v.pitch > 2.5 && rays <= 1200000)) return 16;
+    return rays <= 1200000 || v.pitch > 0.6 ? 4 : 1;
 }
 
 }  // namespace dvr

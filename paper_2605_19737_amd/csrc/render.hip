@@ -183,6 +183,13 @@ __global__ __launch_bounds__(256) void k_render_bwd(KFeat feat, KGrid g, KTF tf,
     pixel_of<true>(L, cam, pi, pj, valid);
     const int pix = valid ? (int)(((size_t)(L.cam_base + cam) * L.H + pj) * L.W + pi) : -1;
     const int kl = valid ? L.k_last[pix] : -1;
+    const int nb = G / (int)gridDim.y;  // blocks of this workgroup
+    if constexpr (G > 1) {
+        // a workgroup without a live ray ends here, before it clears its window (98 KB with feature
+        // gradients and 16 lanes): a 231 x 286 x 6 volume in the middle of four 512^2 views of 5 voxels a
+        // pixel 0.50 -> 0.21 ms (plain 0.24 -> 0.13; with one lane a ray 0.32 and 0.17)
+        if (!__syncthreads_or(kl >= 0 && (int)(threadIdx.x & 63u) / (64 / G) / nb == (int)blockIdx.y)) return;
+    }
     RayGeo r;
     r.N = 0;
     if (kl >= 0) r = ray_setup(load_cam(L, cam), pi, pj, g);
@@ -208,9 +215,10 @@ __global__ __launch_bounds__(256) void k_render_bwd(KFeat feat, KGrid g, KTF tf,
         // every lane of the wave takes part (the dL/dI window is managed wave-wide)
         march_bwd<LAYOUT, DT, KMAX, FG>(feat, g, sh, kx, rp, invg, r, kl, Tl, gr, K, tfl, L.dvol, wwin, L.dfeat, gmb);
     } else {
-        const int nb = G / (int)gridDim.y;  // blocks of this workgroup
         for (int blk = (int)blockIdx.y * nb; blk < ((int)blockIdx.y + 1) * nb; ++blk) {
             const int src = blk * (64 / G) + (int)(threadIdx.x & 63u) / G;
+            const int k1 = __shfl(kl, src, 64);
+            if (!__any(k1 >= 0)) continue;
             GroupRay q;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
@@ -221,7 +229,7 @@ __global__ __launch_bounds__(256) void k_render_bwd(KFeat feat, KGrid g, KTF tf,
             q.N = __shfl(r.N, src, 64);
             q.delta = g.delta_hi;
             q.dlast = __shfl(r.dlast, src, 64);
-            const int px = __shfl(pix, src, 64), k1 = __shfl(kl, src, 64);
+            const int px = __shfl(pix, src, 64);
             float4 gr = make_float4(0.f, 0.f, 0.f, 0.f);
             float Tl = 0.f;
             if (k1 >= 0) {
@@ -250,15 +258,12 @@ enum { kFwd = 0, kBwd = 1, kGather = 2 };
 
 template <int LAYOUT, int DT, int KMAX>
 static hipError_t launch_fwd_t(const KFeat &f, const KGrid &g, const KTF &tf, const KRender &rp, const KLaunch &L,
-                               hipStream_t st, int mode, int lanes)
+                               hipStream_t st, int mode, const RaySplit &split)
 {
+    const int lanes = split.lanes;
     const uint32_t blocks = (uint32_t)tile_groups(L.W, L.H, L.ncam, mode == kFwd ? lanes : 1, L.spread);
-    // a tile's blocks are dealt to as many workgroups as evens the load out (about 4096); more would add
-    // to the error of the TF gradient, which every workgroup adds to the same few FP32 words
-    uint32_t split = 1;
-    while (split < (uint32_t)lanes && blocks * split * 2u <= 4096u) split *= 2;
 #define DVR_BWD(FG, G) \
-    hipLaunchKernelGGL((k_render_bwd<LAYOUT, DT, KMAX, FG, G>), dim3(blocks, split), dim3(256), 0, st, f, g, tf, rp, L)
+    hipLaunchKernelGGL((k_render_bwd<LAYOUT, DT, KMAX, FG, G>), dim3(blocks, split.parts), dim3(256), 0, st, f, g, tf, rp, L)
     if (mode == kGather) {
         hipLaunchKernelGGL((k_render_gather<LAYOUT, DT, KMAX>), dim3(blocks), dim3(256), 0, st, f, g, tf, rp, L);
     } else if (mode == kFwd) {
@@ -283,11 +288,11 @@ static hipError_t launch_fwd_t(const KFeat &f, const KGrid &g, const KTF &tf, co
 
 template <int LAYOUT, int DT>
 static hipError_t launch_k(const KFeat &f, const KGrid &g, const KTF &tf, const KRender &rp, const KLaunch &L,
-                           hipStream_t st, int mode, int lanes)
+                           hipStream_t st, int mode, const RaySplit &split)
 {
-    if (tf.K <= 8) return launch_fwd_t<LAYOUT, DT, 8>(f, g, tf, rp, L, st, mode, lanes);
-    if (tf.K <= 16) return launch_fwd_t<LAYOUT, DT, 16>(f, g, tf, rp, L, st, mode, lanes);
-    return launch_fwd_t<LAYOUT, DT, 64>(f, g, tf, rp, L, st, mode, lanes);
+    if (tf.K <= 8) return launch_fwd_t<LAYOUT, DT, 8>(f, g, tf, rp, L, st, mode, split);
+    if (tf.K <= 16) return launch_fwd_t<LAYOUT, DT, 16>(f, g, tf, rp, L, st, mode, split);
+    return launch_fwd_t<LAYOUT, DT, 64>(f, g, tf, rp, L, st, mode, split);
 }
 
 // Lanes per ray of the adjoint.  Above about 0.4 voxels a pixel the 8 x 8 rays of a wave stop fitting its
@@ -302,6 +307,20 @@ static int bwd_lanes(const KLaunch &L, double pitch)
     return 1;
 }
 
+// Workgroups that share a tile of the adjoint: as many as give about 4096 of them live rays, which evens the
+// load out; more would add to the error of the TF gradient, which every such workgroup adds to the same few
+// FP32 words.  Those without a live ray end at once, but with feature gradients one or two fit a CU, so
+// that 65536 of them take 0.15 ms.  A head (FP16 records, 40 knots) in the middle of three 700 x 500 views of
+// 11 voxels a pixel, plain: 0.26 ms, with the parts chosen by all the tiles 1.47.
+static uint32_t bwd_parts(const KLaunch &L, const RaySplit &s, double hit)
+{
+    const double blocks = (double)tile_groups(L.W, L.H, L.ncam, 1, L.spread);
+    const double most = L.dfeat ? 16384.0 : 65536.0;  // live or not
+    uint32_t parts = 1;
+    while (parts < (uint32_t)s.lanes && blocks * hit * parts * 2.0 <= 4096.0 && blocks * parts * 2.0 <= most) parts *= 2;
+    return parts;
+}
+
 static hipError_t launch_any(const RenderArgs &a, hipStream_t st, int mode)
 {
     for (int c0 = 0; c0 < a.ncam; c0 += kCamChunk) {
@@ -309,23 +328,29 @@ static hipError_t launch_any(const RenderArgs &a, hipStream_t st, int mode)
         L.ncam = a.ncam - c0 < kCamChunk ? a.ncam - c0 : kCamChunk;
         L.cam_base = c0;
         for (int i = 0; i < L.ncam; ++i) L.cams[i] = a.cams[c0 + i];
-        double pitch = 0.0;
-        for (int i = 0; i < L.ncam; ++i) pitch = fmax(pitch, pixel_pitch(L.cams[i], L.W, L.H, a.grid));
+        ViewGeo geo = {0.0, 0.0, 0.0};
+        for (int i = 0; i < L.ncam; ++i) {
+            const ViewGeo v = view_geo(L.cams[i], L.W, L.H, a.grid);
+            geo.pitch = fmax(geo.pitch, v.pitch);
+            geo.chord = fmax(geo.chord, v.chord);
+            geo.hit += v.hit / L.ncam;
+        }
         const double rays = (double)L.W * L.H * L.ncam;
-        const int want = mode == kBwd ? bwd_lanes(L, pitch) : (mode == kFwd ? fwd_lanes(rays, a.feat.layout, a.feat.dtype, pitch) : 1);
-        const RaySplit split = fit_split({want, L.ncam % 8 != 0 ? 1u : 0u}, L.W, L.H, L.ncam, mode == kBwd);
-        const int lanes = split.lanes;
+        const int want = mode == kBwd ? bwd_lanes(L, geo.pitch)
+                                      : (mode == kFwd ? fwd_lanes(rays, a.feat.layout, a.feat.dtype, a.tf.K, geo) : 1);
+        RaySplit split = fit_split({want, L.ncam % 8 != 0 ? 1u : 0u}, L.W, L.H, L.ncam, mode == kBwd);
         L.spread = split.spread;
+        if (mode == kBwd) split.parts = bwd_parts(L, split, geo.hit);
         hipError_t e;
         const int lay = a.feat.layout, dt = a.feat.dtype;
-        if (lay == DVR_PLANAR && dt == DVR_F32) e = launch_k<DVR_PLANAR, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
-        else if (lay == DVR_PLANAR && dt == DVR_F16) e = launch_k<DVR_PLANAR, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
-        else if (lay == DVR_INTERLEAVED && dt == DVR_F32) e = launch_k<DVR_INTERLEAVED, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
-        else if (lay == DVR_INTERLEAVED && dt == DVR_F16) e = launch_k<DVR_INTERLEAVED, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
-        else if (lay == DVR_SPLIT && dt == DVR_F32) e = launch_k<DVR_SPLIT, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
-        else if (lay == DVR_SPLIT && dt == DVR_F16) e = launch_k<DVR_SPLIT, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
-        else if (lay == DVR_QUAD && dt == DVR_F32) e = launch_k<DVR_QUAD, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
-        else if (lay == DVR_QUAD && dt == DVR_F16) e = launch_k<DVR_QUAD, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, st, mode, lanes);
+        if (lay == DVR_PLANAR && dt == DVR_F32) e = launch_k<DVR_PLANAR, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, split);
+        else if (lay == DVR_PLANAR && dt == DVR_F16) e = launch_k<DVR_PLANAR, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, st, mode, split);
+        else if (lay == DVR_INTERLEAVED && dt == DVR_F32) e = launch_k<DVR_INTERLEAVED, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, split);
+        else if (lay == DVR_INTERLEAVED && dt == DVR_F16) e = launch_k<DVR_INTERLEAVED, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, st, mode, split);
+        else if (lay == DVR_SPLIT && dt == DVR_F32) e = launch_k<DVR_SPLIT, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, split);
+        else if (lay == DVR_SPLIT && dt == DVR_F16) e = launch_k<DVR_SPLIT, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, st, mode, split);
+        else if (lay == DVR_QUAD && dt == DVR_F32) e = launch_k<DVR_QUAD, DVR_F32>(a.feat, a.grid, a.tf, a.rp, L, st, mode, split);
+        else if (lay == DVR_QUAD && dt == DVR_F16) e = launch_k<DVR_QUAD, DVR_F16>(a.feat, a.grid, a.tf, a.rp, L, st, mode, split);
         else e = hipErrorInvalidValue;
         if (e != hipSuccess) return e;
     }
