@@ -91,12 +91,22 @@ inline RaySplit fit_split(RaySplit s, int W, int H, int ncam, bool adjoint)
 // cache lines; a 152 x 229 x 177 volume at 512^2 x 32 (1.35 voxels a pixel) 10.8 ms with one lane, 7.4
 // with 4, at 180^2 x 20 (3.8) 3.6, 2.05 and with 16 1.19; a 512 x 512 x 400 one at 1024^2 x 2 (0.8)
 // 3.1, 2.4.
+//
+// More lanes repeat the ray set-up and the workgroup's transfer function for every pixel, also where the ray
+// misses: three more lanes cost 33 ns a thousand rays (50 with more than 16 knots), 15 four times as much.
+// What they save is the chain of a mean ray's samples (1 us each; 0.25 from 4 lanes to 16) and, on coarse
+// views, 0.5 ps a sample (4 from 4 lanes to 16), so a volume that is thin or small in its image keeps fewer.
+// us, 1 / 4 / 16 lanes: 231 x 286 x 6 (27 samples) in three 700 x 500 views 75 / 93 / 294 over a ninth of the
+// image, 75 / 70 / 234 at 4.7 voxels a pixel, in three 1500^2 views at 1.5 131 / 328 / 1290; a head (257) in
+// two 1024^2 views over a 70th 554 / 258 / 476, in nine 2048^2 ones 1695 / 2327 / 8289.
 inline int fwd_lanes(double rays, int layout, int dtype, int K, const ViewGeo &v)
 {
-    (void)K;
     const double most16 = dtype == DVR_F16 ? 40960 : (layout == DVR_PLANAR ? 163840 : 81920);
-    if (rays <= most16 || (v.pitch > 2.5 && rays <= 1200000)) return 16;
-    return rays <= 1200000 || v.pitch > 0.6 ? 4 : 1;
+    const double setup = (K > 16 ? 5e-5 : 3.3e-5) * rays, samples = v.chord * v.hit * rays;
+    if (rays <= most16) return 16;
+    if (v.pitch > 2.5 && rays <= 1200000 && 0.25 * v.chord + 4e-6 * samples > 4.0 * setup) return 16;
+    if (rays > 1200000 && v.pitch <= 0.6) return 1;
+    return v.chord + 5e-7 * samples > setup ? 4 : 1;
 }
 
 }  // namespace dvr

@@ -88,3 +88,16 @@ def test_adjoint_of_sparse_views_is_not_slow():
         t.append(_us(lambda: dvr.render_backward(sv, f, kn, tf, prm, cams, T, k, g)))
     print(f"[sparse] adjoint, large image {t[0]:.1f} us, its middle {t[1]:.1f} us", flush=True)
     assert t[0] <= 4.0 * t[1]
+
+
+def test_render_of_sparse_views_is_not_slow():
+    """A ray that misses costs a set-up for each of its lanes, so a volume that is small in its image keeps
+    fewer of them."""
+    sv, f, kn, tf, prm = _scene((6, 56, 60), abi.DVR_SPLIT, 20)
+    large, middle = _cams(4.0, 1)
+    t = []
+    for cams in (large, middle):
+        img = dvr.render(sv, f, kn, tf, prm, cams)[0]
+        t.append(_us(lambda: dvr.render(sv, f, kn, tf, prm, cams, want_state=False, out=img)))
+    print(f"[sparse] render, large image {t[0]:.1f} us, its middle {t[1]:.1f} us", flush=True)
+    assert t[0] <= 4.0 * t[1]

@@ -62,3 +62,52 @@ def test_every_accepted_launch_fits_one_grid(tmp_path):
     cases, bad, lost, kept, lanes = map(int, _run(tmp_path, FIT).split())
     assert cases > 50000
     assert bad == 0 and lost == 0 and kept == 0 and lanes == 1
+
+
+LANES = r"""
+#include <cstdio>
+#include "lanes.hpp"
+using namespace dvr;
+// an orthographic view along z of a box of nx x ny x nz voxels of h mm, `pitch` voxels a pixel, W x H pixels
+static ViewGeo geo(int nx, int ny, int nz, float h, float pitch, int W, int H, float step)
+{
+    KGrid g;
+    const float hh[3] = {h, h, h};
+    g.n[0] = nx; g.n[1] = ny; g.n[2] = nz;
+    set_grid_steps(g, hh, step);
+    KCam c = {0, {0, 0, -100}, {0, 0, 1}, {pitch * h, 0, 0}, {0, pitch * h, 0}};
+    return view_geo(c, W, H, g);
+}
+int main()
+{
+    const ViewGeo a = geo(41, 61, 101, 0.5f, 2.0f, 100, 60, 0.5f);
+    printf("%.6f %.6f %.6f\n", a.pitch, a.chord, a.hit);
+    KGrid g;
+    const float hh[3] = {1, 1, 1};
+    g.n[0] = g.n[1] = g.n[2] = 101;
+    set_grid_steps(g, hh, 0.5f);
+    // perspective from 200 mm before the box's centre: a pixel is 0.01 rad, 2 voxels there
+    KCam c = {1, {50, 50, -150}, {-1, -1, 1}, {0.01f, 0, 0}, {0, 0.01f, 0}};
+    const ViewGeo p = view_geo(c, 200, 200, g);
+    printf("%.6f %.6f %.6f\n", p.pitch, p.chord, p.hit);
+    // lanes: few rays; a dense coarse view; a fine one; thin and small volumes in large images
+    printf("%d %d %d %d %d %d %d\n", fwd_lanes(16384, 3, 0, 8, geo(181, 217, 181, 1, 1.3f, 128, 128, 0.5f)),
+           fwd_lanes(8388608, 2, 0, 4, geo(152, 229, 177, 1, 0.4f, 512, 512, 0.5f)),
+           fwd_lanes(8388608, 2, 0, 4, geo(152, 229, 177, 1, 0.7f, 512, 512, 0.5f)),
+           fwd_lanes(648000, 0, 0, 8, geo(152, 229, 177, 1, 3.8f, 180, 180, 0.5f)),
+           fwd_lanes(6750000, 2, 0, 8, geo(231, 286, 6, 1, 1.47f, 1500, 1500, 0.5f)),
+           fwd_lanes(1050000, 2, 0, 8, geo(231, 286, 6, 1, 4.7f, 700, 500, 0.5f)),
+           fwd_lanes(37748736, 3, 0, 40, geo(181, 217, 181, 1, 2.5f, 2048, 2048, 0.5f)));
+    return 0;
+}
+"""
+
+
+@pytest.mark.skipif(not Path(HIPCC).exists(), reason="needs hipcc")
+def test_lanes_follow_what_the_view_shows(tmp_path):
+    o, p, lanes = _run(tmp_path, LANES).splitlines()
+    # 40 x 60 x 100 steps of 0.5 mm seen along z: 50 mm of 0.25 mm samples over 20 x 30 mm of 100 x 60 mm
+    assert [float(x) for x in o.split()] == pytest.approx([2.0, 200.0, 0.1], rel=1e-6)
+    # 100 mm of 0.5 mm samples over 100^2 mm^2 of (200 x 2 mm)^2 at the centre
+    assert [float(x) for x in p.split()] == pytest.approx([2.0, 200.0, 1.0 / 16.0], rel=1e-6)
+    assert [int(x) for x in lanes.split()] == [16, 1, 4, 16, 1, 1, 1]
