@@ -188,7 +188,12 @@ __global__ __launch_bounds__(256) void k_render_bwd(KFeat feat, KGrid g, KTF tf,
         // a workgroup without a live ray ends here, before it clears its window (98 KB with feature
         // gradients and 16 lanes): a 231 x 286 x 6 volume in the middle of four 512^2 views of 5 voxels a
         // pixel 0.50 -> 0.21 ms (plain 0.24 -> 0.13; with one lane a ray 0.32 and 0.17)
-        if (!__syncthreads_or(kl >= 0 && (int)(threadIdx.x & 63u) / (64 / G) / nb == (int)blockIdx.y)) return;
+        // (__syncthreads_or here: 170 VGPRs instead of 166, one wave per SIMD fewer, 7 % slower)
+        __shared__ uint32_t alive[4];
+        const uint64_t mine = __ballot(kl >= 0 && (int)(threadIdx.x & 63u) / (64 / G) / nb == (int)blockIdx.y);
+        if ((threadIdx.x & 63u) == 0) alive[threadIdx.x >> 6] = mine != 0;
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(alive[0] | alive[1] | alive[2] | alive[3]) == 0) return;
     }
     RayGeo r;
     r.N = 0;
@@ -317,7 +322,7 @@ static uint32_t bwd_parts(const KLaunch &L, const RaySplit &s, double hit)
     const double blocks = (double)tile_groups(L.W, L.H, L.ncam, 1, L.spread);
     const double most = L.dfeat ? 16384.0 : 65536.0;  // live or not
     uint32_t parts = 1;
-    while (parts < (uint32_t)s.lanes && blocks * hit * parts * 2.0 <= 4096.0 && blocks * parts * 2.0 <= most) parts *= 2;
+    while (parts < (uint32_t)s.lanes && blocks * parts * 2.0 <= most && blocks * hit * parts * 2.0 <= 4096.0) parts *= 2;
     return parts;
 }
 
