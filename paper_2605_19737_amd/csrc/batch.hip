@@ -2,9 +2,9 @@
 // graph.
 //
 //   k_batch_init   clears the stage word, the error flag and every volume's |g|_max;
-//   the feature pass of every volume with the kernels of dvr_features (features.hip), on up to kLanes
-//     parallel branches of the graph, each with a workspace of its own, so that small volumes run beside
-//     each other;
+//   the feature pass of every volume with the kernels of dvr_features (features.hip), small volumes in
+//     shared launches (features_group.hip), on up to kLanes parallel branches of the graph, each with a
+//     workspace of its own;
 //   k_batch_mark   sets the stage word once every branch is done;
 //   k_batch_rays   the tiles of every view: one workgroup a tile, each taking its view and tile from a
 //     table of blocks of 2 x 2 tiles, each view's dealt to the XCDs in turn; one launch for each number
@@ -250,6 +250,116 @@ static hipError_t capture_tail(hipStream_t st, std::vector<hipGraphNode_t> &node
     return hipSuccess;
 }
 
+// ------------------------------------------------------------------------------------------------
+// small volumes in shared launches
+
+constexpr int64_t kGroupVox = 1 << 20;   // a volume up to which it shares launches
+constexpr int64_t kGroupSum = 4 << 20;   // voxels of a group: bounds its workspace (50 MB)
+
+struct Unit {  // of the feature pass: one volume, or a group
+    int64_t vox;
+    std::vector<int> vols;
+    int lane = 0;
+};
+
+enum { kRunZ = 0, kRunXY = 1, kRunQuadV = 2, kRunQuadI = 3 };
+struct GroupRun {  // one launch of a group
+    int unit, kind, R;
+    int64_t groups;  // workgroups of its largest volume
+    size_t first;    // table rows
+    int count;
+};
+
+// Volumes whose launches can be shared: small ones whose stencil radii the shared kernels have.  The features
+// of a batch, us, launches of their own / shared in groups of 4 M / 16 M / 64 M voxels (FP32 split, one scale;
+// FP16 quads, two): 4 x 32^3 73 / 32 / 32 / 32, 120 / 53 / 53 / 53; 64 x 64^3 672 / 325 / 358 / 350, 1468 / 705 /
+// 750 / 753; 32 x 96^3 686 / 584 / 609 / 632, 1399 / 1232 / 1284 / 1408; 16 x 128^3 564 / 571 / 570 / 599, 1199 /
+// 1239 / 1287 / 1340.
+static bool groupable(const dvr_grid &g, const dvr_feature_params &fp)
+{
+    if (nvox(&g) > kGroupVox) return false;
+    for (int sc = 0; sc < fp.nsigma; ++sc) {
+        const double sg = fp.sigma_mm[sc];
+        const int rx = gauss_radius(sg / g.hx) + 1, ry = gauss_radius(sg / g.hy) + 1, rz = gauss_radius(sg / g.hz) + 1;
+        if (rx != ry || rx > kGroupRadius || rz > kGroupRadius) return false;
+    }
+    return true;
+}
+
+// The launches of unit u (ws: its workspace), their table rows appended to items: for each scale the z passes,
+// one a radius, then the x-y passes; the quads after the last scale.
+static void group_runs(const dvr_batch_desc &d, const std::vector<dvr_features_buf> &feats, int u, const Unit &unit,
+                       float *ws, std::vector<FeatItem> &items, std::vector<GroupRun> &runs)
+{
+    const dvr_feature_params &fp = d.fp;
+    const bool quad = feats[unit.vols[0]].layout == DVR_QUAD;
+    for (int sc = 0; sc < fp.nsigma; ++sc) {
+        std::vector<FeatItem> rows;
+        size_t off = 0;
+        for (int v : unit.vols) {
+            const dvr_grid &g = d.vols[v].grid;
+            dvr_features_buf out = feats[v];
+            FeatItem it;
+            it.quads = out.ves;
+            if (quad) {
+                out.layout = DVR_SPLIT;
+                out.ves = out.iquad;
+            }
+            it.a = xy_args(d.vols[v].vol, g, fp, out, ws + off, nullptr, sc, false);
+            const double sg = fp.sigma_mm[sc], h[3] = {g.hx, g.hy, g.hz};
+            for (int a = 0; a < 3; ++a) axis_taps(sg / h[a], h[a], it.taps.ax[a]);
+            it.taps.sigma2 = (float)(sg * sg);
+            rows.push_back(it);
+            off += 3 * (size_t)nvox(&g);
+        }
+        // one launch for the rows of a radius whose workgroups are within a factor of four: the others of a
+        // row end at once, but are launched
+        auto add = [&](int kind, int axis) {
+            std::vector<std::pair<int64_t, size_t>> by_size;
+            for (size_t i = 0; i < rows.size(); ++i) {
+                const int64_t nx = rows[i].a.nx, ny = rows[i].a.ny, nz = rows[i].a.nz;
+                by_size.push_back({kind == kRunZ    ? (nx * ny + 255) / 256 * ((nz + kTZ - 1) / kTZ)
+                                   : kind == kRunXY ? (nx + TX - 1) / TX * ((ny + TY - 1) / TY) * nz
+                                                    : (nx * ny * nz + 255) / 256,
+                                   i});
+            }
+            std::sort(by_size.rbegin(), by_size.rend());
+            const int lo = axis < 0 ? 0 : 2, hi = axis < 0 ? 0 : kGroupRadius;
+            for (int R = lo; R <= hi; ++R) {
+                GroupRun run = {u, kind, R, 0, 0, 0};
+                for (const auto &[n, i] : by_size) {
+                    if (axis >= 0 && rows[i].taps.ax[axis].R != R) continue;
+                    if (run.count && n * 4 < run.groups) {
+                        runs.push_back(run);
+                        run.count = 0;
+                    }
+                    if (!run.count) {
+                        run.groups = n;
+                        run.first = items.size();
+                    }
+                    items.push_back(rows[i]);
+                    ++run.count;
+                }
+                if (run.count) runs.push_back(run);
+            }
+        };
+        add(kRunZ, 2);
+        add(kRunXY, 0);
+        if (quad && sc == fp.nsigma - 1) {
+            add(kRunQuadV, -1);
+            add(kRunQuadI, -1);
+        }
+    }
+}
+
+static hipError_t launch_run(const GroupRun &g, const FeatItem *table, int dt, int layout, hipStream_t st)
+{
+    const FeatItem *t = table + g.first;
+    if (g.kind == kRunZ) return launch_group_z(t, g.count, g.groups, dt, g.R, st);
+    if (g.kind == kRunXY) return launch_group_xy(t, g.count, g.groups, dt, layout == DVR_QUAD ? DVR_SPLIT : layout, g.R, st);
+    return launch_group_quads(t, g.count, g.groups, dt, g.kind == kRunQuadI, st);
+}
+
 static void plan_free(dvr_batch *p)
 {
     if (!p) return;
@@ -386,21 +496,30 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
         for (size_t x = 0; x < 8; ++x)
             for (size_t i = 0; i < xcd[x].size(); ++i) blocks[q][i * 8 + x] = xcd[x][i];
     }
-    // the volumes' feature branches (a small volume alone leaves CUs idle): largest first to the least loaded, a workspace per branch
-    const int nlane = std::min(kLanes, d->nvol);
-    std::vector<int> order(d->nvol), lane_of(d->nvol);
-    for (int v = 0; v < d->nvol; ++v) order[v] = v;
-    std::sort(order.begin(), order.end(), [&](int a, int b) {
-        const int64_t na = nvox(&d->vols[a].grid), nb = nvox(&d->vols[b].grid);
-        return na > nb || (na == nb && a < b);
+    // The features as units of work: a large volume, or small ones whose passes share launches (features_group.hip)
+    std::vector<Unit> units;
+    std::vector<Unit> small;
+    for (int v = 0; v < d->nvol; ++v) {
+        const int64_t n = nvox(&d->vols[v].grid);
+        if (!groupable(d->vols[v].grid, fp)) {
+            units.push_back({n, {v}});
+            continue;
+        }
+        if (small.empty() || small.back().vox + n > kGroupSum) small.push_back({0, {}});
+        small.back().vox += n;
+        small.back().vols.push_back(v);
+    }
+    units.insert(units.end(), small.begin(), small.end());
+    // on branches (one alone leaves CUs idle): largest first to the least loaded, a workspace per branch
+    const int nlane = std::min(kLanes, (int)units.size());
+    std::sort(units.begin(), units.end(), [](const Unit &a, const Unit &b) {
+        return a.vox > b.vox || (a.vox == b.vox && a.vols[0] < b.vols[0]);
     });
     int64_t load[kLanes] = {}, ws_vox[kLanes] = {};
-    for (int v : order) {
-        int l = 0;
-        for (int k = 1; k < nlane; ++k) l = load[k] < load[l] ? k : l;
-        lane_of[v] = l;
-        load[l] += nvox(&d->vols[v].grid);
-        ws_vox[l] = std::max(ws_vox[l], nvox(&d->vols[v].grid));
+    for (Unit &u : units) {
+        for (int k = 1; k < nlane; ++k) u.lane = load[k] < load[u.lane] ? k : u.lane;
+        load[u.lane] += u.vox;
+        ws_vox[u.lane] = std::max(ws_vox[u.lane], u.vox);
     }
 
     dvr_batch *P = new (std::nothrow) dvr_batch();
@@ -430,6 +549,16 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
         plan_free(P);
         return fail(DVR_E_DEVICE, "device allocation of %zu bytes of workspace failed", ws_total);
     }
+    // the groups' tables: one row a volume and scale, in runs of one launch each
+    std::vector<FeatItem> items;
+    std::vector<GroupRun> runs;
+    for (size_t u = 0; u < units.size(); ++u)
+        if (units[u].vols.size() > 1) group_runs(*d, feats, (int)u, units[u], ws[units[u].lane], items, runs);
+    FeatItem *d_items = items.empty() ? nullptr : (FeatItem *)dalloc(sizeof(FeatItem) * items.size());
+    if (!items.empty() && !d_items) {
+        plan_free(P);
+        return fail(DVR_E_DEVICE, "device allocation of the feature tables failed");
+    }
     A.views = (uint64_t)(uintptr_t)d_views;
     A.ray_tile = tune.ray_tile;
     A.stage = d_ctr;
@@ -438,6 +567,8 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
     hipError_t e = hipMemcpy(d_gmax, gmax.data(), sizeof(float *) * gmax.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && !views.empty())
         e = hipMemcpy(d_views, views.data(), sizeof(BView) * views.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess && d_items)
+        e = hipMemcpy(d_items, items.data(), sizeof(FeatItem) * items.size(), hipMemcpyHostToDevice);
     for (int q = 0; q < 3 && e == hipSuccess; ++q)
         if (!blocks[q].empty())
             e = hipMemcpy(d_blocks[q], blocks[q].data(), sizeof(BBlock) * blocks[q].size(), hipMemcpyHostToDevice);
@@ -460,12 +591,17 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
                 if ((r = hipStreamUpdateCaptureDependencies(P->stream, head.data(), head.size(),
                                                             hipStreamSetCaptureDependencies)) != hipSuccess)
                     return r;
-                for (int v : order) {
-                    if (lane_of[v] != l) continue;
-                    const dvr_batch_volume &bv = d->vols[v];
-                    if ((r = enqueue_features(bv.vol, bv.vol_dtype, &bv.grid, &fp, &feats[v], nullptr, ws[l],
-                                              P->stream)) != hipSuccess)
-                        return r;
+                for (size_t u = 0; u < units.size(); ++u) {
+                    if (units[u].lane != l) continue;
+                    if (units[u].vols.size() == 1) {
+                        const int v = units[u].vols[0];
+                        const dvr_batch_volume &bv = d->vols[v];
+                        if ((r = enqueue_features(bv.vol, bv.vol_dtype, &bv.grid, &fp, &feats[v], nullptr, ws[l],
+                                                  P->stream)) != hipSuccess)
+                            return r;
+                    }
+                    for (const GroupRun &g : runs)
+                        if (g.unit == (int)u && (r = launch_run(g, d_items, fdt, layout, P->stream)) != hipSuccess) return r;
                 }
                 if ((r = capture_tail(P->stream, tails)) != hipSuccess) return r;
             }

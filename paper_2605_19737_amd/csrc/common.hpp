@@ -111,6 +111,13 @@ hipError_t launch_init_scalars(float *gmax, float *ws_scalars, hipStream_t st);
 // The six Hessian entries of one scale, [6][N] FP32 in H (z-filtered fields staged in ws_fields, 3N).
 hipError_t launch_hessian(const void *vol, int vol_dt, const dvr_grid &g, const ScaleTaps &taps, float *ws_fields,
                           float *H, hipStream_t st);
+// The passes of many small volumes (features_group.hip): n table rows of one stencil radius R in
+// [2, kGroupRadius] (z, or x and y), `groups` workgroups for the largest of them; features in the volume's dtype.
+constexpr int kGroupRadius = 10;
+struct FeatItem;
+hipError_t launch_group_z(const FeatItem *table, int n, int64_t groups, int dt, int R, hipStream_t st);
+hipError_t launch_group_xy(const FeatItem *table, int n, int64_t groups, int dt, int layout, int R, hipStream_t st);
+hipError_t launch_group_quads(const FeatItem *table, int n, int64_t groups, int dt, bool intensity, hipStream_t st);
 // Feature-pass adjoint (features_bwd.hip); the arguments are validated by the caller.
 struct FeatBwdPlan {
     int nsigma;

@@ -30,37 +30,16 @@ namespace dvr {
 // run-time radius of k_xypass took 1.19.
 constexpr int kRFastMin = 2, kRFastMax = DVR_MAX_RADIUS + 1;
 
-// z pass, (Gz, D1z, D2z) of I for every voxel: a lane takes TZ consecutive voxels of one (x, y) column
-// and keeps the TZ + 2R inputs it needs in registers, so each input is loaded (TZ + 2R) / TZ times
-// instead of 2R + 1 times.  The grid covers each z plane in 256-voxel runs (blockIdx.x, so lanes read
+// z pass (zpass_run): the grid covers each z plane in 256-voxel runs (blockIdx.x, so lanes read
 // consecutive x) and the runs of TZ planes (blockIdx.y).
 template <int DT, int R, int TZ>
 __global__ __launch_bounds__(256) void k_zpass_r(const void *__restrict__ vol, float *__restrict__ ws, int nx, int ny,
                                                  int nz, AxisTaps tz)
 {
-    const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
     const uint32_t e = blockIdx.x * 256u + threadIdx.x;
-    if (e >= plane) return;
-    const int z0 = (int)blockIdx.y * TZ;
-    const uint32_t N = plane * (uint32_t)nz;
-    const Buf b = make_buf(vol, N * ElemSize<DT>::v);
-    float col[TZ + 2 * R];
-#pragma unroll
-    for (int i = 0; i < TZ + 2 * R; ++i) col[i] = ldv<DT>(b, (uint32_t)clampi(z0 - R + i, 0, nz - 1) * plane + e);
-#pragma unroll
-    for (int k = 0; k < TZ; ++k) {
-        const int z = z0 + k;
-        if (z >= nz) break;
-        const int cls = (z == 0) ? 1 : (z == nz - 1 ? 2 : 0);
-        const Line3 o = r3<R>(tz, cls, [&](int m) { return col[k + R + m]; });
-        const uint32_t i = (uint32_t)z * plane + e;
-        ws[i] = o.g;
-        ws[N + i] = o.d1;
-        ws[2u * N + i] = o.d2;
-    }
+    if (e >= (uint32_t)nx * (uint32_t)ny) return;
+    zpass_run<DT, R, TZ>(vol, ws, nx, ny, nz, tz, e, (int)blockIdx.y * TZ);
 }
-
-constexpr int kTZ = 16;  // slices per lane of the fixed-radius z pass (8: 2-16 % slower on the head)
 
 template <int DT, int R>
 static hipError_t launch_z_r(const void *vol, float *ws, const dvr_grid &g, const AxisTaps &tz, hipStream_t st)
@@ -75,8 +54,6 @@ static hipError_t launch_z_r(const void *vol, float *ws, const dvr_grid &g, cons
         return hipGetLastError();
     }
 }
-
-constexpr int TX = 64, TY = 8;
 
 template <int DT, int OUT_DT, int LAYOUT>
 __global__ __launch_bounds__(NT) void k_xypass(XYArgs a, ScaleTaps taps)
@@ -253,16 +230,7 @@ __global__ void __launch_bounds__(256) k_quads(const T *__restrict__ src, T4 *__
                                                uint32_t ny, uint32_t nz)
 {
     const uint32_t v = blockIdx.x * 256u + threadIdx.x;
-    const uint32_t sz = nx * ny;
-    if (v >= sz * nz) return;
-    const uint32_t row = v / nx, y = row % ny, z = row / ny;
-    const bool yi = y + 1u < ny, zi = z + 1u < nz;
-    T4 q;
-    q.x = src[v];
-    q.y = yi ? src[v + nx] : T(0);
-    q.z = zi ? src[v + sz] : T(0);
-    q.w = (yi && zi) ? src[v + sz + nx] : T(0);
-    dst[v] = q;
+    if (v < nx * ny * nz) quad_of(src, dst, nx, ny, nz, v);
 }
 
 hipError_t launch_quads(const void *src, void *dst, const dvr_grid &g, int dtype, hipStream_t st)
@@ -356,29 +324,8 @@ hipError_t launch_features_scale(const void *vol, int vol_dt, const dvr_grid &g,
     hipError_t e = launch_z(vol, vol_dt, g, taps.ax[2], ws_fields, st);
     if (e != hipSuccess) return e;
 
-    XYArgs a;
-    a.ws = ws_fields;
-    a.vol = vol;
-    a.grad = out.grad;
-    a.kappa = out.kappa;
-    a.ves = out.ves;
-    a.gmax = out.gmax;
-    a.fro = ws_scalars;
-    a.nx = g.nx;
-    a.ny = g.ny;
-    a.nz = g.nz;
-    a.inv2h[0] = (float)(1.0 / (2.0 * (double)g.hx));
-    a.inv2h[1] = (float)(1.0 / (2.0 * (double)g.hy));
-    a.inv2h[2] = (float)(1.0 / (2.0 * (double)g.hz));
-    a.c_host = fp.c;
-    a.inv2a2 = (float)(1.0 / (2.0 * (double)fp.alpha * fp.alpha));
-    a.inv2b2 = (float)(1.0 / (2.0 * (double)fp.beta * fp.beta));
-    a.tau = fp.eig_gap_fp64;
-    a.first = (scale_index == 0) && !fro_pass;
-    a.fro_pass = fro_pass;
+    const XYArgs a = xy_args(vol, g, fp, out, ws_fields, ws_scalars, scale_index, fro_pass);
     const int odt = out.dtype, lay = out.layout;
-    a.odt = odt;
-    a.layout = lay;
     if (taps.ax[0].R == taps.ax[1].R) {
         // the layouts that are rendered most have kernels of their own; the others share one whose
         // storage type and layout are run-time values (2-11 % slower than its own kernel where both

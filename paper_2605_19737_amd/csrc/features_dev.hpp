@@ -372,6 +372,42 @@ struct XYArgs {
     int odt, layout;  // storage type and layout of the outputs (read where the kernel's are run-time values)
 };
 
+// Host: the arguments of one scale of dvr_features (out.layout is not DVR_QUAD, whose pass writes DVR_SPLIT).
+inline XYArgs xy_args(const void *vol, const dvr_grid &g, const dvr_feature_params &fp, const dvr_features_buf &out,
+                      const float *ws_fields, float *ws_scalars, int scale_index, bool fro_pass)
+{
+    XYArgs a;
+    a.ws = ws_fields;
+    a.vol = vol;
+    a.grad = out.grad;
+    a.kappa = out.kappa;
+    a.ves = out.ves;
+    a.gmax = out.gmax;
+    a.fro = ws_scalars;
+    a.nx = g.nx;
+    a.ny = g.ny;
+    a.nz = g.nz;
+    a.inv2h[0] = (float)(1.0 / (2.0 * (double)g.hx));
+    a.inv2h[1] = (float)(1.0 / (2.0 * (double)g.hy));
+    a.inv2h[2] = (float)(1.0 / (2.0 * (double)g.hz));
+    a.c_host = fp.c;
+    a.inv2a2 = (float)(1.0 / (2.0 * (double)fp.alpha * fp.alpha));
+    a.inv2b2 = (float)(1.0 / (2.0 * (double)fp.beta * fp.beta));
+    a.tau = fp.eig_gap_fp64;
+    a.first = (scale_index == 0) && !fro_pass;
+    a.fro_pass = fro_pass;
+    a.odt = out.dtype;
+    a.layout = out.layout;
+    return a;
+}
+
+// One scale of one volume in the tables of features_group.hip.
+struct FeatItem {
+    XYArgs a;
+    void *quads;  // DVR_QUAD: the vesselness quads (a.ves: the intensity quads, which hold the plain V first)
+    ScaleTaps taps;
+};
+
 // Stores of one voxel (index v of N) in storage type OUT_DT and layout LAYOUT.  First scale: the
 // gradient and k, and for the interleaved record the intensity; k goes to the record's second half
 // together with V (store_ves).
@@ -1022,6 +1058,52 @@ struct XYSlab {
         return vmax;
     }
 };
+
+constexpr int kTZ = 16;  // slices per lane of the fixed-radius z pass (8: 2-16 % slower on the head)
+
+// z pass of one lane, (Gz, D1z, D2z) of I: TZ consecutive voxels from slice z0 on of the (x, y) column e
+// (inside the plane); it keeps the TZ + 2R inputs it needs in registers, so each input is loaded
+// (TZ + 2R) / TZ times instead of 2R + 1 times.
+template <int DT, int R, int TZ, typename AT>
+__device__ __forceinline__ void zpass_run(const void *__restrict__ vol, float *__restrict__ ws, int nx, int ny, int nz,
+                                          const AT &tz, uint32_t e, int z0)
+{
+    const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
+    const uint32_t N = plane * (uint32_t)nz;
+    const Buf b = make_buf(vol, N * ElemSize<DT>::v);
+    float col[TZ + 2 * R];
+#pragma unroll
+    for (int i = 0; i < TZ + 2 * R; ++i) col[i] = ldv<DT>(b, (uint32_t)clampi(z0 - R + i, 0, nz - 1) * plane + e);
+#pragma unroll
+    for (int k = 0; k < TZ; ++k) {
+        const int z = z0 + k;
+        if (z >= nz) break;
+        const int cls = (z == 0) ? 1 : (z == nz - 1 ? 2 : 0);
+        const Line3 o = r3<R>(tz, cls, [&](int m) { return col[k + R + m]; });
+        const uint32_t i = (uint32_t)z * plane + e;
+        ws[i] = o.g;
+        ws[N + i] = o.d1;
+        ws[2u * N + i] = o.d2;
+    }
+}
+
+// The quad of voxel v: (src(x,y,z), src(x,y+1,z), src(x,y,z+1), src(x,y+1,z+1)), 0 past the last row or slice.
+template <typename T, typename T4>
+__device__ __forceinline__ void quad_of(const T *__restrict__ src, T4 *__restrict__ dst, uint32_t nx, uint32_t ny,
+                                        uint32_t nz, uint32_t v)
+{
+    const uint32_t sz = nx * ny;
+    const uint32_t row = v / nx, y = row % ny, z = row / ny;
+    const bool yi = y + 1u < ny, zi = z + 1u < nz;
+    T4 q;
+    q.x = src[v];
+    q.y = yi ? src[v + nx] : T(0);
+    q.z = zi ? src[v + sz] : T(0);
+    q.w = (yi && zi) ? src[v + sz + nx] : T(0);
+    dst[v] = q;
+}
+
+constexpr int TX = 64, TY = 8;  // the feature tile of dvr_features
 
 // LDS floats of the generic tile: the staged fields (whose space the four waves' compaction lists
 // reuse after the y filters) and the y-filtered fields
