@@ -232,7 +232,7 @@ struct dvr_batch {
     hipStream_t stream = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    std::vector<void *> allocs;
+    char *mem = nullptr;  // tables, stage word, workspaces
     unsigned *d_err = nullptr;
     dvr_tune tune;
 };
@@ -286,10 +286,10 @@ static bool groupable(const dvr_grid &g, const dvr_feature_params &fp)
     return true;
 }
 
-// The launches of unit u (ws: its workspace), their table rows appended to items: for each scale the z passes,
+// The launches of unit u (its workspace taken to start at address 0), their table rows appended to items: for each scale the z passes,
 // one a radius, then the x-y passes; the quads after the last scale.
 static void group_runs(const dvr_batch_desc &d, const std::vector<dvr_features_buf> &feats, int u, const Unit &unit,
-                       float *ws, std::vector<FeatItem> &items, std::vector<GroupRun> &runs)
+                       std::vector<FeatItem> &items, std::vector<GroupRun> &runs)
 {
     const dvr_feature_params &fp = d.fp;
     const bool quad = feats[unit.vols[0]].layout == DVR_QUAD;
@@ -305,7 +305,7 @@ static void group_runs(const dvr_batch_desc &d, const std::vector<dvr_features_b
                 out.layout = DVR_SPLIT;
                 out.ves = out.iquad;
             }
-            it.a = xy_args(d.vols[v].vol, g, fp, out, ws + off, nullptr, sc, false);
+            it.a = xy_args(d.vols[v].vol, g, fp, out, (const float *)(uintptr_t)(4 * off), nullptr, sc, false);
             const double sg = fp.sigma_mm[sc], h[3] = {g.hx, g.hy, g.hz};
             for (int a = 0; a < 3; ++a) axis_taps(sg / h[a], h[a], it.taps.ax[a]);
             it.taps.sigma2 = (float)(sg * sg);
@@ -366,7 +366,7 @@ static void plan_free(dvr_batch *p)
     if (p->exec) hipGraphExecDestroy(p->exec);
     if (p->graph) hipGraphDestroy(p->graph);
     if (p->stream) hipStreamDestroy(p->stream);
-    for (void *a : p->allocs) hipFree(a);
+    if (p->mem) hipFree(p->mem);
     delete p;
 }
 
@@ -525,53 +525,52 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
     dvr_batch *P = new (std::nothrow) dvr_batch();
     if (!P) return fail(DVR_E_NOMEM, "host allocation");
     P->tune = tune;
-    auto dalloc = [&](size_t bytes) -> void * {
-        void *p = nullptr;
-        if (hipMalloc(&p, bytes < 256 ? 256 : bytes) != hipSuccess) return nullptr;
-        P->allocs.push_back(p);
-        return p;
-    };
-    BView *d_views = (BView *)dalloc(sizeof(BView) * views.size());
-    BBlock *d_blocks[3];
-    bool ok = d_views != nullptr;
-    for (int q = 0; q < 3; ++q) ok = (d_blocks[q] = (BBlock *)dalloc(sizeof(BBlock) * blocks[q].size())) && ok;
-    std::vector<float *> gmax(d->nvol);
-    for (int v = 0; v < d->nvol; ++v) gmax[v] = d->vols[v].feat.gmax;
-    float **d_gmax = (float **)dalloc(sizeof(float *) * gmax.size());
-    unsigned *d_ctr = (unsigned *)dalloc(256);
-    float *ws[kLanes];
-    size_t ws_total = 0;
-    for (int l = 0; l < nlane; ++l) {
-        ws_total += 12u * (size_t)ws_vox[l];
-        ok = (ws[l] = (float *)dalloc(12u * (size_t)ws_vox[l])) && ok;
-    }
-    if (!ok || !d_gmax || !d_ctr) {
-        plan_free(P);
-        return fail(DVR_E_DEVICE, "device allocation of %zu bytes of workspace failed", ws_total);
-    }
-    // the groups' tables: one row a volume and scale, in runs of one launch each
+    // the groups' launches: their table holds a row for each volume, scale and pass (workspaces from 0 for now)
     std::vector<FeatItem> items;
     std::vector<GroupRun> runs;
     for (size_t u = 0; u < units.size(); ++u)
-        if (units[u].vols.size() > 1) group_runs(*d, feats, (int)u, units[u], ws[units[u].lane], items, runs);
-    FeatItem *d_items = items.empty() ? nullptr : (FeatItem *)dalloc(sizeof(FeatItem) * items.size());
-    if (!items.empty() && !d_items) {
+        if (units[u].vols.size() > 1) group_runs(*d, feats, (int)u, units[u], items, runs);
+    std::vector<float *> gmax(d->nvol);
+    for (int v = 0; v < d->nvol; ++v) gmax[v] = d->vols[v].feat.gmax;
+    // one allocation: the tables, which one copy fills, then the stage word and the workspaces
+    size_t bytes = 0;
+    auto place = [&](size_t n) {
+        const size_t at = bytes;
+        bytes += (n + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t at_views = place(sizeof(BView) * views.size()), at_gmax = place(sizeof(float *) * gmax.size()),
+                 at_items = place(sizeof(FeatItem) * items.size());
+    size_t at_blocks[3], at_ws[kLanes];
+    for (int q = 0; q < 3; ++q) at_blocks[q] = place(sizeof(BBlock) * blocks[q].size());
+    std::vector<char> tables(bytes);
+    const size_t at_ctr = place(256);
+    for (int l = 0; l < nlane; ++l) at_ws[l] = place(12u * (size_t)ws_vox[l]);
+    if (hipMalloc((void **)&P->mem, bytes) != hipSuccess) {
+        P->mem = nullptr;
         plan_free(P);
-        return fail(DVR_E_DEVICE, "device allocation of the feature tables failed");
+        return fail(DVR_E_DEVICE, "device allocation of %zu bytes of workspace failed", bytes);
     }
-    A.views = (uint64_t)(uintptr_t)d_views;
+    for (const GroupRun &g : runs)
+        for (int i = 0; i < g.count; ++i) {
+            XYArgs &a = items[g.first + i].a;
+            a.ws = (const float *)(P->mem + at_ws[units[g.unit].lane] + (size_t)(uintptr_t)a.ws);
+        }
+    auto fill = [&](size_t at, const void *src, size_t n) {
+        if (n) memcpy(tables.data() + at, src, n);
+    };
+    fill(at_views, views.data(), sizeof(BView) * views.size());
+    fill(at_gmax, gmax.data(), sizeof(float *) * gmax.size());
+    fill(at_items, items.data(), sizeof(FeatItem) * items.size());
+    for (int q = 0; q < 3; ++q) fill(at_blocks[q], blocks[q].data(), sizeof(BBlock) * blocks[q].size());
+    float **d_gmax = (float **)(P->mem + at_gmax);
+    const FeatItem *d_items = (const FeatItem *)(P->mem + at_items);
+    A.views = (uint64_t)(uintptr_t)(P->mem + at_views);
     A.ray_tile = tune.ray_tile;
-    A.stage = d_ctr;
-    A.err = d_ctr + 1;
+    A.stage = (unsigned *)(P->mem + at_ctr);
+    A.err = A.stage + 1;
     P->d_err = A.err;
-    hipError_t e = hipMemcpy(d_gmax, gmax.data(), sizeof(float *) * gmax.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !views.empty())
-        e = hipMemcpy(d_views, views.data(), sizeof(BView) * views.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess && d_items)
-        e = hipMemcpy(d_items, items.data(), sizeof(FeatItem) * items.size(), hipMemcpyHostToDevice);
-    for (int q = 0; q < 3 && e == hipSuccess; ++q)
-        if (!blocks[q].empty())
-            e = hipMemcpy(d_blocks[q], blocks[q].data(), sizeof(BBlock) * blocks[q].size(), hipMemcpyHostToDevice);
+    hipError_t e = hipMemcpy(P->mem, tables.data(), tables.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&P->stream, hipStreamNonBlocking);
     if (e != hipSuccess) {
         plan_free(P);
@@ -596,7 +595,7 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
                     if (units[u].vols.size() == 1) {
                         const int v = units[u].vols[0];
                         const dvr_batch_volume &bv = d->vols[v];
-                        if ((r = enqueue_features(bv.vol, bv.vol_dtype, &bv.grid, &fp, &feats[v], nullptr, ws[l],
+                        if ((r = enqueue_features(bv.vol, bv.vol_dtype, &bv.grid, &fp, &feats[v], nullptr, (float *)(P->mem + at_ws[l]),
                                                   P->stream)) != hipSuccess)
                             return r;
                     }
@@ -615,7 +614,7 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
                 // the 8 XCDs
                 const size_t per = kMaxGroups / 32 * 8;
                 for (size_t b = 0; b < blocks[q].size(); b += per) {
-                    A.blocks = (uint64_t)(uintptr_t)(d_blocks[q] + b);
+                    A.blocks = (uint64_t)(uintptr_t)(P->mem + at_blocks[q] + sizeof(BBlock) * b);
                     const size_t n = std::min(per, blocks[q].size() - b);
                     if ((r = launch_rays(A, layout, fdt, lanes_of[q], (unsigned)(4 * n), P->stream)) != hipSuccess) return r;
                 }
