@@ -391,10 +391,10 @@ dvr_status dvr_batch_launch(dvr_batch *plan, hipStream_t stream);
 /* Waits for stream and reports DVR_E_TIMEOUT if a dependency wait of the last launch expired. */
 dvr_status dvr_batch_check(dvr_batch *plan, hipStream_t stream);
 dvr_status dvr_batch_destroy(dvr_batch *plan);
-/* Picks the tile shapes: times the three ray tiles on this batch (graph replays, HIP events; another
- * xy_tile where the default's halo is refused) and returns the fastest.  With cache_path, results are
- * kept in a JSON file keyed by the batch's shape class and reused.  Synchronous; overwrites the batch's
- * outputs. */
+/* Picks the tile shapes: times the three ray tiles on this batch (graph replays, HIP events) and returns the
+ * fastest; where every view shares a ray among lanes no field has an effect, and the defaults are returned
+ * without timing.  With cache_path, results are kept in a JSON file keyed by the batch's shape class and
+ * reused.  Synchronous; timing overwrites the batch's outputs. */
 dvr_status dvr_batch_autotune(const dvr_batch_desc *desc, const char *cache_path, dvr_tune *best);
 
 #ifdef __cplusplus

@@ -391,6 +391,40 @@ static dvr_status check_tune(const dvr_tune &t)
     return DVR_OK;
 }
 
+// Lanes per ray of a view of a batch of `rays` rays.
+static int view_lanes(const dvr_batch_desc &d, const KCam &cam, int W, int H, const KGrid &g, double rays)
+{
+    return fwd_lanes(rays, d.vols[0].feat.layout, d.vols[0].feat.dtype, d.tf.K, view_geo(cam, W, H, g));
+}
+
+// Whether a view takes one lane per ray, and so tune.ray_tile has an effect.
+static bool has_one_lane(const dvr_batch_desc &d)
+{
+    double rays = 0.0;
+    for (int w = 0; w < d.nview; ++w) rays += (double)d.views[w].cam.width * d.views[w].cam.height;
+    for (int w = 0; w < d.nview; ++w) {
+        const dvr_batch_view &v = d.views[w];
+        if (v.volume < 0 || v.volume >= d.nvol) continue;
+        const dvr_grid &vg = d.vols[v.volume].grid;
+        KCam cam;
+        KGrid g;
+        const float h[3] = {vg.hx, vg.hy, vg.hz};
+        cam.persp = v.cam.persp;
+        for (int k = 0; k < 3; ++k) {
+            cam.o[k] = v.cam.o[k];
+            cam.d0[k] = v.cam.d0[k];
+            cam.du[k] = v.cam.du[k];
+            cam.dv[k] = v.cam.dv[k];
+        }
+        g.n[0] = vg.nx;
+        g.n[1] = vg.ny;
+        g.n[2] = vg.nz;
+        set_grid_steps(g, h, d.rp.step_vox);
+        if (view_lanes(d, cam, v.cam.width, v.cam.height, g, rays) == 1) return true;
+    }
+    return false;
+}
+
 extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan_out)
 {
     if (!d || !plan_out) return fail(DVR_E_NULL, "desc and plan must be non-NULL");
@@ -483,7 +517,7 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
         int64_t turn = 0;
         for (int w = 0; w < d->nview; ++w) {
             const BView &V = views[w];
-            if (fwd_lanes(rays, layout, fdt, d->tf.K, view_geo(V.cam, V.W, V.H, V.grid)) != lanes_of[q]) continue;
+            if (view_lanes(*d, V.cam, V.W, V.H, V.grid, rays) != lanes_of[q]) continue;
             const int S = (int)tile_side(lanes_of[q]), nx = (V.W + S - 1) / S, ny = (V.H + S - 1) / S;
             for (int by = 0; by < ny; by += 2)
                 for (int bx = 0; bx < nx; bx += 2, ++turn)
@@ -661,9 +695,11 @@ extern "C" dvr_status dvr_batch_destroy(dvr_batch *plan)
 }
 
 // ------------------------------------------------------------------------------------------------
-// autotuner: time candidate tile shapes on the batch itself; JSON cache keyed by shape class
+// autotuner: times the ray tiles on the batch itself; JSON cache keyed by shape class
 
-static std::string tune_key(const dvr_batch_desc *d)
+// Batches whose views all share a ray among lanes, where no field has an effect, have keys of their own: their
+// entry says nothing about a batch of the same class with finer views.
+static std::string tune_key(const dvr_batch_desc *d, bool one_lane)
 {
     double vox = 0, pix = 0;
     for (int v = 0; v < d->nvol; ++v) vox += (double)nvox(&d->vols[v].grid);
@@ -676,7 +712,8 @@ static std::string tune_key(const dvr_batch_desc *d)
     std::ostringstream k;
     k << arch.substr(0, arch.find(':')) << "|dt" << d->vols[0].feat.dtype << "|lay" << d->vols[0].feat.layout << "|ns"
       << d->fp.nsigma << "|K" << (d->tf.K <= 16 ? 16 : 64) << "|vox2^" << (int)floor(log2(std::max(vox, 1.0)))
-      << "|pix2^" << (int)floor(log2(std::max(pix, 1.0))) << "|nvol2^" << (int)floor(log2((double)d->nvol));
+      << "|pix2^" << (int)floor(log2(std::max(pix, 1.0))) << "|nvol2^" << (int)floor(log2((double)d->nvol))
+      << (one_lane ? "" : "|shared");
     return k.str();
 }
 
@@ -712,10 +749,53 @@ static void write_cache(const char *path, const std::map<std::string, dvr_tune> 
     f << "}\n";
 }
 
+// Times the three ray tiles on the batch; best_t: the defaults, then the fastest.  (The default feature tile's
+// halo fits at every radius, so no candidate is refused where a plan is not.)
+static dvr_status time_ray_tiles(const dvr_batch_desc &desc, dvr_tune &best_t)
+{
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
+        if (e0) hipEventDestroy(e0);
+        return fail(DVR_E_DEVICE, "event creation");
+    }
+    dvr_status last = DVR_OK;
+    float best_ms = INFINITY;
+    for (int r = 0; r < 3; ++r) {
+        dvr_tune t = default_tune();
+        t.ray_tile = r;
+        // one candidate: build the plan, one warm replay, then two timed replays
+        dvr_batch_desc d = desc;
+        d.tune = &t;
+        dvr_batch *p = nullptr;
+        last = dvr_batch_create(&d, &p);
+        if (last != DVR_OK) break;
+        float ms = INFINITY;
+        if (dvr_batch_launch(p, p->stream) == DVR_OK && dvr_batch_check(p, p->stream) == DVR_OK) {
+            hipEventRecord(e0, p->stream);
+            dvr_batch_launch(p, p->stream);
+            dvr_batch_launch(p, p->stream);
+            hipEventRecord(e1, p->stream);
+            if (dvr_batch_check(p, p->stream) != DVR_OK || hipEventElapsedTime(&ms, e0, e1) != hipSuccess) ms = INFINITY;
+        }
+        dvr_batch_destroy(p);
+        if (ms < best_ms) {
+            best_ms = ms;
+            best_t = t;
+        }
+    }
+    hipEventDestroy(e0);
+    hipEventDestroy(e1);
+    if (last != DVR_OK) return last;
+    return isfinite(best_ms) ? DVR_OK : fail(DVR_E_DEVICE, "no candidate tune ran");
+}
+
 extern "C" dvr_status dvr_batch_autotune(const dvr_batch_desc *desc, const char *cache_path, dvr_tune *best)
 {
     if (!desc || !best) return fail(DVR_E_NULL, "desc and best must be non-NULL");
-    const std::string key = tune_key(desc);
+    if (desc->nvol < 1 || !desc->vols) return fail(DVR_E_INVALID_ARG, "need at least one volume");
+    if (desc->nview < 0 || (desc->nview > 0 && !desc->views)) return fail(DVR_E_INVALID_ARG, "bad view array");
+    const bool one_lane = has_one_lane(*desc);
+    const std::string key = tune_key(desc, one_lane);
     std::map<std::string, dvr_tune> cache;
     if (cache_path) {
         cache = read_cache(cache_path);
@@ -725,54 +805,19 @@ extern "C" dvr_status dvr_batch_autotune(const dvr_batch_desc *desc, const char 
             return DVR_OK;
         }
     }
-    hipEvent_t e0, e1;
-    if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
-        return fail(DVR_E_DEVICE, "event creation");
-    dvr_status last = DVR_OK;
-    // one candidate: build the plan, one warm replay, then two timed replays
-    auto time_tune = [&](const dvr_tune &t) -> float {
-        dvr_batch_desc d = *desc;
-        d.tune = &t;
-        dvr_batch *p = nullptr;
-        dvr_status s = dvr_batch_create(&d, &p);
-        if (s != DVR_OK) {
-            last = s;
-            return INFINITY;  // e.g. a tile whose halo does not fit in LDS
-        }
-        float ms = INFINITY;
-        if (dvr_batch_launch(p, p->stream) == DVR_OK && dvr_batch_check(p, p->stream) == DVR_OK) {
-            hipEventRecord(e0, p->stream);
-            dvr_batch_launch(p, p->stream);
-            dvr_batch_launch(p, p->stream);
-            hipEventRecord(e1, p->stream);
-            if (dvr_batch_check(p, p->stream) == DVR_OK) {
-                hipEventElapsedTime(&ms, e0, e1);
-                ms *= 0.5f;
-            }
-        }
-        dvr_batch_destroy(p);
-        return ms;
-    };
-    // The features' kernels take no shapes from the plan, so the ray tile is what there is to choose; other
-    // feature tiles only where the default's halo is refused.
     dvr_tune best_t = default_tune();
-    float best_ms = time_tune(best_t);
-    for (int x = 1; x < 3 && !isfinite(best_ms); ++x) {
-        best_t.xy_tile = x;
-        best_ms = time_tune(best_t);
+    if (!one_lane) {
+        // nothing to choose: a plan is built for its checks alone
+        dvr_batch_desc d = *desc;
+        d.tune = &best_t;
+        dvr_batch *p = nullptr;
+        const dvr_status s = dvr_batch_create(&d, &p);
+        if (s != DVR_OK) return s;
+        dvr_batch_destroy(p);
+    } else {
+        const dvr_status s = time_ray_tiles(*desc, best_t);
+        if (s != DVR_OK) return s;
     }
-    for (int r = 1; r < 3 && isfinite(best_ms); ++r) {
-        dvr_tune t = best_t;
-        t.ray_tile = r;
-        const float ms = time_tune(t);
-        if (ms < best_ms) {
-            best_ms = ms;
-            best_t = t;
-        }
-    }
-    hipEventDestroy(e0);
-    hipEventDestroy(e1);
-    if (!isfinite(best_ms)) return last != DVR_OK ? last : fail(DVR_E_DEVICE, "no candidate tune ran");
     *best = best_t;
     if (cache_path) {
         cache[key] = best_t;
