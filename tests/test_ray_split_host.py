@@ -111,3 +111,53 @@ def test_lanes_follow_what_the_view_shows(tmp_path):
     # 100 mm of 0.5 mm samples over 100^2 mm^2 of (200 x 2 mm)^2 at the centre
     assert [float(x) for x in p.split()] == pytest.approx([2.0, 200.0, 1.0 / 16.0], rel=1e-6)
     assert [int(x) for x in lanes.split()] == [16, 1, 4, 16, 1, 1, 1]
+
+
+SCENE = r"""
+#include <cstdio>
+#include "lanes.hpp"
+using namespace dvr;
+int main()
+{
+    KGrid g;
+    const float h[3] = {@H@};
+    g.n[0] = @NX@; g.n[1] = @NY@; g.n[2] = @NZ@;
+    const KCam cams[] = {@CAMS@};
+    for (float step : {0.5f, 0.37f}) {
+        set_grid_steps(g, h, step);
+        for (int layout = 0; layout < 4; ++layout)
+            for (int dtype = 0; dtype < 2; ++dtype)
+                for (int n : {32, 8, 1})
+                    for (int i = 0; i < 32; i += n) {
+                        ViewGeo v = {0, 0, 0};
+                        for (int k = i; k < i + n; ++k) {
+                            const ViewGeo o = view_geo(cams[k], @W@, @HH@, g);
+                            v.pitch = fmax(v.pitch, o.pitch);
+                            v.chord = fmax(v.chord, o.chord);
+                            v.hit += o.hit / n;
+                        }
+                        printf("%d %d\n", n, fwd_lanes((double)@W@ * @HH@ * n, layout, dtype, 8, v));
+                    }
+    }
+    return 0;
+}
+"""
+
+
+@pytest.mark.skipif(not Path(HIPCC).exists(), reason="needs hipcc")
+@pytest.mark.parametrize("persp", [False, True])
+def test_lanes_of_the_compared_launches(tmp_path, persp):
+    """The launches of 32, 8 and 1 views that test_gpu_one_lane.py compares take 1, 4 and 16 lanes."""
+    from tests import test_gpu_one_lane as t
+
+    def vec(v):
+        return "{" + ", ".join("%.9gf" % float(x) if "." in "%.9g" % float(x) or "e" in "%.9g" % float(x) else "%.1ff" % float(x)
+                               for x in v) + "}"
+
+    cams = ", ".join("{%d, %s, %s, %s, %s}" % (c.persp, vec(c.o), vec(c.d0), vec(c.du), vec(c.dv)) for c in t.cameras(persp))
+    src = SCENE
+    for key, val in dict(H=", ".join("%.1ff" % x for x in t.SP), NX=t.SHAPE[2], NY=t.SHAPE[1], NZ=t.SHAPE[0], CAMS=cams, W=t.W,
+                         HH=t.H).items():
+        src = src.replace("@%s@" % key, str(val))
+    got = set(tuple(map(int, line.split())) for line in _run(tmp_path, src).splitlines())
+    assert got == {(32, 1), (8, 4), (1, 16)}
