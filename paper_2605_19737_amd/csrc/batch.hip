@@ -259,6 +259,7 @@ constexpr int64_t kGroupSum = 4 << 20;   // voxels of a group: bounds its worksp
 struct Unit {  // of the feature pass: one volume, or a group
     int64_t vox;
     std::vector<int> vols;
+    bool shared = false;  // the kernels of features_group.hip
     int lane = 0;
 };
 
@@ -275,9 +276,16 @@ struct GroupRun {  // one launch of a group
 // FP16 quads, two): 4 x 32^3 73 / 32 / 32 / 32, 120 / 53 / 53 / 53; 64 x 64^3 672 / 325 / 358 / 350, 1468 / 705 /
 // 750 / 753; 32 x 96^3 686 / 584 / 609 / 632, 1399 / 1232 / 1284 / 1408; 16 x 128^3 564 / 571 / 570 / 599, 1199 /
 // 1239 / 1287 / 1340.
+// A volume of more slices, or rows of tiles, than a grid has workgroups along an axis takes the shared kernels
+// whatever its size: their grid runs along x alone.
+static bool too_tall(const dvr_grid &g)
+{
+    return (unsigned)g.nz > kMaxGridYZ || (unsigned)(g.ny + TY - 1) / TY > kMaxGridYZ;
+}
+
 static bool groupable(const dvr_grid &g, const dvr_feature_params &fp)
 {
-    if (nvox(&g) > kGroupVox) return false;
+    if (nvox(&g) > kGroupVox && !too_tall(g)) return false;
     for (int sc = 0; sc < fp.nsigma; ++sc) {
         const double sg = fp.sigma_mm[sc];
         const int rx = gauss_radius(sg / g.hx) + 1, ry = gauss_radius(sg / g.hy) + 1, rz = gauss_radius(sg / g.hz) + 1;
@@ -543,6 +551,7 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
         small.back().vox += n;
         small.back().vols.push_back(v);
     }
+    for (Unit &u : small) u.shared = u.vols.size() > 1 || too_tall(d->vols[u.vols[0]].grid);
     units.insert(units.end(), small.begin(), small.end());
     // on branches (one alone leaves CUs idle): largest first to the least loaded, a workspace per branch
     const int nlane = std::min(kLanes, (int)units.size());
@@ -563,7 +572,7 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
     std::vector<FeatItem> items;
     std::vector<GroupRun> runs;
     for (size_t u = 0; u < units.size(); ++u)
-        if (units[u].vols.size() > 1) group_runs(*d, feats, (int)u, units[u], items, runs);
+        if (units[u].shared) group_runs(*d, feats, (int)u, units[u], items, runs);
     std::vector<float *> gmax(d->nvol);
     for (int v = 0; v < d->nvol; ++v) gmax[v] = d->vols[v].feat.gmax;
     // one allocation: the tables, which one copy fills, then the stage word and the workspaces
@@ -626,7 +635,7 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
                     return r;
                 for (size_t u = 0; u < units.size(); ++u) {
                     if (units[u].lane != l) continue;
-                    if (units[u].vols.size() == 1) {
+                    if (!units[u].shared) {
                         const int v = units[u].vols[0];
                         const dvr_batch_volume &bv = d->vols[v];
                         if ((r = enqueue_features(bv.vol, bv.vol_dtype, &bv.grid, &fp, &feats[v], nullptr, (float *)(P->mem + at_ws[l]),

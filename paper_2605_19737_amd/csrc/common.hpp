@@ -102,6 +102,8 @@ struct ScaleTaps {
     float sigma2;    // sigma^2 (mm^2): scale normalization of the Hessian for the eigenvalues
 };
 
+constexpr unsigned kMaxGridYZ = 65535;  // workgroups of a grid along y or z
+
 // Launchers (host side, defined in the .hip files).
 hipError_t launch_features_scale(const void *vol, int vol_dt, const dvr_grid &g, const ScaleTaps &taps,
                                  int scale_index, bool last_scale, const dvr_feature_params &fp,

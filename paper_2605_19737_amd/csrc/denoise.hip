@@ -249,8 +249,6 @@ __global__ __launch_bounds__(256) void k_median3(const void *__restrict__ in, vo
     }
 }
 
-constexpr unsigned kMaxGridYZ = 65535;  // workgroups of a grid along y or z
-
 template <int DT>
 static void launch_median(const void *vol, const dvr_grid &g, void *out, hipStream_t st)
 {

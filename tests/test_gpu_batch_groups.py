@@ -76,6 +76,30 @@ def test_more_volumes_than_one_group_holds():
     b.close()
 
 
+def test_a_volume_of_more_slices_than_a_grid_has():
+    """Two volumes of 70000 slices, one beside small ones and one above 2^20 voxels: runs of their
+    slices equal the features of a copy of those 80 slices alone, away from the copy's ends."""
+    w = phantoms.c4_volume(0, 64, 64)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    h, shapes = (1.0, 1.0, 1.0), [(70000, 2, 3), (70000, 4, 4), (20, 20, 20)]
+    vols = [torch.rand(s, generator=g, device="cuda") for s in shapes]
+    feats = [dvr.alloc_features(s, h, layout=abi.DVR_SPLIT, bricks=False) for s in shapes]
+    kn, tf = to_dev(w.tf_knots), to_dev(w.tf_rgba)
+    print("[batch groups] 70000 slices", flush=True)
+    b = dvr.Batch(vols, [h] * 3, feats, [], [1.0], kn, tf, w.params, c=w.c)
+    b.launch()
+    b.check()
+    R = 4  # stencil radius at sigma 1
+    for v, f in zip(vols[:2], feats[:2]):
+        n = v.shape[0]
+        for z0 in (0, 33333, 65500, n - 80):
+            part = v[z0:z0 + 80].clone()
+            r = dvr.features(part, h, [1.0], c=w.c, layout=abi.DVR_SPLIT)
+            lo, hi = (0 if z0 == 0 else R), (80 if z0 + 80 == n else 80 - R)
+            assert torch.equal(f.grad[z0 + lo:z0 + hi], r.grad[lo:hi]) and torch.equal(f.ves[z0 + lo:z0 + hi], r.ves[lo:hi])
+    b.close()
+
+
 def _us(f):
     f()
     best = float("inf")
