@@ -28,6 +28,7 @@
 #include <algorithm>
 #include <fstream>
 #include <map>
+#include <memory>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -433,7 +434,7 @@ static bool has_one_lane(const dvr_batch_desc &d)
     return false;
 }
 
-extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan_out)
+static dvr_status create_plan(const dvr_batch_desc *d, dvr_batch **plan_out)
 {
     if (!d || !plan_out) return fail(DVR_E_NULL, "desc and plan must be non-NULL");
     *plan_out = nullptr;
@@ -567,6 +568,7 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
 
     dvr_batch *P = new (std::nothrow) dvr_batch();
     if (!P) return fail(DVR_E_NOMEM, "host allocation");
+    std::unique_ptr<dvr_batch, void (*)(dvr_batch *)> own(P, plan_free);
     P->tune = tune;
     // the groups' launches: their table holds a row for each volume, scale and pass (workspaces from 0 for now)
     std::vector<FeatItem> items;
@@ -591,7 +593,6 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
     for (int l = 0; l < nlane; ++l) at_ws[l] = place(12u * (size_t)ws_vox[l]);
     if (hipMalloc((void **)&P->mem, bytes) != hipSuccess) {
         P->mem = nullptr;
-        plan_free(P);
         return fail(DVR_E_DEVICE, "device allocation of %zu bytes of workspace failed", bytes);
     }
     for (const GroupRun &g : runs)
@@ -616,7 +617,6 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
     hipError_t e = hipMemcpy(P->mem, tables.data(), tables.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&P->stream, hipStreamNonBlocking);
     if (e != hipSuccess) {
-        plan_free(P);
         return dev_fail(e, "batch plan setup");
     }
     e = hipStreamBeginCapture(P->stream, hipStreamCaptureModeThreadLocal);
@@ -670,11 +670,19 @@ extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan
     }
     if (e == hipSuccess) e = hipGraphInstantiate(&P->exec, P->graph, nullptr, nullptr, 0);
     if (e != hipSuccess) {
-        plan_free(P);
         return dev_fail(e, "batch graph capture");
     }
-    *plan_out = P;
+    *plan_out = own.release();
     return DVR_OK;
+}
+
+extern "C" dvr_status dvr_batch_create(const dvr_batch_desc *d, dvr_batch **plan_out)
+{
+    try {
+        return create_plan(d, plan_out);
+    } catch (const std::exception &) {  // the tables' std::bad_alloc
+        return fail(DVR_E_NOMEM, "host allocation");
+    }
 }
 
 extern "C" dvr_status dvr_batch_launch(dvr_batch *plan, hipStream_t stream)
@@ -798,7 +806,7 @@ static dvr_status time_ray_tiles(const dvr_batch_desc &desc, dvr_tune &best_t)
     return isfinite(best_ms) ? DVR_OK : fail(DVR_E_DEVICE, "no candidate tune ran");
 }
 
-extern "C" dvr_status dvr_batch_autotune(const dvr_batch_desc *desc, const char *cache_path, dvr_tune *best)
+static dvr_status autotune(const dvr_batch_desc *desc, const char *cache_path, dvr_tune *best)
 {
     if (!desc || !best) return fail(DVR_E_NULL, "desc and best must be non-NULL");
     if (desc->nvol < 1 || !desc->vols) return fail(DVR_E_INVALID_ARG, "need at least one volume");
@@ -833,4 +841,13 @@ extern "C" dvr_status dvr_batch_autotune(const dvr_batch_desc *desc, const char 
         write_cache(cache_path, cache);
     }
     return DVR_OK;
+}
+
+extern "C" dvr_status dvr_batch_autotune(const dvr_batch_desc *desc, const char *cache_path, dvr_tune *best)
+{
+    try {
+        return autotune(desc, cache_path, best);
+    } catch (const std::exception &) {
+        return fail(DVR_E_NOMEM, "host allocation");
+    }
 }
