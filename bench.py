@@ -34,7 +34,7 @@ PEAK_HBM_GBS = 8000.0
 # Algorithmic flops per raymarch sample (FMA = 2); see the design notes for the breakdown.
 FLOP_SHADED = 144
 FLOP_TRANSPARENT = 40
-RENDER_SOURCES = ["render.hip", "render_dev.hpp", "render_args.hpp", "common.hpp"]
+RENDER_SOURCES = ["render.hip", "render_dev.hpp", "render_args.hpp", "lanes.hpp", "common.hpp"]
 # Feature pass: compulsory bytes per voxel in FP32 (read I, write g, k, V) and the algorithmic flop
 # estimate per voxel at three scales (stencils, eigenvalues, vesselness; see the design notes).
 FEAT_BYTES_F32 = 24
@@ -659,10 +659,10 @@ def leg_c5(dev, stream, dvr, torch, np, log):
            "normalize_hbm_frac": 6 * raw.numel() / (t[0] / 1e3) / (PEAK_HBM_GBS * 1e9),
            "histogram_ms": th, "histogram_hbm_frac": 2 * raw.numel() / (th / 1e3) / (PEAK_HBM_GBS * 1e9),
            "tissue_peaks": pk,
-           # the median is ALU work: 388 min/max per voxel (forgetful selection over 27 values) against
-           # 256 CU x 4 SIMD x 16 lanes x 2.4 GHz = 3.93e13 32-bit operations per second
+           # the median is ALU work: 160 packed min/max for two FP16 voxels (15 sorts of three, 6 each, and a
+           # network of 70) against 256 CU x 4 SIMD x 16 lanes x 2.4 GHz = 3.93e13 32-bit operations per second
            "median3_ms": tdn, "median3_hbm_frac": 4 * raw.numel() / (tdn / 1e3) / (PEAK_HBM_GBS * 1e9),
-           "median3_alu_frac": 388.0 * raw.numel() / (tdn / 1e3) / 3.93216e13,
+           "median3_alu_frac": 80.0 * raw.numel() / (tdn / 1e3) / 3.93216e13,
            # the feature pass's compulsory bytes: read the 2-byte volume, write g, k, V in FP16 (10 B)
            "features_hbm_frac": 12 * raw.numel() / (t[1] / 1e3) / (PEAK_HBM_GBS * 1e9),
            "single_scale_fp32_features_ms": tf32,

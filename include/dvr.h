@@ -342,7 +342,8 @@ dvr_status dvr_features_backward(const void *vol, int32_t vol_dtype, const dvr_g
  * raymarch of many views of them, recorded in a HIP graph: the volumes' features on up to four
  * parallel branches, then the ray tiles of every view in one launch (one for each number of lanes per
  * ray that the views take).  A ray tile checks a stage word that the graph sets when every feature is
- * there; that wait is bounded and reports DVR_E_TIMEOUT through dvr_batch_check instead of hanging.
+ * there; that wait is bounded and reports DVR_E_TIMEOUT through dvr_batch_check instead of hanging (the
+ * graph's own order sets the word first, so that it never expires in normal use).
  * The transfer function is read from device memory at every launch: editing it needs no new plan
  * (the analogue of the paper's uniform buffers, Sec. 4). */
 
@@ -362,7 +363,7 @@ typedef struct dvr_batch_view {
 } dvr_batch_view;
 
 /* Tile shapes of a batched launch (chosen by dvr_batch_autotune or given).  All are checked; ray_tile
- * shapes the launches that give a ray one lane, the others no longer change how the work is split. */
+ * shapes the launches that give a ray one lane, the others do not change how the work is split. */
 typedef struct dvr_tune {
     int32_t wg_per_cu; /* 1..8 */
     int32_t xy_tile;   /* feature tile (x by y voxels): 0 = 64x8, 1 = 32x16, 2 = 128x4; its halo must fit 60 KB */

@@ -10,15 +10,17 @@
 //     table of blocks of 2 x 2 tiles, each view's dealt to the XCDs in turn; one launch for each number
 //     of lanes per ray (1, 4, 16) that the views take.
 //
-// Bound by the rays' gathers (features 0.7 of 6.7 ms on eight thick-slice volumes of 2.2-6.1 M voxels with
-// four 512^2 views each, split FP32).  One persistent kernel that drained a queue of feature and ray items
-// took 10.5 ms there: the feature items' 168 VGPRs held the rays to three waves a SIMD, neighbouring tiles
-// went to different XCDs, and every feature item wrote the L2 back.  The tile table in blocks of 1 / 2 x 2 /
-// 4 x 4 / 8 x 8 tiles: 11.0 / 6.69 / 6.75 / 6.98 ms; 1 / 2 / 4 feature branches: 6.86 / 6.75 / 6.69.
-// 64 such volumes, tuned, 69 -> 62 ms; one to four views of two volumes of 1-3 M voxels 3.3-4.1 times faster.
+// Bound by the rays' gathers (texture data busy on 99 % of the cycles, VALU issue 82 %; features 0.7 of 6.7 ms
+// on eight thick-slice volumes of 2.2-6.1 M voxels with four 512^2 views each, split FP32).  One persistent
+// kernel that drained a queue of feature and ray items took 10.5 ms there: the feature items' 168 VGPRs held
+// the rays to three waves a SIMD, neighbouring tiles went to different XCDs, and every feature item wrote the
+// L2 back.  The tile table in blocks of 1 / 2 x 2 / 4 x 4 / 8 x 8 tiles: 11.0 / 6.69 / 6.75 / 6.98 ms; 1 / 2 / 4
+// feature branches: 6.86 / 6.75 / 6.69.  64 such volumes, tuned, 69 -> 62 ms; one to four views of two volumes
+// of 1-3 M voxels 3.3-4.1 times faster.
 //
-// A ray tile checks that the stage word says the features are there (bounded, normally one load) and sets
-// the error flag instead of hanging.
+// A ray tile checks that the stage word says the features are there, and sets the error flag instead of
+// hanging.  The graph orders the mark before the rays, so the check is one load that finds it set: it waits, and
+// DVR_E_TIMEOUT is reported, only under the test variable DVR_BATCH_TEST_TIMEOUT.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdio.h>

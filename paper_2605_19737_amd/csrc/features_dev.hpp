@@ -803,9 +803,9 @@ struct XYTileR {
     static constexpr int NF = NST > NCW ? NST : NCW;  // the staging area, reused by the lists
 };
 
-// One 64 x TY tile of the fixed-radius pass, for a run of z slices: the loads of a slice (its staged
-// z-filtered fields with halo, the intensities of the gradient and, after the first scale, the V so
-// far) are issued into registers while the previous slice is computed.
+// One 64 x TY tile of the fixed-radius pass on one z slice: load() issues the slice's loads into registers
+// (its staged z-filtered fields with halo, the intensities of the gradient and, after the first scale, the V
+// so far), store() stages the fields in LDS, compute() filters them and writes the outputs.
 // The y-filtered fields may be written over the staged ones (F == Fy: max(NF, NFY) floats of LDS
 // instead of NF + NFY): the y filters keep their results in registers until every lane has finished
 // reading the staged rows, and a barrier separates the x filters from the epilogue's compaction
@@ -917,7 +917,7 @@ struct XYSlab {
         }
     }
 
-    // write the staged rows of the slice in flight to LDS (all F readers of the previous slice done)
+    // write the rows in flight to LDS
     __device__ __forceinline__ void store()
     {
 #pragma unroll
@@ -930,8 +930,7 @@ struct XYSlab {
         }
     }
 
-    // the filters and the epilogue of slice z from the staged rows in F, with that slice's intensities
-    // and earlier V (In, Vp: copies taken before the next slice's loads were issued)
+    // the filters and the epilogue of slice z from the staged rows in F, with its intensities and earlier V
     __device__ __forceinline__ float compute(int z, const float (&Ic)[NV][7], const float (&Vc)[NV])
     {
         const auto &tx = taps.ax[0];

@@ -1,9 +1,10 @@
 // Front-to-back raymarcher (Sec. 2.4 Eq. 4-6) and its adjoint, for gfx950.
 //
-// Mapping: one lane per ray; a wave covers an 8 x 8 pixel tile and a 256-lane workgroup a
-// 16 x 16 tile, so the lanes of a wave gather neighbouring voxels.  A lane leaves the sample loop
-// when its ray ends or terminates early; the wave leaves when every lane has (the exec mask of the
-// loop empties), which is the wave-ballot early termination.
+// Mapping: one lane per ray, or 4 or 16 where the rays are few or coarse (lanes.hpp); with one a wave
+// covers an 8 x 8 pixel tile and a 256-lane workgroup a 16 x 16 tile, so the lanes of a wave gather
+// neighbouring voxels.  A lane leaves the sample loop when its ray ends or terminates early; the wave
+// leaves when every lane has (the exec mask of the loop empties), which is the wave-ballot early
+// termination.
 //
 // Ray geometry.  The camera ray, the slab clip against [0,(n-1)h] and the segment count are
 // computed once per ray in double-float FP32 (pairs of FP32 numbers, ~48 bits, from error-free

@@ -1,5 +1,5 @@
-"""A batched plan whose host tables do not fit in memory: dvr_batch_create returns DVR_E_NOMEM, and no exception leaves the C entry (on the CPU, in a process with a bounded address space; the view
-array is never reached)."""
+"""A batched plan whose host tables do not fit in memory: dvr_batch_create returns DVR_E_NOMEM, and no exception
+leaves the C entry (on the CPU, in a process with a bounded address space; the view array is never reached)."""
 import subprocess
 import sys
 from pathlib import Path
