@@ -188,7 +188,7 @@ __global__ __launch_bounds__(256) void k_render_bwd(KFeat feat, KGrid g, KTF tf,
     if constexpr (G > 1) {
         // a workgroup without a live ray ends here, before it clears its window (98 KB with feature
         // gradients and 16 lanes): a 231 x 286 x 6 volume in the middle of four 512^2 views of 5 voxels a
-        // pixel 0.50 -> 0.21 ms (plain 0.24 -> 0.13; with one lane a ray 0.32 and 0.17)
+        // pixel 0.50 -> 0.20 ms (plain 0.24 -> 0.11; with one lane a ray 0.32 and 0.17)
         // (__syncthreads_or here: 170 VGPRs instead of 166, one wave per SIMD fewer, 7 % slower)
         __shared__ uint32_t alive[4];
         const uint64_t mine = __ballot(kl >= 0 && (int)(threadIdx.x & 63u) / (64 / G) / nb == (int)blockIdx.y);
@@ -246,11 +246,16 @@ __global__ __launch_bounds__(256) void k_render_bwd(KFeat feat, KGrid g, KTF tf,
                                                           L.dfeat, gmb);
         }
     }
+    __shared__ float gw[4];
     if constexpr (FG) {
         for (int o = 32; o > 0; o >>= 1) gmb += __shfl_xor(gmb, o, 64);
-        if ((threadIdx.x & 63) == 0 && gmb != 0.f) atomicAdd(L.dgmax, gmb);
+        if ((threadIdx.x & 63) == 0) gw[threadIdx.x >> 6] = gmb;
     }
     __syncthreads();
+    if constexpr (FG) {  // one add a workgroup: each rounds the one FP32 word
+        const double acc = ((double)gw[0] + gw[1]) + ((double)gw[2] + gw[3]);
+        if (threadIdx.x == 0 && acc != 0.0) atomicAdd(L.dgmax, (float)acc);
+    }
     for (int p = threadIdx.x; p < K * 4; p += 256) {
         double acc = 0.0;
 #pragma unroll
@@ -313,17 +318,23 @@ static int bwd_lanes(const KLaunch &L, double pitch)
     return 1;
 }
 
-// Workgroups that share a tile of the adjoint: as many as give about 4096 of them live rays, which evens the
-// load out; more would add to the error of the TF gradient, which every such workgroup adds to the same few
-// FP32 words.  Those without a live ray end at once, but with feature gradients one or two fit a CU, so
+// Workgroups that share a tile of the adjoint, which evens the load out.  Every one with a live ray adds to the
+// same few FP32 words of the TF gradient (and to dL/d|g|_max), and each add rounds them, so there are at most
+// about 1024 such workgroups, or twice as many as tiles: relative error of the TF gradient (mean and largest of
+// nine runs) of a 114 x 60 x 453 volume in six 184 x 194 views, 217 such tiles, one lane per ray 1.9e-7, 2.6e-7; 1 /
+// 4 / 8 / 16 workgroups a tile 0.6e-7, 2.1e-7, 5.5e-7, 6.1e-7 in 4.01 / 3.65 / 3.60 / 3.56 ms; of two 512^2
+// views of a head, 706 tiles, 7.2e-7, 1.4e-6; 1 / 2 / 4 a tile 4.5e-7, 3.7e-7, 8.0e-7 (largest 1.4e-6) in 4.83 /
+// 4.54 / 4.48.  Workgroups without a live ray end at once, but with feature gradients one or two fit a CU, so
 // that 65536 of them take 0.15 ms.  A head (FP16 records, 40 knots) in the middle of three 700 x 500 views of
-// 11 voxels a pixel, plain: 0.26 ms, with the parts chosen by all the tiles 1.47.
+// 11 voxels a pixel, plain: 0.22 ms, with the parts chosen by all the tiles 1.47.
 static uint32_t bwd_parts(const KLaunch &L, const RaySplit &s, double hit)
 {
-    const double blocks = (double)tile_groups(L.W, L.H, L.ncam, 1, L.spread);
+    const double blocks = (double)tile_groups(L.W, L.H, L.ncam, 1, L.spread), live = blocks * hit;
     const double most = L.dfeat ? 16384.0 : 65536.0;  // live or not
     uint32_t parts = 1;
-    while (parts < (uint32_t)s.lanes && blocks * parts * 2.0 <= most && blocks * hit * parts * 2.0 <= 4096.0) parts *= 2;
+    while (parts < (uint32_t)s.lanes && blocks * parts * 2.0 <= most &&
+           live * parts * 2.0 <= (parts == 1 ? 4096.0 : 1024.0))
+        parts *= 2;
     return parts;
 }
 
