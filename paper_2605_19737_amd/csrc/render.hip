@@ -58,12 +58,12 @@ __device__ __forceinline__ KCam load_cam(const KLaunch &L, uint32_t cam)
 // gives rows of background to some XCDs and the whole object to others, so the tiles are grouped into
 // blocks of 2 x 2, which the XCDs take in turn, rotated from one round of eight to the next so that none
 // keeps a column of the image or the centre of every view: one 1024^2 view of a head 0.81 -> 0.55 ms, two
-// 2048^2 views of a 512 x 512 x 400 volume 14.2 -> 7.9.  (Eight views of the head: 2.65 ms as whole
-// views, 2.76 dealt out; their adjoint on a 128^3 volume 3.85 against 4.23.)
+// 2048^2 views of a 512 x 512 x 400 volume 14.2 -> 7.9.  Eight views are within 5 % either way, so whole
+// views stay: the head 2.68 ms as whole views, 2.78 dealt out; eight 2048^2 views of the 512 x 512 x 400 volume
+// 30.2, 28.9; training steps on it at 1024^2 31.1, 31.9, on a 128^3 volume 5.92, 5.99.
 //
-// MORTON: a wave's rays take their pixels in
-// Morton order (bits x0 y0 x1 y1 x2 y2), so each quad of lanes (G = 1) is a 2 x 2 pixel block and each
-// row of 16 a 4 x 4 one; otherwise row-major.
+// MORTON: a wave's rays take their pixels in Morton order (bits x0 y0 x1 y1 x2 y2), so each quad of lanes
+// (G = 1) is a 2 x 2 pixel block and each row of 16 a 4 x 4 one; otherwise row-major.
 template <bool MORTON = false, int G = 1>
 __device__ __forceinline__ void pixel_of(const KLaunch &L, uint32_t &cam, int &pi, int &pj, bool &valid)
 {
