@@ -297,8 +297,8 @@ static bool groupable(const dvr_grid &g, const dvr_feature_params &fp)
     return true;
 }
 
-// The launches of unit u (its workspace taken to start at address 0), their table rows appended to items: for each scale the z passes,
-// one a radius, then the x-y passes; the quads after the last scale.
+// The launches of unit u (its workspace taken to start at address 0), their table rows appended to items: for
+// each scale the z passes, one a radius, then the x-y passes; the quads after the last scale.
 static void group_runs(const dvr_batch_desc &d, const std::vector<dvr_features_buf> &feats, int u, const Unit &unit,
                        std::vector<FeatItem> &items, std::vector<GroupRun> &runs)
 {
